@@ -26,6 +26,7 @@
 #include "batch.h"
 #include "device_ops.h"
 #include "fused_ops.h"
+#include "tail_ops.h"
 
 namespace mg {
 
@@ -288,21 +289,22 @@ __global__ __launch_bounds__(dev::TAIL_THREADS) void kb_tail(const BProb* __rest
                                                  const BState* __restrict__ state,
                                                  const int* __restrict__ wl, int Lc, int mask) {
     __shared__ dev::TailLevels<float> tl;
+    __shared__ dev::TailLds<float> m;
     FOR_ITEMS(wl)
     if (!(flags & mask) || P.L <= Lc) continue;
-    __syncthreads();  // the previous item's cycle has read tl
+    __syncthreads();  // the previous item's cycle has read tl and its LDS
     if (threadIdx.x == 0) {
         const int top = min(P.L - 1, dev::TAIL_MAX);
         for (int l = Lc; l <= top; ++l) {
             const BLevel& v = P.lv[l];
-            tl.lv[l] = dev::TailLevel<float>{v.bands32, v.x32, v.b32, v.t32, v.bs, v.n, v.N, 0};
+            tl.lv[l] = dev::TailLevel<float>{v.bands32, v.x32, v.b32, v.bs};
         }
         tl.cs = P.cs;
         tl.top = top;
         tl.Lc = Lc;
     }
     __syncthreads();
-    dev::tail_cycle<float>(tl, (float)P.omega);
+    dev::tail_cycle<float, 2>(m, tl, (float)P.omega);
     END_ITEMS
 }
 

@@ -824,195 +824,5 @@ __device__ void post_block(BlockLds<T, BR, BC>& s, const T* __restrict__ bands, 
     }
 }
 
-// ---------------------------------------------------------------- coarse tail
-// Levels at and below TAIL_MAX hold at most 33 x 33 nodes: one workgroup
-// runs the whole V(2,2) sub-cycle over them, with workgroup barriers
-// between the steps instead of kernel launches.  The bands of these levels
-// and every work vector live in LDS for the whole sub-cycle (one load of the
-// bands and of b at the top level, one store of x at the top level), so the
-// chain of dependent steps runs at LDS latency.  Per-node arithmetic is the
-// one of the separate kernels: same results, bit for bit.
-constexpr int TAIL_MAX = 5;
-constexpr int TAIL_THREADS = 1024;  // about one node of the 33 x 33 level per thread
-
-template <typename T>
-struct TailLevel {
-    const T* bands;
-    T* x;
-    T* b;
-    T* t;
-    int64_t bs;
-    int64_t n;
-    int N;
-    int pad;
-};
-
-template <typename T>
-struct TailLevels {
-    TailLevel<T> lv[TAIL_MAX + 1];  // index = level
-    CoarseSolver cs;                // coarsest solve; cs.dmask: the Dirichlet sides
-    int top;  // highest level of the tail; entered with a zero iterate
-    int Lc;
-};
-
-// LDS image of level l: 9 bands (band-major, stride n), then x with N+1
-// zeros on either side, b, and t with N+1 zeros on either side (the zeros
-// stand for the neighbours outside the grid of the band products).
-__host__ __device__ constexpr int tail_level_elems(int l) {
-    return 12 * ((1 << l) + 1) * ((1 << l) + 1) + 4 * ((1 << l) + 2);
-}
-__host__ __device__ constexpr int tail_lds_elems() {
-    int e = 0;
-    for (int l = 1; l <= TAIL_MAX; ++l) e += tail_level_elems(l);
-    return e;
-}
-
-template <typename T>
-struct TailLds {
-    T* bands;
-    T* x;
-    T* b;
-    T* t;
-    int N, n;
-    __device__ TailLds(T* lds, int Lc, int l) {
-        int off = 0;
-        for (int m = Lc; m < l; ++m) off += tail_level_elems(m);
-        N = (1 << l) + 1;
-        n = N * N;
-        const int pad = N + 1;
-        bands = lds + off;
-        x = bands + 9 * n + pad;
-        b = x + n + pad;
-        t = b + n + pad;
-    }
-};
-
-// Band product at node p of an LDS level: the fma chain of stencil_tile.
-template <typename T>
-__device__ __forceinline__ T tail_product(const TailLds<T>& v, const T* __restrict__ x, int p) {
-    T acc = T(0);
-#pragma unroll
-    for (int k = 0; k < 9; ++k)
-        acc = fma(v.bands[k * v.n + p], x[p + (k / 3 - 1) * v.N + (k % 3 - 1)], acc);
-    return acc;
-}
-
-// Damped Jacobi sweep xo = x + omega (b - A x) / a_pp on an LDS level.
-template <typename T>
-__device__ __forceinline__ void tail_jacobi(const TailLds<T>& v, const T* x, T* xo, T omega) {
-    for (int p = threadIdx.x; p < v.n; p += TAIL_THREADS) {
-        const T acc = tail_product(v, x, p);
-        xo[p] = x[p] + jacobi_div(omega * (v.b[p] - acc), v.bands[4 * v.n + p]);
-    }
-}
-
-// x_top = V(top, 0, b_top) over levels top..Lc (one workgroup of TAIL_THREADS
-// threads).
-// Elements per thread of one level's nine bands, and of the top level's b.
-__host__ __device__ constexpr int tail_band_loads(int l) {
-    return (9 * ((1 << l) + 1) * ((1 << l) + 1) + TAIL_THREADS - 1) / TAIL_THREADS;
-}
-__host__ __device__ constexpr int tail_all_loads() {
-    int c = ((1 << TAIL_MAX) + 1) * ((1 << TAIL_MAX) + 1) / TAIL_THREADS + 1;
-    for (int l = 1; l <= TAIL_MAX; ++l) c += tail_band_loads(l);
-    return c;
-}
-
-// The bands of levels Lc..top and b of level top from global memory into
-// LDS.  Every load is issued, unconditionally, before the first store (the
-// levels and the elements per thread are unrolled to constants; a load that
-// is not needed reads a valid element of the top level and is not stored), so
-// the copy costs about one memory latency instead of one per element a
-// thread moves.
-template <typename T>
-__device__ __forceinline__ void tail_load(const TailLevels<T>& tl, T* lds) {
-    T r[tail_all_loads()];
-    const TailLevel<T>& gt = tl.lv[tl.top];
-    int o = 0;
-#pragma unroll
-    for (int l = 1; l <= TAIL_MAX; ++l) {
-        const int n = ((1 << l) + 1) * ((1 << l) + 1);
-        const bool on = l >= tl.Lc && l <= tl.top;
-        const TailLevel<T>& g = tl.lv[l];
-#pragma unroll
-        for (int u = 0; u < tail_band_loads(l); ++u) {
-            const int e = (int)threadIdx.x + u * TAIL_THREADS;
-            const int ec = min(e, 9 * n - 1);
-            const int k = ec / n, p = ec - k * n;
-            r[o + u] = *(on ? g.bands + (int64_t)k * g.bs + p : gt.bands);
-        }
-        o += tail_band_loads(l);
-    }
-    constexpr int BL = ((1 << TAIL_MAX) + 1) * ((1 << TAIL_MAX) + 1) / TAIL_THREADS + 1;
-#pragma unroll
-    for (int u = 0; u < BL; ++u) {
-        const int p = (int)threadIdx.x + u * TAIL_THREADS;
-        r[o + u] = gt.b[min(p, (int)gt.n - 1)];
-    }
-    o = 0;
-#pragma unroll
-    for (int l = 1; l <= TAIL_MAX; ++l) {
-        const int n = ((1 << l) + 1) * ((1 << l) + 1);
-        if (l >= tl.Lc && l <= tl.top) {
-            const TailLds<T> v(lds, tl.Lc, l);
-#pragma unroll
-            for (int u = 0; u < tail_band_loads(l); ++u) {
-                const int e = (int)threadIdx.x + u * TAIL_THREADS;
-                if (e < 9 * n) v.bands[e] = r[o + u];
-            }
-            for (int e = threadIdx.x; e < v.N + 1; e += TAIL_THREADS) {
-                v.x[-v.N - 1 + e] = v.x[v.n + e] = T(0);
-                v.t[-v.N - 1 + e] = v.t[v.n + e] = T(0);
-            }
-        }
-        o += tail_band_loads(l);
-    }
-    {
-        const TailLds<T> v(lds, tl.Lc, tl.top);
-#pragma unroll
-        for (int u = 0; u < BL; ++u) {
-            const int p = (int)threadIdx.x + u * TAIL_THREADS;
-            if (p < v.n) v.b[p] = r[o + u];
-        }
-    }
-}
-
-template <typename T>
-__device__ void tail_cycle(const TailLevels<T>& tl, T omega) {
-    __shared__ T lds[tail_lds_elems()];
-    tail_load(tl, lds);
-    __syncthreads();
-    for (int l = tl.top; l > tl.Lc; --l) {
-        const TailLds<T> v(lds, tl.Lc, l);
-        for (int p = threadIdx.x; p < v.n; p += TAIL_THREADS)
-            jacobi_zero_elem(v.bands + 4 * v.n, v.b, v.t, p, omega);
-        __syncthreads();
-        tail_jacobi(v, v.t, v.x, omega);
-        __syncthreads();
-        for (int p = threadIdx.x; p < v.n; p += TAIL_THREADS) v.t[p] = v.b[p] - tail_product(v, v.x, p);
-        __syncthreads();
-        const TailLds<T> c(lds, tl.Lc, l - 1);
-        for (int q = threadIdx.x; q < c.n; q += TAIL_THREADS)
-            restrict_elem<T>(v.N, v.t, c.b, q % c.N, q / c.N, tl.cs.dmask);
-        __syncthreads();
-    }
-    {
-        const TailLds<T> c(lds, tl.Lc, tl.Lc);
-        coarse_block<T>(tl.cs, c.N, c.b, c.x);
-    }
-    for (int l = tl.Lc + 1; l <= tl.top; ++l) {
-        const TailLds<T> v(lds, tl.Lc, l);
-        const TailLds<T> c(lds, tl.Lc, l - 1);
-        for (int p = threadIdx.x; p < v.n; p += TAIL_THREADS) prolong_elem<T>(v.N, c.x, v.x, p % v.N, p / v.N);
-        __syncthreads();
-        tail_jacobi(v, v.x, v.t, omega);
-        __syncthreads();
-        tail_jacobi(v, v.t, v.x, omega);
-        __syncthreads();
-    }
-    const TailLds<T> v(lds, tl.Lc, tl.top);
-    for (int p = threadIdx.x; p < v.n; p += TAIL_THREADS) tl.lv[tl.top].x[p] = v.x[p];
-}
-
 }  // namespace dev
 }  // namespace mg

@@ -17,6 +17,7 @@
 #include "device_ops.h"
 #include "fused_ops.h"
 #include "mg_internal.h"
+#include "tail_ops.h"
 
 namespace mg {
 
@@ -219,7 +220,7 @@ __global__ __launch_bounds__(BLOCK) void k_reduce_segs(const double* __restrict_
 
 
 template <typename T>
-__global__ void k_coarse(dev::CoarseSolver cs, int Nc, const T* __restrict__ b,
+__global__ __launch_bounds__(64) void k_coarse(dev::CoarseSolver cs, int Nc, const T* __restrict__ b,
                          T* __restrict__ x) {
     dev::coarse_block<T>(cs, Nc, b, x);
 }
@@ -278,12 +279,22 @@ __global__ __launch_bounds__(dev::BLK_THREADS) void k_post_blk(
                                      (int)(lb % g.nstrips), (int)(lb / g.nstrips));
 }
 
-// Coarse tail: the V(2,2) sub-cycle over levels top..Lc in one workgroup.
-template <typename T>
+// Coarse tail: the V(nu_pre, nu_post) sub-cycle over levels top..Lc in one
+// workgroup (see tail_ops.h).
+template <typename T, int NU>
 __global__ __launch_bounds__(dev::TAIL_THREADS) void k_tail(dev::TailLevels<T> tl, T omega,
                                                              const double* __restrict__ guard) {
+    // The kernel arguments span several cache lines of host-written memory.
+    // Asked for here, all at once, they cost one miss; read where the cycle
+    // branches on them they cost one each.
+    asm volatile("" ::"s"(tl.lv[5].bands), "s"(tl.lv[5].b), "s"(tl.lv[5].bs), "s"(tl.lv[5].x),
+                 "s"(tl.lv[4].bands), "s"(tl.lv[4].bs), "s"(tl.lv[3].bands), "s"(tl.lv[3].bs),
+                 "s"(tl.lv[2].bands), "s"(tl.lv[2].bs), "s"(tl.cs.chol), "s"(tl.cs.m),
+                 "s"(tl.cs.dmask), "s"(tl.cs.cg), "s"(tl.top), "s"(tl.Lc), "s"(omega),
+                 "s"(guard));
     if (skipped(guard)) return;
-    dev::tail_cycle<T>(tl, omega);
+    __shared__ dev::TailLds<T> m;
+    dev::tail_cycle<T, NU>(m, tl, omega);
 }
 
 // Dense Cholesky factor (lower triangle, row-major m x m) of the coarsest
@@ -1112,8 +1123,8 @@ hipError_t launch_post(const Level& lv, const T* bands, const T* x, const T* xc,
 }
 
 template <typename T>
-hipError_t launch_tail(const Level* lv, int top, int Lc, const dev::CoarseSolver& cs, T omega,
-                       hipStream_t st, const double* guard) {
+hipError_t launch_tail(const Level* lv, int top, int Lc, const dev::CoarseSolver& cs, int nu_pre,
+                       int nu_post, T omega, hipStream_t st, const double* guard) {
     dev::TailLevels<T> tl{};
     for (int l = Lc; l <= top; ++l) {
         dev::TailLevel<T>& d = tl.lv[l];
@@ -1121,15 +1132,19 @@ hipError_t launch_tail(const Level* lv, int top, int Lc, const dev::CoarseSolver
         d.bands = std::is_same<T, float>::value ? (const T*)v.bands32 : (const T*)v.bands64;
         d.x = std::is_same<T, float>::value ? (T*)v.x32 : (T*)v.x64;
         d.b = std::is_same<T, float>::value ? (T*)v.b32 : (T*)v.b64;
-        d.t = std::is_same<T, float>::value ? (T*)v.t32 : (T*)v.t64;
         d.bs = v.bs;
-        d.n = v.n;
-        d.N = v.N;
     }
     tl.cs = cs;
     tl.top = top;
     tl.Lc = Lc;
-    hipLaunchKernelGGL(k_tail<T>, dim3(1), dim3(dev::TAIL_THREADS), 0, st, tl, omega, guard);
+    tl.nu_pre = nu_pre;
+    tl.nu_post = nu_post;
+    if (nu_pre == 2 && nu_post == 2)
+        hipLaunchKernelGGL((k_tail<T, 2>), dim3(1), dim3(dev::TAIL_THREADS), 0, st, tl, omega,
+                           guard);
+    else
+        hipLaunchKernelGGL((k_tail<T, 0>), dim3(1), dim3(dev::TAIL_THREADS), 0, st, tl, omega,
+                           guard);
     return hipGetLastError();
 }
 
@@ -1309,8 +1324,8 @@ hipError_t launch_scalar_copy(double* scal, int from, int to, hipStream_t st) {
     template hipError_t launch_post<T>(const Level&, const T*, const T*, const T*, const T*, T, \
                                        T*, double*, double*, int, double*, hipStream_t,       \
                                        const double*, RedCtl);                                \
-    template hipError_t launch_tail<T>(const Level*, int, int, const dev::CoarseSolver&, T,    \
-                                       hipStream_t, const double*);
+    template hipError_t launch_tail<T>(const Level*, int, int, const dev::CoarseSolver&, int,  \
+                                       int, T, hipStream_t, const double*);
 
 MG_INSTANTIATE(float)
 MG_INSTANTIATE(double)

@@ -280,11 +280,12 @@ template <typename T>
 hipError_t launch_post(const Level& lv, const T* bands, const T* x, const T* xc, const T* b,
                        T omega, T* xout, double* partials, double* scal, int slot, double* host,
                        hipStream_t st, const double* guard = nullptr, RedCtl ctl = {});
-// The V(2,2) sub-cycle over levels top..Lc (top <= tail_max_level(), entered
-// with a zero iterate on level top) in one workgroup.  lv is indexed by level.
+// The V(nu_pre, nu_post) sub-cycle over levels top..Lc (top <=
+// tail_max_level(), entered with a zero iterate on level top) in one
+// workgroup.  lv is indexed by level.
 template <typename T>
-hipError_t launch_tail(const Level* lv, int top, int Lc, const dev::CoarseSolver& cs, T omega,
-                       hipStream_t st, const double* guard = nullptr);
+hipError_t launch_tail(const Level* lv, int top, int Lc, const dev::CoarseSolver& cs, int nu_pre,
+                       int nu_post, T omega, hipStream_t st, const double* guard = nullptr);
 int tail_max_level();
 // Tiling of the fused passes on a level of N nodes per side: workgroup
 // width, chunk height for a pass over `count` problems, geometry of a

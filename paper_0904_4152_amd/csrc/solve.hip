@@ -155,7 +155,8 @@ hipError_t enqueue_vcycle_fused(mg_hierarchy* h, int l, T* x, const T* b, bool x
     q.bytes += (x_zero ? 11 : 12) * s * n + s * (double)lc.n;
     if (l - 1 <= tail_max_level()) {
         // every coarser level in one workgroup; same bytes as the unfused cycle there
-        MG_TRY(launch_tail<T>(h->lv, l - 1, h->Lc, coarse_solver(h), om, q.st, q.guard));
+        MG_TRY(launch_tail<T>(h->lv, l - 1, h->Lc, coarse_solver(h), 2, 2, om, q.st,
+                              q.guard));
         for (int k = h->Lc + 1; k < l; ++k) q.bytes += 84.0 * s * (double)h->lv[k].n;
     } else {
         MG_TRY(enqueue_vcycle_fused<T>(h, l - 1, LV<T>::x(lc), LV<T>::b(lc), true, omega, q,
