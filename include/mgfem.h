@@ -283,7 +283,9 @@ mg_status mg_batch_set_tile(int level, int problems, int tile_rows, int row_wave
                             int tile_cols);
 mg_status mg_batch_clear_tiles(void);
 /* The same tuning for the single-problem solver (mg_solve, mg_vcycle and
- * the fused-pass entry points read the table's entries for one problem): for
+ * the fused-pass entry points read the table's entries for one problem;
+ * without an entry they use 8 x 32 block tiles on levels of at most 513 nodes
+ * per side and above them the marching tile of least modelled cost): for
  * every level on which h's V(2,2) cycle runs fused passes, times the FP32
  * pre- and post-smoothing passes as the mixed solve runs them (reps pairs
  * per candidate, on h's FP32 work vectors) for 4, 8, 12, 16, 24, 32, 40, 48,

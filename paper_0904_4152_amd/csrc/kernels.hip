@@ -1005,6 +1005,52 @@ int fused_rh(int N, int bt, int64_t count) {
     return rh;
 }
 
+// Tiles of one problem's fused passes on a level without a tuned entry.
+//
+// Up to 513 nodes per side: block tiles of 8 x 32 nodes.  There a march is
+// bound by its chain of row steps (a pass of 4-row chunks is 13 steps of
+// ~0.5 us), a block tile by one memory latency.  Pre (zero start) / post pass
+// of L = 6, 7, 8, 9, marching -> block tiles: FP32 6.2/6.4 -> 3.9/3.6, 6.8/7.1 ->
+// 4.0/3.7, 5.9/6.3 -> 4.3/4.0, 7.6/8.4 -> 6.1/5.5 us; FP64 7.4/7.6 -> 4.5/4.1,
+// 8.1/9.1 -> 4.6/4.2, 7.4/7.5 -> 5.5/5.0, 10.6/11.5 -> 9.6/8.5 us.  At L = 10 the
+// halo (2.5 x the owned nodes) makes them slower than the best march.
+//
+// Above: the march that minimises a cost model fitted to a sweep of heights
+// and widths at L = 10, 11, 12 in both types.  A tile of rh rows takes rh + 9
+// row steps; a step takes at least `lat` (its two barriers and LDS round
+// trips), and at least `per_wave` for every wavefront the busiest compute unit
+// runs (its share of the memory and issue rate; less where the level's
+// 5 bands and vectors fit the last-level caches).  Few rows waste steps on the
+// halo, many rows leave compute units idle or unevenly loaded.  Rules before
+// (64 rows or fewer so that there are ~3500 wavefronts) -> model, pre/post:
+// FP32 L = 10 13.9/15.8 -> 11.6/10.8, L = 11 35.5/37.1 -> 34/34, L = 12 113/121
+// -> 99/103 us; FP64 L = 10 29.5/34.5 -> 18.5/20.0, L = 11 65/73 -> 56/61, L = 12
+// 237/274 -> 211/252 us.
+dev::FusedGeom single_rule(int N, int elem_bytes) {
+    if (N <= 513) return dev::block_geom(N, 1);
+    static const int kRows[] = {8, 12, 16, 24, 32, 48, 64, 96, 128, 160, 192, 224, 256};
+    constexpr int kCus = 256;
+    const bool fp64 = elem_bytes == 8;
+    const bool cached = (int64_t)N * N * elem_bytes * 8 <= (int64_t)48 << 20;
+    const double lat = fp64 ? 0.68 : 0.55;
+    const double per_wave = fp64 ? 0.175 : (cached ? 0.055 : 0.08);
+    dev::FusedGeom best{};
+    double best_us = 0.0;
+    for (int bt = dev::F_MIN_THREADS; bt <= dev::F_MAX_THREADS; bt += 64) {
+        for (int rh : kRows) {
+            const dev::FusedGeom g = dev::fused_geom(N, bt, rh);
+            const int64_t tiles = (int64_t)g.nstrips * g.nchunks;
+            const int64_t waves = (tiles + kCus - 1) / kCus * (bt / 64);
+            const double us = (rh + 9) * std::max(lat, per_wave * (double)waves);
+            if (best_us == 0.0 || us < best_us) {
+                best_us = us;
+                best = g;
+            }
+        }
+    }
+    return best;
+}
+
 // The autotuner's trial of one level (per thread: the tuner launches from
 // the calling thread only).
 static thread_local int t_trial_N = 0, t_trial_rows = 0, t_trial_bt = 0, t_trial_cols = 0;
@@ -1022,27 +1068,31 @@ static int level_of(int N) {
     return l;
 }
 
-dev::FusedGeom single_geom(int N) {
+dev::FusedGeom single_geom(int N, int elem_bytes) {
+    // the rule's choices, made once (they depend on the level and type alone)
+    struct Rules {
+        dev::FusedGeom g[2][MG_MAX_LEVEL + 1];
+        Rules() {
+            for (int l = 1; l <= MG_MAX_LEVEL; ++l)
+                for (int d = 0; d < 2; ++d) g[d][l] = single_rule((1 << l) + 1, d ? 8 : 4);
+        }
+    };
+    static const Rules rules;
+    const int l = level_of(N);
     int bt = 0, rh = 0, cols = 0;
     if (N == t_trial_N) {
         bt = t_trial_bt;
         rh = t_trial_rows;
         cols = t_trial_cols;
     } else {
-        const TileEntry te = tile_table_get(level_of(N), 1);
+        const TileEntry te = tile_table_get(l, 1);
         bt = te.bt;
         rh = te.rows;
         cols = te.cols;
     }
     if (const int shape = cols ? dev::block_shape(rh, cols) : 0) return dev::block_geom(N, shape);
-    if (!bt) bt = fused_bt(N);
-    if (!rh) rh = fused_rh(N, bt, 1);
-    return dev::fused_geom(N, bt, rh);
-}
-
-int64_t fused_tiles(int N) {
-    const dev::FusedGeom g = single_geom(N);
-    return (int64_t)g.nstrips * g.nchunks;
+    if (!rh) return rules.g[elem_bytes == 8][l];
+    return dev::fused_geom(N, bt ? bt : fused_bt(N), rh);
 }
 
 #define MG_FUSED_BT_SWITCH(bt, LAUNCH) \
@@ -1056,7 +1106,7 @@ int64_t fused_tiles(int N) {
 template <typename T>
 hipError_t launch_pre(const Level& lv, const T* bands, const T* x, bool x_zero, const T* b,
                       T omega, T* x2out, T* bc, int dmask, hipStream_t st, const double* guard) {
-    const dev::FusedGeom g = single_geom(lv.N);
+    const dev::FusedGeom g = single_geom(lv.N, sizeof(T));
     const dim3 grid(grid8((int64_t)g.nstrips * g.nchunks)), block(g.bt);
 #define PRE(BT)                                                                               \
     if (x_zero)                                                                               \
@@ -1090,7 +1140,7 @@ template <typename T>
 hipError_t launch_post(const Level& lv, const T* bands, const T* x, const T* xc, const T* b,
                        T omega, T* xout, double* partials, double* scal, int slot, double* host,
                        hipStream_t st, const double* guard, RedCtl ctl) {
-    const dev::FusedGeom g = single_geom(lv.N);
+    const dev::FusedGeom g = single_geom(lv.N, sizeof(T));
     const dim3 grid(grid8((int64_t)g.nstrips * g.nchunks)), block(g.bt);
 #define POST(BT)                                                                             \
     if (partials)                                                                            \

@@ -288,9 +288,9 @@ hipError_t launch_tail(const Level* lv, int top, int Lc, const dev::CoarseSolver
                        int nu_post, T omega, hipStream_t st, const double* guard = nullptr);
 int tail_max_level();
 // Tiling of the fused passes on a level of N nodes per side: workgroup
-// width, chunk height for a pass over `count` problems, geometry of a
-// single-problem pass, tiles per single-problem pass, and the residual
-// partials of a fused post pass (one layout for every width).
+// width and chunk height of a batched pass over `count` problems, geometry of
+// a single-problem pass, and the residual partials of a fused post pass (one
+// layout for every width).
 namespace dev {
 struct FusedGeom;
 }  // namespace dev
@@ -298,8 +298,9 @@ int fused_bt(int N);
 int fused_rh(int N, int bt, int64_t count);
 // Tiling of a single-problem fused pass: a choice under trial by the
 // autotuner (set_single_trial; 0, 0, 0 ends it), else the tile table's
-// entry for one problem at the level, else the rules.
-dev::FusedGeom single_geom(int N);
+// entry for one problem at the level, else the rule for the type's size.
+dev::FusedGeom single_geom(int N, int elem_bytes);
+dev::FusedGeom single_rule(int N, int elem_bytes);
 void set_single_trial(int N, int rows, int bt, int cols = 0);
 
 // Process-wide table of tuned tiles of the fused passes, keyed by level and
@@ -317,7 +318,6 @@ TileEntry tile_table_get(int level, int64_t problems);
 void tile_table_set(int level, int64_t problems, int rows, int bt, int cols = 0);
 void tile_table_clear();
 uint64_t tile_table_epoch();
-int64_t fused_tiles(int N);
 int64_t fused_max_norm_parts(int N);
 
 // Workgroups (= tiles) of a band-product launch and of a vector-norm launch.
