@@ -334,10 +334,10 @@ __global__ __launch_bounds__(BT) void kb_fpre(const BProb* __restrict__ probs,
     const int strip = tile % lv.nstrips, chunk = tile / lv.nstrips;
     const float om = (float)P.omega;
     if (l < P.L || state[p].first)
-        dev::pre_tile<float, true, BT>(lv.bands32, lv.bs, lv.N, lv.x32, lv.b32, om, lv.t32,
+        dev::pre_tile<float, true, BT, false>(lv.bands32, lv.bs, lv.N, lv.x32, lv.b32, om, lv.t32,
                                        P.lv[l - 1].b32, P.dmask, strip, chunk, lv.rh, lv.cw);
     else
-        dev::pre_tile<float, false, BT>(lv.bands32, lv.bs, lv.N, lv.x32, lv.b32, om, lv.t32,
+        dev::pre_tile<float, false, BT, false>(lv.bands32, lv.bs, lv.N, lv.x32, lv.b32, om, lv.t32,
                                         P.lv[l - 1].b32, P.dmask, strip, chunk, lv.rh, lv.cw);
     END_ITEMS
 }
@@ -354,10 +354,10 @@ __global__ __launch_bounds__(BT) void kb_fpost(const BProb* __restrict__ probs,
     const int strip = tile % lv.nstrips, chunk = tile / lv.nstrips;
     const float om = (float)P.omega;
     if (l == P.L)
-        dev::post_tile<float, true, BT>(lv.bands32, lv.bs, lv.N, lv.t32, P.lv[l - 1].x32, lv.b32,
+        dev::post_tile<float, true, BT, false>(lv.bands32, lv.bs, lv.N, lv.t32, P.lv[l - 1].x32, lv.b32,
                                         om, lv.x32, P.partials, strip, chunk, lv.rh, lv.cw);
     else
-        dev::post_tile<float, false, BT>(lv.bands32, lv.bs, lv.N, lv.t32, P.lv[l - 1].x32,
+        dev::post_tile<float, false, BT, false>(lv.bands32, lv.bs, lv.N, lv.t32, P.lv[l - 1].x32,
                                          lv.b32, om, lv.x32, nullptr, strip, chunk, lv.rh, lv.cw);
     END_ITEMS
 }

@@ -160,10 +160,8 @@ __device__ __forceinline__ double stencil_tile(const T* __restrict__ bands, int6
     T bk[9][W];
 #pragma unroll
     for (int k = SYM ? 4 : 0; k < 9; ++k) {
-        // band arrays are padded beyond n, so the vector load stays in bounds;
-        // with SYM the bands read again by later tiles stay cacheable
-        const VT* src = reinterpret_cast<const VT*>(bands + k * bs + p0);
-        VT v = (!SYM || k == 4) ? __builtin_nontemporal_load(src) : *src;
+        // band arrays are padded beyond n, so the vector load stays in bounds
+        const VT v = *reinterpret_cast<const VT*>(bands + k * bs + p0);
         __builtin_memcpy(bk[k], &v, sizeof(VT));
     }
     if (SYM) {
@@ -237,10 +235,16 @@ __device__ __forceinline__ double stencil_tile(const T* __restrict__ bands, int6
 // three rows of x and the previous row's bands 6, 7 and 8 that the tile
 // touches with aligned 16-byte loads (one or two per thread and row) and
 // passes band 5 to the next node through LDS, instead of per-element loads
-// of every neighbour.  Every node's operands and fma chain are those of
-// stencil_tile, so the results are the same bits.  Tiles at either end of
-// the vector take stencil_tile itself.  Every thread of the workgroup must
-// call it (barriers inside).
+// of every neighbour.  Bound by HBM: five band streams, x (and b) and the
+// output, 4.9 (FP32) and 5.25 TB/s (FP64) of those bytes at L = 12 on matrices
+// the caches do not hold (SpMV 96 and 179 us; all nine bands read 134 and 272
+// us).  The output is stored non-temporally (3-5% at L = 10 to 12); band
+// loads are not: the next row's tiles read bands 6, 7 and 8 again, and
+// non-temporal lines are gone by then (SpMV 108 and 215 us).
+// Every node's operands and fma chain are those of stencil_tile, so the
+// results are the same bits.  Tiles at either end of the vector take
+// stencil_tile itself.  Every thread of the workgroup must call it (barriers
+// inside).
 template <typename T, int OP, bool NORM, bool STORE, bool CAST = false>
 __device__ __forceinline__ double stencil_tile_staged(const T* __restrict__ bands, int64_t bs,
                                                       int N, int64_t n,
@@ -273,7 +277,7 @@ __device__ __forceinline__ double stencil_tile_staged(const T* __restrict__ band
 #pragma unroll
     for (int k = 4; k < 9; ++k) {
         const VT* src = reinterpret_cast<const VT*>(bands + k * bs + p0);
-        VT v = k == 4 ? __builtin_nontemporal_load(src) : *src;
+        const VT v = *src;
         __builtin_memcpy(bk[k], &v, sizeof(VT));
     }
     T bb[W];
@@ -350,7 +354,7 @@ __device__ __forceinline__ double stencil_tile_staged(const T* __restrict__ band
     } else if (STORE) {
         VT v;
         __builtin_memcpy(&v, res, sizeof(VT));
-        *reinterpret_cast<VT*>(out + p0) = v;
+        __builtin_nontemporal_store(v, reinterpret_cast<VT*>(out + p0));
     }
     return sq;
 }

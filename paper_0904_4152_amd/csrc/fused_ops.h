@@ -116,7 +116,19 @@ __device__ __forceinline__ T band_row_product(const T (&bk)[9], const T* __restr
 // below the grid need no checks (negative offsets wrap to huge unsigned ones).
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
 constexpr int RSRC_WORD3 = 0x00020000;  // raw (untyped) buffer access on CDNA
-constexpr int AUX_NT = 2;               // non-temporal: bands are read once
+constexpr int AUX_NT = 2;               // non-temporal
+
+// A pass over more than the last-level cache holds (STREAM, see
+// pass_streams) loads the bands and stores its iterate non-temporally, so
+// that b, x and the coarse vectors stay cached; a smaller pass finds all of
+// it in the cache from the pass before.
+template <bool STREAM, typename T>
+__device__ __forceinline__ void pass_store(T* p, T v) {
+    if (STREAM)
+        __builtin_nontemporal_store(v, p);
+    else
+        *p = v;
+}
 
 __device__ __forceinline__ rsrc_t make_rsrc(const void* base, int64_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0,
@@ -163,27 +175,17 @@ static_assert((uint64_t)((1 << MG_MAX_LEVEL) + 1) * ((1 << MG_MAX_LEVEL) + 1) * 
                   (uint64_t)OFF_NONE,
               "out-of-range offset inside a buffer");
 
-// Bands and b of one node at byte offset off; zeros when !need.  The loads
-// are issued on every lane (an unneeded lane reads past the buffer), so no
-// branch separates a load from its later use and the compiler's wait
-// counting stays exact across the loop.
-template <typename T>
-__device__ __forceinline__ void load_row(const RowRsrc<T>& R, uint32_t off, bool need,
-                                         T (&bk)[9], T& bb) {
-    const uint32_t o = need ? off : OFF_NONE;
-#pragma unroll
-    for (int k = 0; k < 9; ++k) bk[k] = bload<T, AUX_NT>(R.band[k], o);
-    bb = bload<T>(R.b, o);
-}
-
-// The diagonal and upper bands (4..8) and b of one node; the lower bands
-// are rebuilt from the neighbours' upper bands (see LowerBands).
-template <typename T>
+// The diagonal and upper bands (4..8) and b of one node at byte offset off,
+// zeros when !need; the lower bands are rebuilt from the neighbours' upper
+// bands (see LowerBands).  The loads are issued on every lane (an unneeded
+// lane reads past the buffer), so no branch separates a load from its later
+// use and the compiler's wait counting stays exact across the loop.
+template <bool STREAM, typename T>
 __device__ __forceinline__ void load_upper(const RowRsrc<T>& R, uint32_t off, bool need,
                                            T (&bk)[9], T& bb) {
     const uint32_t o = need ? off : OFF_NONE;
 #pragma unroll
-    for (int k = 4; k < 9; ++k) bk[k] = bload<T, AUX_NT>(R.band[k], o);
+    for (int k = 4; k < 9; ++k) bk[k] = bload<T, STREAM ? AUX_NT : 0>(R.band[k], o);
     bb = bload<T>(R.b, o);
 }
 
@@ -245,7 +247,7 @@ __device__ __forceinline__ uint32_t node_off(int j, int N, int col, int size) {
 // first-sweep row of phase A) and the restriction at row jx-5 (from the
 // defect row of phase A).  Every LDS row ring has three slots: a slot is
 // rewritten only in a window that no reader of its old row shares.
-template <typename T, bool XZERO, int BT>
+template <typename T, bool XZERO, int BT, bool STREAM>
 __device__ void pre_tile(const T* __restrict__ bands, int64_t bs, int N, const T* __restrict__ x,
                          const T* __restrict__ b, T omega, T* __restrict__ x2out,
                          T* __restrict__ bc, int dmask, int strip, int chunk, int rh, int cw) {
@@ -296,9 +298,9 @@ __device__ void pre_tile(const T* __restrict__ bands, int64_t bs, int N, const T
     pfx[0] = xload(js);
     pfx[1] = xload(js + 1);
     pfx[2] = xload(js + 2);
-    load_upper(R, node_off(js - 1, N, col, sizeof(T)), needb(js - 1), bk[5], bb[5]);
-    load_upper(R, node_off(js, N, col, sizeof(T)), needb(js), bk[0], bb[0]);
-    load_upper(R, node_off(js + 1, N, col, sizeof(T)), needb(js + 1), bk[1], bb[1]);
+    load_upper<STREAM>(R, node_off(js - 1, N, col, sizeof(T)), needb(js - 1), bk[5], bb[5]);
+    load_upper<STREAM>(R, node_off(js, N, col, sizeof(T)), needb(js), bk[0], bb[0]);
+    load_upper<STREAM>(R, node_off(js + 1, N, col, sizeof(T)), needb(js + 1), bk[1], bb[1]);
 #pragma unroll 1
     for (int jb = js; jb < jend; jb += 6) {
 #pragma unroll
@@ -338,7 +340,7 @@ __device__ void pre_tile(const T* __restrict__ bands, int64_t bs, int N, const T
                 D[l1][t] = (c_op3 & in_win(jd, lo3, hi3)) ? bb[bd] - acc : T(0);
             }
             // the bands of row jx+2 into the slot row jd no longer needs
-            load_upper(R, node_off(jx + 2, N, col, sizeof(T)), needb(jx + 2), bk[bd], bb[bd]);
+            load_upper<STREAM>(R, node_off(jx + 2, N, col, sizeof(T)), needb(jx + 2), bk[bd], bb[bd]);
             __syncthreads();
             // ---- phase B
             // second sweep at row j2 (written on owned nodes)
@@ -346,7 +348,8 @@ __device__ void pre_tile(const T* __restrict__ bands, int64_t bs, int N, const T
                 const T acc = band_row_product(bk[b2], A[x3], A[l2], A[l1], t);
                 T v = A[l2][t] + jacobi_div(omega * (bb[b2] - acc), bk[b2][4]);
                 v = (c_op2 & in_win(j2, lo2, hi2)) ? v : T(0);
-                if (in_win(j2, r0, r1) && c_own) x2out[(int64_t)j2 * N + col] = v;
+                if (in_win(j2, r0, r1) && c_own)
+                    pass_store<STREAM>(x2out + (int64_t)j2 * N + col, v);
                 B[l2][t] = v;
             }
             // restriction of defect rows jr-1, jr, jr+1 to coarse row jr/2
@@ -385,7 +388,7 @@ __host__ __device__ inline int64_t fused_norm_parts(int N) {
 // heights nor the strip widths change a bit of it.  Same register ring as
 // pre_tile; a barrier before each of the first sweep (row jx-1), the second
 // (row jx-2) and the norm (row jx-3).
-template <typename T, bool NORM, int BT>
+template <typename T, bool NORM, int BT, bool STREAM>
 __device__ void post_tile(const T* __restrict__ bands, int64_t bs, int N, const T* __restrict__ x,
                           const T* __restrict__ xc, const T* __restrict__ b, T omega,
                           T* __restrict__ xout, double* __restrict__ rowpart, int strip, int chunk,
@@ -470,10 +473,10 @@ __device__ void post_tile(const T* __restrict__ bands, int64_t bs, int N, const 
     xrow_load(jstart, pfx[0], pc0[0], pc1[0], pc2[0], pc3[0]);
     xrow_load(jstart + 1, pfx[1], pc0[1], pc1[1], pc2[1], pc3[1]);
     if (AHEAD == 3) xrow_load(jstart + 2, pfx[2], pc0[2], pc1[2], pc2[2], pc3[2]);
-    load_upper(R, node_off(jstart - 1, N, col, sizeof(T)), needb(jstart - 1), bk[5], bb[5]);
-    load_upper(R, node_off(jstart, N, col, sizeof(T)), needb(jstart), bk[0], bb[0]);
+    load_upper<STREAM>(R, node_off(jstart - 1, N, col, sizeof(T)), needb(jstart - 1), bk[5], bb[5]);
+    load_upper<STREAM>(R, node_off(jstart, N, col, sizeof(T)), needb(jstart), bk[0], bb[0]);
     if (AHEAD == 3)
-        load_upper(R, node_off(jstart + 1, N, col, sizeof(T)), needb(jstart + 1), bk[1], bb[1]);
+        load_upper<STREAM>(R, node_off(jstart + 1, N, col, sizeof(T)), needb(jstart + 1), bk[1], bb[1]);
 #pragma unroll 1
     for (int jb = jstart; jb < jend; jb += 6) {
 #pragma unroll
@@ -491,7 +494,7 @@ __device__ void post_tile(const T* __restrict__ bands, int64_t bs, int N, const 
                 const int xs = (x3 + AHEAD) % 3;
                 xrow_load(jx + AHEAD, pfx[xs], pc0[xs], pc1[xs], pc2[xs], pc3[xs]);
             }
-            load_upper(R, node_off(jx + AHEAD - 1, N, col, sizeof(T)), needb(jx + AHEAD - 1),
+            load_upper<STREAM>(R, node_off(jx + AHEAD - 1, N, col, sizeof(T)), needb(jx + AHEAD - 1),
                        bk[(ph + AHEAD - 1) % 6], bb[(ph + AHEAD - 1) % 6]);
             __syncthreads();
             if (NORM && pend >= 0) {
@@ -511,7 +514,8 @@ __device__ void post_tile(const T* __restrict__ bands, int64_t bs, int N, const 
                 const T acc = band_row_product(bk[b2], A[x3], A[l2], A[l1], t);
                 T v = A[l2][t] + jacobi_div(omega * (bb[b2] - acc), bk[b2][4]);
                 v = (c_op2 & in_win(j2, lo2, hi2)) ? v : T(0);
-                if (in_win(j2, r0, r1) && c_own) xout[(int64_t)j2 * N + col] = v;
+                if (in_win(j2, r0, r1) && c_own)
+                    pass_store<STREAM>(xout + (int64_t)j2 * N + col, v);
                 if (NORM) B[l2][t] = v;
             }
             if (NORM) __syncthreads();

@@ -5,10 +5,10 @@
 //
 // All band-streaming kernels are HBM-bandwidth bound (about 0.2-0.4 flop per
 // byte), so they use no matrix cores: each thread owns 16 contiguous bytes of
-// every band (4 floats or 2 doubles), bands are read with non-temporal loads
-// (single use), the x halo of the three grid rows comes through L1/L2, and
-// workgroups are renumbered so that each XCD walks a contiguous part of the
-// grid (its L2 then sees the row reuse of x).
+// every band (4 floats or 2 doubles), the x halo of the three grid rows and
+// the lower bands (shifted upper bands) come through L1/L2, and workgroups
+// are renumbered so that each XCD walks a contiguous part of the grid (its L2
+// then sees the row reuse).
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
@@ -93,8 +93,10 @@ __device__ void red_control(const RedCtl& c, double* __restrict__ scal, double* 
     }
 }
 
-// One tile per workgroup of the band product family (see dev::stencil_tile).
-template <typename T, int OP, bool NORM, bool STORE, bool SYM = false>
+// One tile per workgroup of the band product family: SMALL reads all nine
+// bands (dev::stencil_tile), else five bands go through LDS
+// (dev::stencil_tile_staged); see small_product.
+template <typename T, int OP, bool NORM, bool STORE, bool SMALL>
 __global__ __launch_bounds__(BLOCK) void k_stencil(const T* __restrict__ bands, int64_t bs,
                                                    int N, int64_t n, const T* __restrict__ x,
                                                    const T* __restrict__ b,
@@ -105,10 +107,10 @@ __global__ __launch_bounds__(BLOCK) void k_stencil(const T* __restrict__ bands, 
     if (lb < 0 || skipped(guard)) return;
     const int64_t blo = lb * (int64_t)dev::tile_rows<T>();
     double sq;
-    if constexpr (SYM)
-        sq = dev::stencil_tile_staged<T, OP, NORM, STORE>(bands, bs, N, n, x, b, out, omega, blo);
+    if constexpr (SMALL)
+        sq = dev::stencil_tile<T, OP, NORM, STORE>(bands, bs, N, n, x, b, out, omega, blo);
     else
-        sq = dev::stencil_tile<T, OP, NORM, STORE, SYM>(bands, bs, N, n, x, b, out, omega, blo);
+        sq = dev::stencil_tile_staged<T, OP, NORM, STORE>(bands, bs, N, n, x, b, out, omega, blo);
     if (NORM) {
         const double s = dev::block_sum(sq);
         if (threadIdx.x == 0) partials[lb] = s;
@@ -118,6 +120,7 @@ __global__ __launch_bounds__(BLOCK) void k_stencil(const T* __restrict__ bands, 
 // The mixed scheme's FP64 defect (k_stencil's SYM defect with the norm),
 // d written as float(d sc) into the FP32 right-hand side, sc =
 // pow2_scale(||b||).
+template <bool SMALL>
 __global__ __launch_bounds__(BLOCK) void k_defect_cast(const double* __restrict__ bands,
                                                        int64_t bs, int N, int64_t n,
                                                        const double* __restrict__ x,
@@ -130,8 +133,14 @@ __global__ __launch_bounds__(BLOCK) void k_defect_cast(const double* __restrict_
     const int64_t lb = xcd_block(nblk);
     if (lb < 0 || skipped(guard)) return;
     const dev::Cast32 cast{d32, dev::pow2_scale(scal[SC_B + 1])};
-    const double sq = dev::stencil_tile_staged<double, OP_DEFECT, true, true, true>(
-        bands, bs, N, n, x, b, nullptr, 0.0, lb * (int64_t)dev::tile_rows<double>(), cast);
+    const int64_t blo = lb * (int64_t)dev::tile_rows<double>();
+    double sq;
+    if constexpr (SMALL)
+        sq = dev::stencil_tile<double, OP_DEFECT, true, true, false, true>(
+            bands, bs, N, n, x, b, nullptr, 0.0, blo, cast);
+    else
+        sq = dev::stencil_tile_staged<double, OP_DEFECT, true, true, true>(
+            bands, bs, N, n, x, b, nullptr, 0.0, blo, cast);
     const double s = dev::block_sum(sq);
     if (threadIdx.x == 0) partials[lb] = s;
 }
@@ -227,7 +236,7 @@ __global__ __launch_bounds__(64) void k_coarse(dev::CoarseSolver cs, int Nc, con
 
 // Fused pre-smoothing pass: one (strip, chunk) tile per workgroup of BT
 // threads.
-template <typename T, bool XZERO, int BT>
+template <typename T, bool XZERO, int BT, bool STREAM>
 __global__ __launch_bounds__(BT) void k_pre(const T* __restrict__ bands, int64_t bs, int N,
                                             const T* __restrict__ x, const T* __restrict__ b,
                                             T omega, T* __restrict__ x2out, T* __restrict__ bc,
@@ -235,14 +244,14 @@ __global__ __launch_bounds__(BT) void k_pre(const T* __restrict__ bands, int64_t
                                             const double* __restrict__ guard) {
     const int64_t lb = xcd_block((int64_t)g.nstrips * g.nchunks);
     if (lb < 0 || skipped(guard)) return;
-    dev::pre_tile<T, XZERO, BT>(bands, bs, N, x, b, omega, x2out, bc, dmask,
+    dev::pre_tile<T, XZERO, BT, STREAM>(bands, bs, N, x, b, omega, x2out, bc, dmask,
                                 (int)(lb % g.nstrips), (int)(lb / g.nstrips), g.rh, g.cw);
 }
 
 // Fused post-smoothing pass; with NORM the residual partials of
 // dev::post_tile (one per group of F_NORM_ROWS rows and F_NORM_COLS
 // columns, dev::fused_norm_parts(N) in all).
-template <typename T, bool NORM, int BT>
+template <typename T, bool NORM, int BT, bool STREAM>
 __global__ __launch_bounds__(BT) void k_post(const T* __restrict__ bands, int64_t bs, int N,
                                              const T* __restrict__ x, const T* __restrict__ xc,
                                              const T* __restrict__ b, T omega,
@@ -250,7 +259,7 @@ __global__ __launch_bounds__(BT) void k_post(const T* __restrict__ bands, int64_
                                              dev::FusedGeom g, const double* __restrict__ guard) {
     const int64_t lb = xcd_block((int64_t)g.nstrips * g.nchunks);
     if (lb < 0 || skipped(guard)) return;
-    dev::post_tile<T, NORM, BT>(bands, bs, N, x, xc, b, omega, xout, partials,
+    dev::post_tile<T, NORM, BT, STREAM>(bands, bs, N, x, xc, b, omega, xout, partials,
                                 (int)(lb % g.nstrips), (int)(lb / g.nstrips), g.rh, g.cw);
 }
 
@@ -912,18 +921,30 @@ hipError_t launch_rhs_uniform(int N, uint64_t seed, int dmask, double* b, double
     return hipGetLastError();
 }
 
+// A band product reads all nine bands of a matrix of at most 12 MB (9.5 MB: FP32
+// at L = 9): they come from the caches, and the staged tile's two barriers cost
+// more than the four bands it saves (SpMV L = 8 FP32 3.1 against 3.8 us, FP64 2.6
+// against 3.1; from L = 9 FP64, 19 MB, 4.7 against 4.4, and L = 10 FP32, 38 MB, 8.5
+// against 7.1, the staged tile is faster).
+static bool small_product(int64_t n, int elem_bytes) {
+    return n * 9 * elem_bytes <= (int64_t)12 << 20;
+}
+#define MG_STENCIL(T, OP, NORM, STORE, ...)                                                    \
+    do {                                                                                       \
+        const dim3 g_(grid8(nb)), b_(BLOCK);                                                   \
+        if (small_product(lv.n, sizeof(T)))                                                    \
+            hipLaunchKernelGGL((k_stencil<T, OP, NORM, STORE, true>), g_, b_, 0, st,           \
+                               __VA_ARGS__);                                                   \
+        else                                                                                   \
+            hipLaunchKernelGGL((k_stencil<T, OP, NORM, STORE, false>), g_, b_, 0, st,          \
+                               __VA_ARGS__);                                                   \
+    } while (0)
+
 template <typename T>
-hipError_t launch_spmv(const Level& lv, const T* bands, const T* x, T* y, hipStream_t st,
-                       bool sym) {
+hipError_t launch_spmv(const Level& lv, const T* bands, const T* x, T* y, hipStream_t st) {
     const int64_t nb = stencil_blocks(lv.n, sizeof(T));
-    if (sym)
-        hipLaunchKernelGGL((k_stencil<T, OP_SPMV, false, true, true>), dim3(grid8(nb)),
-                           dim3(BLOCK), 0, st, bands, lv.bs, lv.N, lv.n, x, (const T*)nullptr, y,
-                           T(0), (double*)nullptr, nb, (const double*)nullptr);
-    else
-        hipLaunchKernelGGL((k_stencil<T, OP_SPMV, false, true>), dim3(grid8(nb)), dim3(BLOCK), 0,
-                           st, bands, lv.bs, lv.N, lv.n, x, (const T*)nullptr, y, T(0),
-                           (double*)nullptr, nb, (const double*)nullptr);
+    MG_STENCIL(T, OP_SPMV, false, true, bands, lv.bs, lv.N, lv.n, x, (const T*)nullptr, y, T(0),
+               (double*)nullptr, nb, (const double*)nullptr);
     return hipGetLastError();
 }
 
@@ -932,16 +953,15 @@ hipError_t launch_defect(const Level& lv, const T* bands, const T* b, const T* x
                          double* partials, double* scal, int slot, double* host, hipStream_t st,
                          const double* guard, RedCtl ctl) {
     const int64_t nb = stencil_blocks(lv.n, sizeof(T));
-    const dim3 g(grid8(nb)), blk(BLOCK);
     if (partials && d)
-        hipLaunchKernelGGL((k_stencil<T, OP_DEFECT, true, true, true>), g, blk, 0, st, bands,
-                           lv.bs, lv.N, lv.n, x, b, d, T(0), partials, nb, guard);
+        MG_STENCIL(T, OP_DEFECT, true, true, bands, lv.bs, lv.N, lv.n, x, b, d, T(0), partials, nb,
+                   guard);
     else if (partials)
-        hipLaunchKernelGGL((k_stencil<T, OP_DEFECT, true, false, true>), g, blk, 0, st, bands,
-                           lv.bs, lv.N, lv.n, x, b, (T*)nullptr, T(0), partials, nb, guard);
+        MG_STENCIL(T, OP_DEFECT, true, false, bands, lv.bs, lv.N, lv.n, x, b, (T*)nullptr, T(0),
+                   partials, nb, guard);
     else
-        hipLaunchKernelGGL((k_stencil<T, OP_DEFECT, false, true, true>), g, blk, 0, st, bands,
-                           lv.bs, lv.N, lv.n, x, b, d, T(0), (double*)nullptr, nb, guard);
+        MG_STENCIL(T, OP_DEFECT, false, true, bands, lv.bs, lv.N, lv.n, x, b, d, T(0),
+                   (double*)nullptr, nb, guard);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !partials) return e;
     return launch_reduce(partials, nb, scal, slot, host, st, guard, ctl);
@@ -951,9 +971,8 @@ template <typename T>
 hipError_t launch_jacobi(const Level& lv, const T* bands, const T* b, const T* x, T* xo,
                          T omega, hipStream_t st) {
     const int64_t nb = stencil_blocks(lv.n, sizeof(T));
-    hipLaunchKernelGGL((k_stencil<T, OP_JACOBI, false, true>), dim3(grid8(nb)), dim3(BLOCK), 0,
-                       st, bands, lv.bs, lv.N, lv.n, x, b, xo, omega, (double*)nullptr, nb,
-                       (const double*)nullptr);
+    MG_STENCIL(T, OP_JACOBI, false, true, bands, lv.bs, lv.N, lv.n, x, b, xo, omega,
+               (double*)nullptr, nb, (const double*)nullptr);
     return hipGetLastError();
 }
 
@@ -1095,6 +1114,18 @@ dev::FusedGeom single_geom(int N, int elem_bytes) {
     return dev::fused_geom(N, bt ? bt : fused_bt(N), rh);
 }
 
+// Whether a fused pass over n nodes (eight streams: five bands, x, b, the
+// output) is too large for the 256 MB last-level cache to keep until the next
+// pass; it then bypasses it (dev::pass_store).  Bands and iterate cached /
+// bands non-temporal / both non-temporal: L = 12 mixed solve 5.56 / 5.56 / 5.43
+// ms (537 MB a pass), L = 12 FP64 6.84 / 6.97 / 6.77 ms, but L = 11 PCG 1.98 / 2.00 /
+// 2.02 ms (134 MB), L = 10 mixed 1.09 / 1.11 / 1.12 ms, 256-problem batch 7.85 /
+// 8.24 / 8.36 ms (under 9 MB a problem's pass); with both ways for the 268 MB
+// of FP64 at L = 11 the L = 12 FP64 solve took 6.76 and 6.78 ms.
+static bool pass_streams(int64_t n, int elem_bytes) {
+    return n * 8 * elem_bytes > ((int64_t)384 << 20);
+}
+
 #define MG_FUSED_BT_SWITCH(bt, LAUNCH) \
     switch (bt) {                      \
         case 64: LAUNCH(64); break;    \
@@ -1108,13 +1139,19 @@ hipError_t launch_pre(const Level& lv, const T* bands, const T* x, bool x_zero, 
                       T omega, T* x2out, T* bc, int dmask, hipStream_t st, const double* guard) {
     const dev::FusedGeom g = single_geom(lv.N, sizeof(T));
     const dim3 grid(grid8((int64_t)g.nstrips * g.nchunks)), block(g.bt);
-#define PRE(BT)                                                                               \
-    if (x_zero)                                                                               \
-        hipLaunchKernelGGL((k_pre<T, true, BT>), grid, block, 0, st, bands, lv.bs, lv.N, x, b, \
-                           omega, x2out, bc, dmask, g, guard);                                \
-    else                                                                                      \
-        hipLaunchKernelGGL((k_pre<T, false, BT>), grid, block, 0, st, bands, lv.bs, lv.N, x,   \
-                           b, omega, x2out, bc, dmask, g, guard);
+    const bool stream = pass_streams(lv.n, sizeof(T));
+#define PRE_T(ZERO, BT, STREAM)                                                               \
+    hipLaunchKernelGGL((k_pre<T, ZERO, BT, STREAM>), grid, block, 0, st, bands, lv.bs, lv.N,  \
+                       x, b, omega, x2out, bc, dmask, g, guard)
+#define PRE(BT)                   \
+    if (x_zero && stream)         \
+        PRE_T(true, BT, true);    \
+    else if (x_zero)              \
+        PRE_T(true, BT, false);   \
+    else if (stream)              \
+        PRE_T(false, BT, true);   \
+    else                          \
+        PRE_T(false, BT, false);
 #define PRE_BLK(BR, BC)                                                                        \
     if (x_zero)                                                                                \
         hipLaunchKernelGGL((k_pre_blk<T, true, BR, BC>), grid, block, 0, st, bands, lv.bs,     \
@@ -1133,6 +1170,7 @@ hipError_t launch_pre(const Level& lv, const T* bands, const T* x, bool x_zero, 
     }
 #undef PRE_BLK
 #undef PRE
+#undef PRE_T
     return hipGetLastError();
 }
 
@@ -1142,13 +1180,19 @@ hipError_t launch_post(const Level& lv, const T* bands, const T* x, const T* xc,
                        hipStream_t st, const double* guard, RedCtl ctl) {
     const dev::FusedGeom g = single_geom(lv.N, sizeof(T));
     const dim3 grid(grid8((int64_t)g.nstrips * g.nchunks)), block(g.bt);
-#define POST(BT)                                                                             \
-    if (partials)                                                                            \
-        hipLaunchKernelGGL((k_post<T, true, BT>), grid, block, 0, st, bands, lv.bs, lv.N, x, \
-                           xc, b, omega, xout, partials, g, guard);                          \
-    else                                                                                     \
-        hipLaunchKernelGGL((k_post<T, false, BT>), grid, block, 0, st, bands, lv.bs, lv.N,   \
-                           x, xc, b, omega, xout, (double*)nullptr, g, guard);
+    const bool stream = pass_streams(lv.n, sizeof(T));
+#define POST_T(NORM, BT, STREAM)                                                              \
+    hipLaunchKernelGGL((k_post<T, NORM, BT, STREAM>), grid, block, 0, st, bands, lv.bs, lv.N, \
+                       x, xc, b, omega, xout, partials, g, guard)
+#define POST(BT)                  \
+    if (partials && stream)       \
+        POST_T(true, BT, true);   \
+    else if (partials)            \
+        POST_T(true, BT, false);  \
+    else if (stream)              \
+        POST_T(false, BT, true);  \
+    else                          \
+        POST_T(false, BT, false);
 #define POST_BLK(BR, BC)                                                                      \
     if (partials)                                                                             \
         hipLaunchKernelGGL((k_post_blk<T, true, BR, BC>), grid, block, 0, st, bands, lv.bs,   \
@@ -1167,6 +1211,7 @@ hipError_t launch_post(const Level& lv, const T* bands, const T* x, const T* xc,
     }
 #undef POST_BLK
 #undef POST
+#undef POST_T
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !partials) return e;
     return launch_reduce(partials, dev::fused_norm_parts(lv.N), scal, slot, host, st, guard, ctl);
@@ -1290,8 +1335,12 @@ hipError_t launch_defect_cast(const Level& lv, const double* bands, const double
                               int slot, double* host, hipStream_t st, const double* guard,
                               RedCtl ctl) {
     const int64_t nb = stencil_blocks(lv.n, sizeof(double));
-    hipLaunchKernelGGL(k_defect_cast, dim3(grid8(nb)), dim3(BLOCK), 0, st, bands, lv.bs, lv.N,
-                       lv.n, x, b, d32, scal, partials, nb, guard);
+    if (small_product(lv.n, sizeof(double)))
+        hipLaunchKernelGGL(k_defect_cast<true>, dim3(grid8(nb)), dim3(BLOCK), 0, st, bands, lv.bs,
+                           lv.N, lv.n, x, b, d32, scal, partials, nb, guard);
+    else
+        hipLaunchKernelGGL(k_defect_cast<false>, dim3(grid8(nb)), dim3(BLOCK), 0, st, bands,
+                           lv.bs, lv.N, lv.n, x, b, d32, scal, partials, nb, guard);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_reduce(partials, nb, scal, slot, host, st, guard, ctl);
@@ -1353,7 +1402,7 @@ hipError_t launch_scalar_copy(double* scal, int from, int to, hipStream_t st) {
 }
 
 #define MG_INSTANTIATE(T)                                                                     \
-    template hipError_t launch_spmv<T>(const Level&, const T*, const T*, T*, hipStream_t, bool); \
+    template hipError_t launch_spmv<T>(const Level&, const T*, const T*, T*, hipStream_t);     \
     template hipError_t launch_defect<T>(const Level&, const T*, const T*, const T*, T*,      \
                                          double*, double*, int, double*, hipStream_t,         \
                                          const double*, RedCtl);                              \

@@ -172,12 +172,11 @@ hipError_t launch_rhs_sinsin(const double* xy, int N, double* b, hipStream_t st)
 hipError_t launch_rhs_uniform(int N, uint64_t seed, int dmask, double* b, double* x0,
                               hipStream_t st);
 
-// Stencil family on one level.
+// Stencil family on one level.  The lower bands are read as shifted upper
+// bands (the assembled matrices are symmetric bit for bit; five band streams
+// from HBM instead of nine).
 template <typename T>
-// sym: read the lower bands as shifted upper bands (same values for the
-// assembled, symmetric matrices; five band streams from HBM instead of nine).
-hipError_t launch_spmv(const Level& lv, const T* bands, const T* x, T* y, hipStream_t st,
-                       bool sym = false);
+hipError_t launch_spmv(const Level& lv, const T* bands, const T* x, T* y, hipStream_t st);
 // Reductions land in scal[slot] (sum of squares) and scal[slot+1] (norm) in
 // device memory and, when host is not null, also in host[slot], host[slot+1]
 // (pinned memory, for the host to read once the stream has synchronized).
