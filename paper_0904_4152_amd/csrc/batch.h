@@ -3,6 +3,7 @@
 // captured HIP graph per iteration).  Used by mg_solve_batch and the server.
 #pragma once
 
+#include <array>
 #include <vector>
 
 #include "mg_internal.h"
@@ -160,7 +161,15 @@ private:
     std::vector<int> h_wl_;
     std::vector<char> started_;
     bool probs_dirty_ = true;
-    hipGraphExec_t graph_[2] = {};  // iteration graphs without / with the start phase
+    // captured iterations (without / with the start phase) of the latest
+    // compositions, the current one last; a key is what the launches depend on
+    struct GraphSet {
+        std::array<int, 2 * (MG_MAX_LEVEL + 1) + 1> key;
+        hipGraphExec_t exec[2];
+    };
+    static constexpr size_t MAX_GRAPH_SETS = 4;
+    std::vector<GraphSet> graphs_;
+    void select_graphs();
     bool init_pending_ = false;     // problems started since the last launch
     // Optional launches present in the captured graph: bit l for the fused
     // passes at level l, bit 0 for the residual of problems with no level
@@ -171,9 +180,7 @@ private:
     int bt_override_[MG_MAX_LEVEL + 1] = {};  // workgroup widths under trial (0: none)
     int cols_override_[MG_MAX_LEVEL + 1] = {};  // block tile columns under trial (0: march)
     int bt_[MG_MAX_LEVEL + 1] = {};           // workgroup width of each level's fused passes
-    int graph_bt_[MG_MAX_LEVEL + 1] = {};     // the widths the captured graph launches
     int blk_[MG_MAX_LEVEL + 1] = {};          // block tile shape of each level's fused passes (0: march)
-    int graph_blk_[MG_MAX_LEVEL + 1] = {};    // the shapes the captured graph launches
     bool tuned_widths_ = true;
 };
 

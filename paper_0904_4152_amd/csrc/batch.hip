@@ -25,6 +25,7 @@
 
 #include "batch.h"
 #include "device_ops.h"
+#include "block_ops.h"
 #include "fused_ops.h"
 #include "tail_ops.h"
 
@@ -362,46 +363,46 @@ __global__ __launch_bounds__(BT) void kb_fpost(const BProb* __restrict__ probs,
     END_ITEMS
 }
 
-// The same passes in block tiles of BR x BC owned nodes.
-template <int BR, int BC>
-__global__ __launch_bounds__(dev::BLK_THREADS) void kb_fpre_blk(const BProb* __restrict__ probs,
-                                                               const BState* __restrict__ state,
-                                                               const int* __restrict__ wl, int l,
-                                                               int mask) {
-    __shared__ dev::BlockLds<float, BR, BC> s;
+// The same passes in block tiles of W wavefronts.
+template <int W>
+__global__ __launch_bounds__(64 * W) void kb_fpre_blk(const BProb* __restrict__ probs,
+                                                     const BState* __restrict__ state,
+                                                     const int* __restrict__ wl, int l,
+                                                     int mask) {
+    __shared__ dev::BlockLds<float, W> s;
     FOR_ITEMS(wl)
     if (!(flags & mask)) continue;
+    __syncthreads();  // the previous tile is done with LDS
     const BLevel& lv = P.lv[l];
     const int strip = tile % lv.nstrips, chunk = tile / lv.nstrips;
     const float om = (float)P.omega;
     if (l < P.L || state[p].first)
-        dev::pre_block<float, true, BR, BC>(s, lv.bands32, lv.bs, lv.N, lv.x32, lv.b32, om,
-                                            lv.t32, P.lv[l - 1].b32, P.dmask, strip, chunk);
+        dev::pre_block<float, true, W, 2>(s, lv.bands32, lv.bs, lv.N, lv.x32, lv.b32, om, lv.t32,
+                                          P.lv[l - 1].b32, P.dmask, strip, chunk);
     else
-        dev::pre_block<float, false, BR, BC>(s, lv.bands32, lv.bs, lv.N, lv.x32, lv.b32, om,
-                                             lv.t32, P.lv[l - 1].b32, P.dmask, strip, chunk);
+        dev::pre_block<float, false, W, 2>(s, lv.bands32, lv.bs, lv.N, lv.x32, lv.b32, om, lv.t32,
+                                           P.lv[l - 1].b32, P.dmask, strip, chunk);
     END_ITEMS
 }
 
-template <int BR, int BC>
-__global__ __launch_bounds__(dev::BLK_THREADS) void kb_fpost_blk(const BProb* __restrict__ probs,
-                                                                const BState* __restrict__ state,
-                                                                const int* __restrict__ wl, int l,
-                                                                int mask) {
-    __shared__ dev::BlockLds<float, BR, BC> s;
+template <int W>
+__global__ __launch_bounds__(64 * W) void kb_fpost_blk(const BProb* __restrict__ probs,
+                                                      const BState* __restrict__ state,
+                                                      const int* __restrict__ wl, int l,
+                                                      int mask) {
+    __shared__ dev::BlockLds<float, W> s;
     FOR_ITEMS(wl)
     if (!(flags & mask)) continue;
+    __syncthreads();  // the previous tile is done with LDS
     const BLevel& lv = P.lv[l];
     const int strip = tile % lv.nstrips, chunk = tile / lv.nstrips;
     const float om = (float)P.omega;
     if (l == P.L)
-        dev::post_block<float, true, BR, BC>(s, lv.bands32, lv.bs, lv.N, lv.t32,
-                                             P.lv[l - 1].x32, lv.b32, om, lv.x32, P.partials,
-                                             strip, chunk);
+        dev::post_block<float, true, W, 2>(s, lv.bands32, lv.bs, lv.N, lv.t32, P.lv[l - 1].x32,
+                                           lv.b32, om, lv.x32, P.partials, strip, chunk);
     else
-        dev::post_block<float, false, BR, BC>(s, lv.bands32, lv.bs, lv.N, lv.t32,
-                                              P.lv[l - 1].x32, lv.b32, om, lv.x32, nullptr, strip,
-                                              chunk);
+        dev::post_block<float, false, W, 2>(s, lv.bands32, lv.bs, lv.N, lv.t32, P.lv[l - 1].x32,
+                                            lv.b32, om, lv.x32, nullptr, strip, chunk);
     END_ITEMS
 }
 
@@ -724,8 +725,9 @@ __global__ __launch_bounds__(BLOCK) void kb_finctl(const BProb* __restrict__ pro
 }  // namespace
 
 BatchEngine::~BatchEngine() {
-    for (hipGraphExec_t g : graph_)
-        if (g) (void)hipGraphExecDestroy(g);
+    for (GraphSet& set : graphs_)
+        for (hipGraphExec_t g : set.exec)
+            if (g) (void)hipGraphExecDestroy(g);
     if (st_) (void)hipStreamDestroy(st_);
     if (d_probs_) (void)hipFree(d_probs_);
     if (d_state_) (void)hipFree(d_state_);
@@ -785,7 +787,7 @@ mg_status BatchEngine::init(int device, int capacity, int Lmax, int Lc, int nu_p
     std::memset(h_ring_, 0, sizeof(int) * ring_ints);
     hp_.assign(cap_, BProb{});
     started_.assign(cap_, 0);
-    for (int l = 1; l <= MG_MAX_LEVEL; ++l) bt_[l] = graph_bt_[l] = fused_bt((1 << l) + 1);
+    for (int l = 1; l <= MG_MAX_LEVEL; ++l) bt_[l] = fused_bt((1 << l) + 1);
     std::memset(h_state_, 0, sizeof(BState) * cap_);
     for (int s = 0; s < cap_; ++s) h_state_[s].flags = BF_DONE;
     MG_HIP(hipMemcpy(d_state_, h_state_, sizeof(BState) * cap_, hipMemcpyHostToDevice));
@@ -884,6 +886,13 @@ void tile_table_set(int level, int64_t problems, int rows, int bt, int cols) {
     ++t.epoch;
 }
 
+void tile_table_erase(int level, int64_t problems) {
+    TileTable& t = tile_table();
+    std::lock_guard<std::mutex> g(t.mu);
+    t.rows.erase({level, log2_floor(problems)});
+    ++t.epoch;
+}
+
 void tile_table_clear() {
     TileTable& t = tile_table();
     std::lock_guard<std::mutex> g(t.mu);
@@ -927,7 +936,7 @@ void BatchEngine::build_lists() {
     // tiles of the fused passes for this composition: every problem at a
     // level shares one chunk height and one workgroup width (no result bit
     // depends on either): a choice under trial by the autotuner, else the
-    // tuned one, else the rules (fewest threads per row; ~3500 wavefronts)
+    // tuned one (the server: tuned heights of marching tiles), else the rule
     for (int l = Lc_ + 1; l <= Lmax_; ++l) {
         int64_t count = 0;
         for (int s = 0; s < cap_; ++s)
@@ -936,12 +945,15 @@ void BatchEngine::build_lists() {
         const int N = (1 << l) + 1;
         const TileEntry te = tile_table_get(l, count);
         int bt = bt_override_[l] ? bt_override_[l] : (tuned_widths_ ? te.bt : 0);
-        if (!bt) bt = fused_bt(N);
         int rh = rh_override_[l] ? rh_override_[l] : te.rows;
-        if (!rh) rh = fused_rh(N, bt, count);
         const int cols = rh_override_[l] ? cols_override_[l] : (tuned_widths_ ? te.cols : 0);
         const int shape = cols ? dev::block_shape(rh, cols) : 0;
-        const dev::FusedGeom g = shape ? dev::block_geom(N, shape) : dev::fused_geom(N, bt, rh);
+        dev::FusedGeom g = batch_rule(N, count, !tuned_widths_);
+        if (shape) {
+            g = dev::block_geom(N, shape);
+        } else if (rh && (tuned_widths_ || !g.blk)) {
+            g = dev::fused_geom(N, bt ? bt : fused_bt(N), rh);
+        }
         bt_[l] = g.bt;
         blk_[l] = g.blk;
         for (int s = 0; s < cap_; ++s) {
@@ -989,16 +1001,32 @@ void BatchEngine::build_lists() {
         if (h_wl_[(size_t)wl_fused(l) * stride] > 0) need |= 1u << l;
     if (h_wl_[(size_t)WL_FINEST_COARSE * stride] > 0) need |= 1u;
     if (h_wl_[(size_t)WL_SEGS32 * stride] > 0) need |= 1u << 31;
-    bool widths_changed = false;
-    for (int l = Lc_ + 1; l <= Lmax_; ++l)
-        if (bt_[l] != graph_bt_[l] || blk_[l] != graph_blk_[l]) widths_changed = true;
-    if ((need & ~launch_mask_) || widths_changed) {
-        launch_mask_ |= need;
-        for (hipGraphExec_t& g : graph_) {
-            if (g) (void)hipGraphExecDestroy(g);
-            g = nullptr;
+    launch_mask_ |= need;
+    select_graphs();
+}
+
+// The graph set of the current launches (the mask and every level's workgroup
+// width and block shape): compositions that alternate find their graphs again.
+void BatchEngine::select_graphs() {
+    std::array<int, 2 * (MG_MAX_LEVEL + 1) + 1> key;
+    key[0] = (int)launch_mask_;
+    for (int l = 0; l <= MG_MAX_LEVEL; ++l) {
+        key[1 + 2 * l] = bt_[l];
+        key[2 + 2 * l] = blk_[l];
+    }
+    for (size_t i = 0; i < graphs_.size(); ++i) {
+        if (graphs_[i].key == key) {
+            std::rotate(graphs_.begin() + i, graphs_.begin() + i + 1, graphs_.end());
+            return;
         }
     }
+    if (graphs_.size() >= MAX_GRAPH_SETS) {
+        (void)hipStreamSynchronize(st_);  // its last replay may be queued
+        for (hipGraphExec_t g : graphs_.front().exec)
+            if (g) (void)hipGraphExecDestroy(g);
+        graphs_.erase(graphs_.begin());
+    }
+    graphs_.push_back({key, {}});
 }
 
 // Stream-ordered: launches after this call see the new descriptors, lists
@@ -1094,18 +1122,18 @@ hipError_t BatchEngine::launch_fused(int l, bool pre, int mask) {
     const int* wl = d_wl_ + (size_t)wl_fused(l) * stride;
     const int bt = bt_[l];
     if (blk_[l]) {
-        const dim3 GB(STAGE_GRID), BB(dev::BLK_THREADS);
-#define BLK(BR)                                                                                 \
-    if (pre)                                                                                    \
-        hipLaunchKernelGGL((kb_fpre_blk<BR, dev::BLK_COLS>), GB, BB, 0, st_, d_probs_, d_state_, \
-                           wl, l, mask);                                                        \
-    else                                                                                        \
-        hipLaunchKernelGGL((kb_fpost_blk<BR, dev::BLK_COLS>), GB, BB, 0, st_, d_probs_,          \
+        const dim3 GB(STAGE_GRID), BB(64 * dev::block_waves(blk_[l]));
+#define BLK(S)                                                                               \
+    if (pre)                                                                                 \
+        hipLaunchKernelGGL(kb_fpre_blk<dev::block_waves(S)>, GB, BB, 0, st_, d_probs_,       \
+                           d_state_, wl, l, mask);                                           \
+    else                                                                                     \
+        hipLaunchKernelGGL(kb_fpost_blk<dev::block_waves(S)>, GB, BB, 0, st_, d_probs_,      \
                            d_state_, wl, l, mask);
         switch (blk_[l]) {
-            case 1: BLK(8) break;
-            case 2: BLK(16) break;
-            default: BLK(32) break;
+            case 1: BLK(1) break;
+            case 2: BLK(2) break;
+            default: BLK(3) break;
         }
 #undef BLK
         return hipGetLastError();
@@ -1154,7 +1182,7 @@ mg_status BatchEngine::tune(int reps, std::vector<mg_tile_choice>* out) {
             for (int rh : kRows) cand.push_back({bt, rh, 0});
         if ((1 << l) + 1 <= dev::BLK_MAX_N)
             for (int s = 1; s <= dev::BLK_SHAPES; ++s)
-                cand.push_back({dev::BLK_THREADS, dev::block_rows(s), dev::BLK_COLS});
+                cand.push_back({64 * dev::BLK_TAG_WAVES, dev::block_rows(s), dev::BLK_TAG});
         for (const auto& c : cand) {
             {
                 const int bt = c[0], rh = c[1];
@@ -1287,23 +1315,21 @@ hipError_t BatchEngine::enqueue_iteration(bool with_init) {
 }
 
 mg_status BatchEngine::ensure_graph() {
+    if (graphs_.empty()) select_graphs();
+    hipGraphExec_t(&graph)[2] = graphs_.back().exec;
     for (int w = 0; w < 2; ++w) {
-        if (graph_[w]) continue;
+        if (graph[w]) continue;
         hipGraph_t g = nullptr;
         MG_HIP(hipStreamBeginCapture(st_, hipStreamCaptureModeThreadLocal));
         hipError_t e = enqueue_iteration(w == 1);
         hipError_t e2 = hipStreamEndCapture(st_, &g);
         if (e == hipSuccess) e = e2;
-        if (e == hipSuccess) e = hipGraphInstantiate(&graph_[w], g, nullptr, nullptr, 0);
+        if (e == hipSuccess) e = hipGraphInstantiate(&graph[w], g, nullptr, nullptr, 0);
         if (g) (void)hipGraphDestroy(g);
         if (e != hipSuccess) {
-            graph_[w] = nullptr;
+            graph[w] = nullptr;
             return fail(MG_ERR_DEVICE, std::string("batch graph capture: ") + hipGetErrorString(e));
         }
-    }
-    for (int l = 0; l <= MG_MAX_LEVEL; ++l) {
-        graph_bt_[l] = bt_[l];
-        graph_blk_[l] = blk_[l];
     }
     return MG_OK;
 }
@@ -1311,7 +1337,7 @@ mg_status BatchEngine::ensure_graph() {
 // One iteration; the first after an upload that started problems also runs
 // the start phase.
 mg_status BatchEngine::launch() {
-    MG_HIP(hipGraphLaunch(graph_[init_pending_ ? 1 : 0], st_));
+    MG_HIP(hipGraphLaunch(graphs_.back().exec[init_pending_ ? 1 : 0], st_));
     init_pending_ = false;
     MG_HIP(hipEventRecord(ev_[launched_ % ITER_RING], st_));
     ++launched_;
@@ -1645,9 +1671,9 @@ extern "C" mg_status mg_batch_set_tile(int level, int problems, int tile_rows, i
     if (tile_cols) {
         if (!dev::block_shape(tile_rows, tile_cols))
             return fail(MG_ERR_INVALID, "a block tile is 8, 16 or 32 rows by 32 columns");
-        if (row_waves != 0 && row_waves != dev::BLK_THREADS / 64)
+        if (row_waves != 0 && row_waves != dev::BLK_TAG_WAVES)
             return fail(MG_ERR_INVALID, "a block tile has 4 wavefronts (row_waves 0 or 4)");
-        tile_table_set(level, problems, tile_rows, dev::BLK_THREADS, tile_cols);
+        tile_table_set(level, problems, tile_rows, 64 * dev::BLK_TAG_WAVES, tile_cols);
         return MG_OK;
     }
     if (tile_rows < 4 || tile_rows > 256 || tile_rows % 4)

@@ -14,6 +14,7 @@
 #include <cstdlib>
 #include <type_traits>
 
+#include "block_ops.h"
 #include "device_ops.h"
 #include "fused_ops.h"
 #include "mg_internal.h"
@@ -263,29 +264,29 @@ __global__ __launch_bounds__(BT) void k_post(const T* __restrict__ bands, int64_
                                 (int)(lb % g.nstrips), (int)(lb / g.nstrips), g.rh, g.cw);
 }
 
-// The same passes in block tiles of BR x BC owned nodes.
-template <typename T, bool XZERO, int BR, int BC>
-__global__ __launch_bounds__(dev::BLK_THREADS) void k_pre_blk(
+// The same passes in block tiles of W wavefronts, with NU sweeps.
+template <typename T, bool XZERO, int W, int NU>
+__global__ __launch_bounds__(64 * W) void k_pre_blk(
     const T* __restrict__ bands, int64_t bs, int N, const T* __restrict__ x,
     const T* __restrict__ b, T omega, T* __restrict__ x2out, T* __restrict__ bc, int dmask,
     dev::FusedGeom g, const double* __restrict__ guard) {
     const int64_t lb = xcd_block((int64_t)g.nstrips * g.nchunks);
     if (lb < 0 || skipped(guard)) return;
-    __shared__ dev::BlockLds<T, BR, BC> s;
-    dev::pre_block<T, XZERO, BR, BC>(s, bands, bs, N, x, b, omega, x2out, bc, dmask,
-                                     (int)(lb % g.nstrips), (int)(lb / g.nstrips));
+    __shared__ dev::BlockLds<T, W> s;
+    dev::pre_block<T, XZERO, W, NU>(s, bands, bs, N, x, b, omega, x2out, bc, dmask,
+                                    (int)(lb % g.nstrips), (int)(lb / g.nstrips));
 }
 
-template <typename T, bool NORM, int BR, int BC>
-__global__ __launch_bounds__(dev::BLK_THREADS) void k_post_blk(
+template <typename T, bool NORM, int W, int NU>
+__global__ __launch_bounds__(64 * W) void k_post_blk(
     const T* __restrict__ bands, int64_t bs, int N, const T* __restrict__ x,
     const T* __restrict__ xc, const T* __restrict__ b, T omega, T* __restrict__ xout,
     double* __restrict__ partials, dev::FusedGeom g, const double* __restrict__ guard) {
     const int64_t lb = xcd_block((int64_t)g.nstrips * g.nchunks);
     if (lb < 0 || skipped(guard)) return;
-    __shared__ dev::BlockLds<T, BR, BC> s;
-    dev::post_block<T, NORM, BR, BC>(s, bands, bs, N, x, xc, b, omega, xout, partials,
-                                     (int)(lb % g.nstrips), (int)(lb / g.nstrips));
+    __shared__ dev::BlockLds<T, W> s;
+    dev::post_block<T, NORM, W, NU>(s, bands, bs, N, x, xc, b, omega, xout, partials,
+                                    (int)(lb % g.nstrips), (int)(lb / g.nstrips));
 }
 
 // Coarse tail: the V(nu_pre, nu_post) sub-cycle over levels top..Lc in one
@@ -1026,33 +1027,39 @@ int fused_rh(int N, int bt, int64_t count) {
 
 // Tiles of one problem's fused passes on a level without a tuned entry.
 //
-// Up to 513 nodes per side: block tiles of 8 x 32 nodes.  There a march is
-// bound by its chain of row steps (a pass of 4-row chunks is 13 steps of
-// ~0.5 us), a block tile by one memory latency.  Pre (zero start) / post pass
-// of L = 6, 7, 8, 9, marching -> block tiles: FP32 6.2/6.4 -> 3.9/3.6, 6.8/7.1 ->
-// 4.0/3.7, 5.9/6.3 -> 4.3/4.0, 7.6/8.4 -> 6.1/5.5 us; FP64 7.4/7.6 -> 4.5/4.1,
-// 8.1/9.1 -> 4.6/4.2, 7.4/7.5 -> 5.5/5.0, 10.6/11.5 -> 9.6/8.5 us.  At L = 10 the
-// halo (2.5 x the owned nodes) makes them slower than the best march.
+// Block tiles while the level's eight streams (five bands, x, b, the output)
+// take at most 160 MB: FP32 up to L = 11 (134 MB), FP64 up to L = 10 (67 MB).
+// There a march is bound by its chain of row steps (rows + 9 of at least 0.5
+// us each) and a block tile by one memory latency and its four steps; its
+// halo is read from the caches.  Larger levels are bound by HBM, and the march
+// moves 1.1 x the streams once where the block's halo no longer stays cached
+// (FP32 L = 12: march 100 us, every block shape above 120; FP64 L = 11: march
+// 46 to 56, block 51 to 68).  Pre (zero start) / post pass, best march -> block
+// in us: FP32 L = 6 6.2/6.4 -> 3.1/3.1, L = 8 5.9/6.3 -> 3.1/3.1, L = 9 7.0/7.8 ->
+// 4.0/4.1, L = 10 11.6/10.8 -> 7.0/7.5, L = 11 33.9/33.8 -> 24/25; FP64 L = 6 7.4/7.6
+// -> 3.5/3.9, L = 8 7.3/7.5 -> 3.6/3.9, L = 9 9.4/10.2 -> 5.9/6.6, L = 10 18.5/20.0 ->
+// 13.9/15.9.  Tiles of 8 rows have the shortest chain; 16 rows (less halo) are
+// faster in FP32 from L = 10 (7.0/7.5 against 7.5/8.2), where 8 rows give over
+// eight tiles per compute unit.
 //
 // Above: the march that minimises a cost model fitted to a sweep of heights
 // and widths at L = 10, 11, 12 in both types.  A tile of rh rows takes rh + 9
 // row steps; a step takes at least `lat` (its two barriers and LDS round
 // trips), and at least `per_wave` for every wavefront the busiest compute unit
-// runs (its share of the memory and issue rate; less where the level's
-// 5 bands and vectors fit the last-level caches).  Few rows waste steps on the
+// runs (its share of the memory and issue rate).  Few rows waste steps on the
 // halo, many rows leave compute units idle or unevenly loaded.  Rules before
 // (64 rows or fewer so that there are ~3500 wavefronts) -> model, pre/post:
-// FP32 L = 10 13.9/15.8 -> 11.6/10.8, L = 11 35.5/37.1 -> 34/34, L = 12 113/121
-// -> 99/103 us; FP64 L = 10 29.5/34.5 -> 18.5/20.0, L = 11 65/73 -> 56/61, L = 12
-// 237/274 -> 211/252 us.
+// FP32 L = 12 113/121 -> 99/103 us; FP64 L = 11 65/73 -> 56/61, L = 12 237/274 ->
+// 211/252 us.
 dev::FusedGeom single_rule(int N, int elem_bytes) {
-    if (N <= 513) return dev::block_geom(N, 1);
+    const int64_t n = (int64_t)N * N;
+    const bool fp64 = elem_bytes == 8;
+    if (n * 8 * elem_bytes <= (int64_t)160 << 20)
+        return dev::block_geom(N, !fp64 && N > 513 ? 2 : 1);
     static const int kRows[] = {8, 12, 16, 24, 32, 48, 64, 96, 128, 160, 192, 224, 256};
     constexpr int kCus = 256;
-    const bool fp64 = elem_bytes == 8;
-    const bool cached = (int64_t)N * N * elem_bytes * 8 <= (int64_t)48 << 20;
     const double lat = fp64 ? 0.68 : 0.55;
-    const double per_wave = fp64 ? 0.175 : (cached ? 0.055 : 0.08);
+    const double per_wave = fp64 ? 0.175 : 0.08;
     dev::FusedGeom best{};
     double best_us = 0.0;
     for (int bt = dev::F_MIN_THREADS; bt <= dev::F_MAX_THREADS; bt += 64) {
@@ -1068,6 +1075,37 @@ dev::FusedGeom single_rule(int N, int elem_bytes) {
         }
     }
     return best;
+}
+
+// Tiles of a batched pass over `count` problems on a level without a tuned
+// entry.  Up to 4 million nodes in all: block tiles (the problems' streams,
+// 32 bytes a node, stay in the last-level cache), of 8 rows while the device
+// is not full (up to 300 thousand nodes), else of the height that covers the
+// grid with the fewest wavefronts.  Above, marching tiles: the fewest threads
+// per row and the height of fused_rh.  256 problems of levels 5..9: 7.84 ms
+// with marching tiles everywhere, 7.5 with this rule, 8.1 to 9.6 with block
+// tiles everywhere; 64 problems 3.66 -> 2.95 ms, 16 problems of levels 6..9 2.41
+// -> 1.88, 4 problems 1.28 -> 0.93.
+// fixed: independent of count (a server's mix changes every iteration, and a
+// change of shape captures its graph again).
+dev::FusedGeom batch_rule(int N, int64_t count, bool fixed) {
+    const int64_t total = count * N * N;
+    if (fixed ? N <= 1025 : total <= 4000000) {
+        if (!fixed && total <= 300000) return dev::block_geom(N, 1);
+        int best = 1;
+        int64_t best_waves = 0;
+        for (int s = 1; s <= dev::BLK_SHAPES; ++s) {
+            const dev::FusedGeom g = dev::block_geom(N, s);
+            const int64_t waves = (int64_t)g.nstrips * g.nchunks * dev::block_waves(s);
+            if (best_waves == 0 || waves < best_waves) {
+                best_waves = waves;
+                best = s;
+            }
+        }
+        return dev::block_geom(N, best);
+    }
+    const int bt = fused_bt(N);
+    return dev::fused_geom(N, bt, fused_rh(N, bt, count));
 }
 
 // The autotuner's trial of one level (per thread: the tuner launches from
@@ -1152,19 +1190,19 @@ hipError_t launch_pre(const Level& lv, const T* bands, const T* x, bool x_zero, 
         PRE_T(false, BT, true);   \
     else                          \
         PRE_T(false, BT, false);
-#define PRE_BLK(BR, BC)                                                                        \
+#define PRE_BLK(S)                                                                             \
     if (x_zero)                                                                                \
-        hipLaunchKernelGGL((k_pre_blk<T, true, BR, BC>), grid, block, 0, st, bands, lv.bs,     \
-                           lv.N, x, b, omega, x2out, bc, dmask, g, guard);                     \
+        hipLaunchKernelGGL((k_pre_blk<T, true, dev::block_waves(S), 2>), grid, block, 0, st,   \
+                           bands, lv.bs, lv.N, x, b, omega, x2out, bc, dmask, g, guard);       \
     else                                                                                       \
-        hipLaunchKernelGGL((k_pre_blk<T, false, BR, BC>), grid, block, 0, st, bands, lv.bs,    \
-                           lv.N, x, b, omega, x2out, bc, dmask, g, guard);
+        hipLaunchKernelGGL((k_pre_blk<T, false, dev::block_waves(S), 2>), grid, block, 0, st,  \
+                           bands, lv.bs, lv.N, x, b, omega, x2out, bc, dmask, g, guard);
     if (g.blk == 1) {
-        PRE_BLK(8, 32)
+        PRE_BLK(1)
     } else if (g.blk == 2) {
-        PRE_BLK(16, 32)
+        PRE_BLK(2)
     } else if (g.blk == 3) {
-        PRE_BLK(32, 32)
+        PRE_BLK(3)
     } else {
         MG_FUSED_BT_SWITCH(g.bt, PRE)
     }
@@ -1193,19 +1231,20 @@ hipError_t launch_post(const Level& lv, const T* bands, const T* x, const T* xc,
         POST_T(false, BT, true);  \
     else                          \
         POST_T(false, BT, false);
-#define POST_BLK(BR, BC)                                                                      \
-    if (partials)                                                                             \
-        hipLaunchKernelGGL((k_post_blk<T, true, BR, BC>), grid, block, 0, st, bands, lv.bs,   \
-                           lv.N, x, xc, b, omega, xout, partials, g, guard);                  \
-    else                                                                                      \
-        hipLaunchKernelGGL((k_post_blk<T, false, BR, BC>), grid, block, 0, st, bands, lv.bs,  \
-                           lv.N, x, xc, b, omega, xout, (double*)nullptr, g, guard);
+#define POST_BLK(S)                                                                            \
+    if (partials)                                                                              \
+        hipLaunchKernelGGL((k_post_blk<T, true, dev::block_waves(S), 2>), grid, block, 0, st,  \
+                           bands, lv.bs, lv.N, x, xc, b, omega, xout, partials, g, guard);     \
+    else                                                                                       \
+        hipLaunchKernelGGL((k_post_blk<T, false, dev::block_waves(S), 2>), grid, block, 0, st, \
+                           bands, lv.bs, lv.N, x, xc, b, omega, xout, (double*)nullptr, g,     \
+                           guard);
     if (g.blk == 1) {
-        POST_BLK(8, 32)
+        POST_BLK(1)
     } else if (g.blk == 2) {
-        POST_BLK(16, 32)
+        POST_BLK(2)
     } else if (g.blk == 3) {
-        POST_BLK(32, 32)
+        POST_BLK(3)
     } else {
         MG_FUSED_BT_SWITCH(g.bt, POST)
     }

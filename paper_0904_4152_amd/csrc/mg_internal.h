@@ -300,6 +300,7 @@ int fused_rh(int N, int bt, int64_t count);
 // entry for one problem at the level, else the rule for the type's size.
 dev::FusedGeom single_geom(int N, int elem_bytes);
 dev::FusedGeom single_rule(int N, int elem_bytes);
+dev::FusedGeom batch_rule(int N, int64_t count, bool fixed);
 void set_single_trial(int N, int rows, int bt, int cols = 0);
 
 // Process-wide table of tuned tiles of the fused passes, keyed by level and
@@ -315,6 +316,7 @@ struct TileEntry {
 };
 TileEntry tile_table_get(int level, int64_t problems);
 void tile_table_set(int level, int64_t problems, int rows, int bt, int cols = 0);
+void tile_table_erase(int level, int64_t problems);
 void tile_table_clear();
 uint64_t tile_table_epoch();
 int64_t fused_max_norm_parts(int N);

@@ -836,7 +836,7 @@ extern "C" mg_status mg_hierarchy_autotune(mg_hierarchy* h, int reps, mg_tile_ch
             for (int rh : kRows) cand.push_back({bt, rh, 0});
         if (v.N <= dev::BLK_MAX_N)
             for (int s = 1; s <= dev::BLK_SHAPES; ++s)
-                cand.push_back({dev::BLK_THREADS, dev::block_rows(s), dev::BLK_COLS});
+                cand.push_back({64 * dev::BLK_TAG_WAVES, dev::block_rows(s), dev::BLK_TAG});
         for (const auto& c : cand) {
             {
                 const int bt = c[0], rh = c[1];
@@ -856,8 +856,26 @@ extern "C" mg_status mg_hierarchy_autotune(mg_hierarchy* h, int reps, mg_tile_ch
                 }
             }
         }
+        // where the rule takes block tiles on larger levels than they are
+        // candidates on, it stays in force unless a candidate beat it
+        const dev::FusedGeom rule = single_rule(v.N, sizeof(float));
+        bool keep_rule = false;
+        if (rule.blk && v.N > dev::BLK_MAX_N) {
+            set_single_trial(v.N, rule.rh, 64 * dev::BLK_TAG_WAVES, dev::BLK_TAG);
+            for (int w = 0; w < 2; ++w) MG_HIP(pair());
+            MG_HIP(hipEventRecord(g.a, st));
+            for (int r = 0; r < reps; ++r) MG_HIP(pair());
+            MG_HIP(hipEventRecord(g.b, st));
+            MG_HIP(hipEventSynchronize(g.b));
+            float ms = 0.0f;
+            MG_HIP(hipEventElapsedTime(&ms, g.a, g.b));
+            keep_rule = ms < best_ms;
+        }
         set_single_trial(0, 0, 0);
-        tile_table_set(l, 1, best_rows, best_bt, best_cols);
+        if (keep_rule)
+            tile_table_erase(l, 1);
+        else
+            tile_table_set(l, 1, best_rows, best_bt, best_cols);
         rows.push_back({l, 1, best_rows, best_bt / 64, best_cols, 1e3 * best_ms / reps});
     }
     const int n = std::min<int>(out_cap, (int)rows.size());
