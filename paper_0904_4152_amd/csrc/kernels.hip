@@ -1256,6 +1256,36 @@ hipError_t launch_post(const Level& lv, const T* bands, const T* x, const T* xc,
     return launch_reduce(partials, dev::fused_norm_parts(lv.N), scal, slot, host, st, guard, ctl);
 }
 
+// One sweep instead of two (V(1,1) and the like): block tiles of 8 rows, on
+// levels where the rule takes block tiles.
+bool one_sweep_blocks(int N, int elem_bytes) { return single_rule(N, elem_bytes).blk != 0; }
+
+template <typename T>
+hipError_t launch_pre1(const Level& lv, const T* bands, const T* x, bool x_zero, const T* b,
+                       T omega, T* xout, T* bc, int dmask, hipStream_t st) {
+    constexpr int W = dev::block_waves(1);
+    const dev::FusedGeom g = dev::block_geom(lv.N, 1);
+    const dim3 grid(grid8((int64_t)g.nstrips * g.nchunks)), block(g.bt);
+    if (x_zero)
+        hipLaunchKernelGGL((k_pre_blk<T, true, W, 1>), grid, block, 0, st, bands, lv.bs, lv.N, x,
+                           b, omega, xout, bc, dmask, g, (const double*)nullptr);
+    else
+        hipLaunchKernelGGL((k_pre_blk<T, false, W, 1>), grid, block, 0, st, bands, lv.bs, lv.N, x,
+                           b, omega, xout, bc, dmask, g, (const double*)nullptr);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_post1(const Level& lv, const T* bands, const T* x, const T* xc, const T* b,
+                        T omega, T* xout, hipStream_t st) {
+    constexpr int W = dev::block_waves(1);
+    const dev::FusedGeom g = dev::block_geom(lv.N, 1);
+    hipLaunchKernelGGL((k_post_blk<T, false, W, 1>), dim3(grid8((int64_t)g.nstrips * g.nchunks)),
+                       dim3(g.bt), 0, st, bands, lv.bs, lv.N, x, xc, b, omega, xout,
+                       (double*)nullptr, g, (const double*)nullptr);
+    return hipGetLastError();
+}
+
 template <typename T>
 hipError_t launch_tail(const Level* lv, int top, int Lc, const dev::CoarseSolver& cs, int nu_pre,
                        int nu_post, T omega, hipStream_t st, const double* guard) {
@@ -1462,6 +1492,10 @@ hipError_t launch_scalar_copy(double* scal, int from, int to, hipStream_t st) {
     template hipError_t launch_post<T>(const Level&, const T*, const T*, const T*, const T*, T, \
                                        T*, double*, double*, int, double*, hipStream_t,       \
                                        const double*, RedCtl);                                \
+    template hipError_t launch_pre1<T>(const Level&, const T*, const T*, bool, const T*, T, T*, \
+                                       T*, int, hipStream_t);                                 \
+    template hipError_t launch_post1<T>(const Level&, const T*, const T*, const T*, const T*, \
+                                        T, T*, hipStream_t);                                  \
     template hipError_t launch_tail<T>(const Level*, int, int, const dev::CoarseSolver&, int,  \
                                        int, T, hipStream_t, const double*);
 

@@ -279,6 +279,15 @@ template <typename T>
 hipError_t launch_post(const Level& lv, const T* bands, const T* x, const T* xc, const T* b,
                        T omega, T* xout, double* partials, double* scal, int slot, double* host,
                        hipStream_t st, const double* guard = nullptr, RedCtl ctl = {});
+// The same passes with one sweep (out of place, without the norm), on levels
+// where one_sweep_blocks holds.
+bool one_sweep_blocks(int N, int elem_bytes);
+template <typename T>
+hipError_t launch_pre1(const Level& lv, const T* bands, const T* x, bool x_zero, const T* b,
+                       T omega, T* xout, T* bc, int dmask, hipStream_t st);
+template <typename T>
+hipError_t launch_post1(const Level& lv, const T* bands, const T* x, const T* xc, const T* b,
+                        T omega, T* xout, hipStream_t st);
 // The V(nu_pre, nu_post) sub-cycle over levels top..Lc (top <=
 // tail_max_level(), entered with a zero iterate on level top) in one
 // workgroup.  lv is indexed by level.

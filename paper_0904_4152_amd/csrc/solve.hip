@@ -64,10 +64,24 @@ struct LV<float> {
 
 }  // namespace
 
-// Byte model (algorithmic HBM traffic, s = sizeof(T)): band product family
-// 9 bands + x (+ b) (+ output); Jacobi from zero: diagonal + b + output;
-// restriction: fine defect + coarse rhs; prolongation: coarse x + fine x
-// read and written.
+// Byte model (algorithmic HBM traffic, s = sizeof(T)) of one level of the
+// cycle as separate kernels: band product family 9 bands + x (+ b) (+ output);
+// Jacobi from zero: diagonal + b + output; restriction: fine defect + coarse
+// rhs; prolongation: coarse x + fine x read and written; a copy of the iterate
+// after an odd number of sweeps.
+static double unfused_level_bytes(double s, double n, double nc, bool x_zero, int nu_pre,
+                                  int nu_post) {
+    double b = x_zero && nu_pre == 0 ? s * n : 0.0;
+    b += nu_pre > 0 && x_zero ? 3 * s * n + 12 * s * n * (nu_pre - 1) : 12 * s * n * nu_pre;
+    b += 12 * s * n + s * (n + nc) + s * (nc + 2 * n) + 12 * s * n * nu_post;
+    return b + ((nu_pre + nu_post) % 2 ? 2 * s * n : 0.0);
+}
+
+// The V(nu_pre, nu_post) cycle as separate kernels.  Cycles other than
+// V(2,2) -- which has its own fused form (enqueue_vcycle_fused) and stays
+// unfused here, as its reference -- run the levels of the coarse tail in its
+// one launch, and a level with a single pre- or post-smoothing sweep as block
+// passes where those exist; the same bits.
 template <typename T>
 hipError_t enqueue_vcycle(mg_hierarchy* h, int l, T* x, const T* b, bool x_zero, int nu_pre,
                           int nu_post, double omega, Enq& q) {
@@ -79,44 +93,54 @@ hipError_t enqueue_vcycle(mg_hierarchy* h, int l, T* x, const T* b, bool x_zero,
         q.bytes += 2 * s * n;
         return hipSuccess;
     }
+    const bool reference = nu_pre == 2 && nu_post == 2;
+    const bool one = !reference && one_sweep_blocks(lv.N, sizeof(T));
     const T* bands = LV<T>::bands(lv);
+    Level& lc = h->lv[l - 1];
+    q.bytes += unfused_level_bytes(s, n, (double)lc.n, x_zero, nu_pre, nu_post);
     T* cur = x;
     T* oth = LV<T>::t(lv);
-    bool zero = x_zero;
-    if (zero && nu_pre == 0) {
-        MG_TRY(launch_fill<T>(cur, lv.n, T(0), q.st));
-        q.bytes += s * n;
-        zero = false;
-    }
-    for (int k = 0; k < nu_pre; ++k) {
-        if (zero) {
-            MG_TRY(launch_jacobi_zero<T>(lv, bands, b, oth, om, q.st));
-            q.bytes += 3 * s * n;
+    if (one && nu_pre == 1) {
+        MG_TRY(launch_pre1<T>(lv, bands, cur, x_zero, b, om, oth, LV<T>::b(lc), h->dmask, q.st));
+        std::swap(cur, oth);
+    } else {
+        bool zero = x_zero;
+        if (zero && nu_pre == 0) {
+            MG_TRY(launch_fill<T>(cur, lv.n, T(0), q.st));
             zero = false;
-        } else {
-            MG_TRY(launch_jacobi<T>(lv, bands, b, cur, oth, om, q.st));
-            q.bytes += 12 * s * n;
         }
+        for (int k = 0; k < nu_pre; ++k) {
+            if (zero)
+                MG_TRY(launch_jacobi_zero<T>(lv, bands, b, oth, om, q.st));
+            else
+                MG_TRY(launch_jacobi<T>(lv, bands, b, cur, oth, om, q.st));
+            zero = false;
+            std::swap(cur, oth);
+        }
+        MG_TRY(launch_defect<T>(lv, bands, b, cur, oth, nullptr, nullptr, 0, nullptr, q.st));
+        MG_TRY(launch_restrict<T>(lv.N, oth, LV<T>::b(lc), h->dmask, q.st));
+    }
+    if (!reference && l - 1 <= tail_max_level()) {
+        MG_TRY(launch_tail<T>(h->lv, l - 1, h->Lc, coarse_solver(h), nu_pre, nu_post, om, q.st));
+        for (int k = h->Lc + 1; k < l; ++k)
+            q.bytes += unfused_level_bytes(s, (double)h->lv[k].n, (double)h->lv[k - 1].n, true,
+                                           nu_pre, nu_post);
+        q.bytes += 2 * s * (double)h->lv[h->Lc].n;
+    } else {
+        MG_TRY(enqueue_vcycle<T>(h, l - 1, LV<T>::x(lc), LV<T>::b(lc), true, nu_pre, nu_post,
+                                 omega, q));
+    }
+    if (one && nu_post == 1) {
+        MG_TRY(launch_post1<T>(lv, bands, cur, LV<T>::x(lc), b, om, oth, q.st));
         std::swap(cur, oth);
+    } else {
+        MG_TRY(launch_prolong<T>(lv.N, LV<T>::x(lc), cur, q.st));
+        for (int k = 0; k < nu_post; ++k) {
+            MG_TRY(launch_jacobi<T>(lv, bands, b, cur, oth, om, q.st));
+            std::swap(cur, oth);
+        }
     }
-    MG_TRY(launch_defect<T>(lv, bands, b, cur, oth, nullptr, nullptr, 0, nullptr, q.st));
-    q.bytes += 12 * s * n;
-    Level& lc = h->lv[l - 1];
-    MG_TRY(launch_restrict<T>(lv.N, oth, LV<T>::b(lc), h->dmask, q.st));
-    q.bytes += s * (n + (double)lc.n);
-    MG_TRY(enqueue_vcycle<T>(h, l - 1, LV<T>::x(lc), LV<T>::b(lc), true, nu_pre, nu_post, omega,
-                             q));
-    MG_TRY(launch_prolong<T>(lv.N, LV<T>::x(lc), cur, q.st));
-    q.bytes += s * ((double)lc.n + 2 * n);
-    for (int k = 0; k < nu_post; ++k) {
-        MG_TRY(launch_jacobi<T>(lv, bands, b, cur, oth, om, q.st));
-        q.bytes += 12 * s * n;
-        std::swap(cur, oth);
-    }
-    if (cur != x) {
-        MG_TRY(launch_copy<T>(cur, x, lv.n, q.st));
-        q.bytes += 2 * s * n;
-    }
+    if (cur != x) MG_TRY(launch_copy<T>(cur, x, lv.n, q.st));
     return hipSuccess;
 }
 

@@ -1,5 +1,6 @@
-"""GPU: the coarse tail (levels of at most 33 x 33 nodes in one launch) against
-the same cycle composed of the library's single operators, bit for bit."""
+"""GPU: the coarse tail (levels of at most 33 x 33 nodes in one launch) and the
+one-sweep block passes against the same cycle composed of the library's single
+operators, bit for bit."""
 import numpy as np
 import pytest
 
@@ -46,7 +47,7 @@ def test_tail_equals_single_operators(ctx, L, Lc, sides, dtype):
         h.rhs_uniform(77, b64)
         b = b64.to(dtype)
         x0 = (0.01 * b64.roll(5) * (b64 != 0)).to(dtype)
-        for pre, post in ((2, 2),):
+        for pre, post in ((2, 2), (1, 1), (3, 0), (0, 2)):
             x = x0.clone()
             h.vcycle(L, b, x, nu_pre=pre, nu_post=post)
             y = x0.clone()
@@ -54,3 +55,22 @@ def test_tail_equals_single_operators(ctx, L, Lc, sides, dtype):
             torch.cuda.synchronize()
             assert np.array_equal(x.cpu().numpy(), y.cpu().numpy()), (cg, pre, post)
         h.close()
+
+
+# one-sweep block passes above the tail: FP32 up to L = 11, FP64 up to L = 10;
+# one side with a single sweep, the other separate kernels
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("L", [6, 7, 9, 11])
+@pytest.mark.parametrize("nu", [(1, 1), (1, 3), (2, 1)])
+def test_one_sweep_cycles_equal_single_operators(ctx, L, nu, dtype):
+    h = mg.Hierarchy(ctx, L, jitter=0.2, seed=3, dirichlet_sides=13)
+    b64 = torch.zeros(h.n, dtype=torch.float64, device="cuda")
+    h.rhs_uniform(78, b64)
+    b = b64.to(dtype)
+    x = (0.01 * b64.roll(5) * (b64 != 0)).to(dtype)
+    y = x.clone()
+    h.vcycle(L, b, x, nu_pre=nu[0], nu_post=nu[1])
+    composed_cycle(h, L, b, y, *nu)
+    torch.cuda.synchronize()
+    assert np.array_equal(x.cpu().numpy(), y.cpu().numpy())
+    h.close()
