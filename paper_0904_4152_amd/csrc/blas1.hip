@@ -7,7 +7,10 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
+#include <chrono>
 #include <cmath>
+#include <cstring>
 #include <mutex>
 #include <string>
 
@@ -59,6 +62,20 @@ __global__ __launch_bounds__(BLOCK) void k_axpy(int64_t n, T alpha, const T* __r
                 if (p + e < n) y[p + e] = fma(alpha, x[p + e], y[p + e]);
         }
     }
+}
+
+// The sum of np partials, its square root and then, once the host can see
+// both, the call's number into the context's pinned mirror (one workgroup).
+__global__ __launch_bounds__(BLOCK) void k_reduce_host(const double* __restrict__ partials,
+                                                       int64_t np, double* __restrict__ host,
+                                                       double seq) {
+    const double s = dev::reduce_partials(partials, np);
+    if (threadIdx.x != 0) return;
+    volatile double* h = host;
+    h[0] = s;
+    h[1] = sqrt(s);
+    __threadfence_system();
+    h[2] = seq;
 }
 
 // Partial sums of x_i y_i (SQUARE: x_i^2) in FP64 per tile: each thread sums
@@ -115,6 +132,7 @@ mg_status blas_scratch(mg_context* ctx, int64_t tiles) {
             ctx->blas_host = nullptr;
             return fail(MG_ERR_NOMEM, "pinned host allocation failed");
         }
+        std::memset(ctx->blas_host, 0, 64 * sizeof(double));
     }
     if (ctx->blas_bytes >= need) return MG_OK;
     if (!ctx->reserve(need)) return fail(MG_ERR_NOMEM, "reduction scratch over the context budget");
@@ -151,11 +169,35 @@ mg_status blas_reduce(mg_context* ctx, int64_t n, const T* x, const T* y, double
         *host_out = 0.0;
         return MG_OK;
     }
+    volatile double* host = ctx->blas_host;
+    const double seq = host[2] + 1.0;
     hipLaunchKernelGGL((k_dot_tiles<T, SQUARE>), dim3(tiles_of(n, blas_tile<T>())), dim3(BLOCK),
                        0, st, n, x, y, partials);
     MG_HIP(hipGetLastError());
-    MG_HIP(launch_reduce(partials, tiles, scal, 0, ctx->blas_host, st));
-    MG_HIP(hipStreamSynchronize(st));
+    // up to RED_SEG partials in one launch that also writes the mirror; the
+    // segmented sum of more leaves one partial for it
+    const double* last = partials;
+    int64_t left = tiles;
+    if (tiles > dev::RED_SEG) {
+        MG_HIP(launch_reduce(partials, tiles, scal, 0, nullptr, st));
+        last = scal;
+        left = 1;
+    }
+    hipLaunchKernelGGL(k_reduce_host, dim3(1), dim3(BLOCK), 0, st, last, left, ctx->blas_host,
+                       seq);
+    MG_HIP(hipGetLastError());
+    // The host watches the mirror for the call's number, which saves the
+    // wake-up of a blocking synchronisation; after 50 ms it blocks (and then
+    // also sees device errors).
+    const auto t0 = std::chrono::steady_clock::now();
+    for (unsigned i = 1; host[2] != seq; ++i) {
+        if ((i & 4095u) == 0 &&
+            std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(50)) {
+            MG_HIP(hipStreamSynchronize(st));
+            if (host[2] != seq) return fail(MG_ERR_DEVICE, "reduction did not finish");
+        }
+    }
+    std::atomic_thread_fence(std::memory_order_acquire);
     *host_out = ((volatile double*)ctx->blas_host)[root ? 1 : 0];
     return MG_OK;
 }

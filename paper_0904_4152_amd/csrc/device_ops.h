@@ -53,15 +53,55 @@ __device__ __forceinline__ float jacobi_div<float>(float num, float diag) {
     return num * __builtin_amdgcn_rcpf(diag);
 }
 
-// Deterministic block sum (wave shuffles, then the waves in order); the
+// v + (v of lane ^ o), as __shfl_xor gives it, without LDS-crossbar latency:
+// row swaps for o = 32 and 16, DPP below.
+template <int CTRL, int BANKS = 0xf>
+__device__ __forceinline__ int dpp_mov(int old, int v) {
+    return __builtin_amdgcn_update_dpp(old, v, CTRL, 0xf, BANKS, false);
+}
+template <int O>
+__device__ __forceinline__ int lane_xor(int v) {
+    if (O == 1) return dpp_mov<0xB1>(v, v);   // quad_perm [1,0,3,2]
+    if (O == 2) return dpp_mov<0x4E>(v, v);   // quad_perm [2,3,0,1]
+    if (O == 8) return dpp_mov<0x128>(v, v);  // row_ror:8
+    // 4: lanes 0-3 and 8-11 of a row read lane + 4, the others lane - 4
+    const int up = dpp_mov<0x104, 0x5>(v, v);
+    return dpp_mov<0x114, 0xa>(up, v);
+}
+__device__ __forceinline__ double make_double(unsigned lo, unsigned hi) {
+    return __hiloint2double((int)hi, (int)lo);
+}
+// Sum over the wavefront by the butterfly o = 32, 16, .., 1; every lane gets it.
+__device__ __forceinline__ double wave_sum(double v) {
+    {
+        const auto l = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v),
+                                                        false, false);
+        const auto h = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v),
+                                                        false, false);
+        v = make_double(l[0], h[0]) + make_double(l[1], h[1]);
+    }
+    {
+        const auto l = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v),
+                                                        false, false);
+        const auto h = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v),
+                                                        false, false);
+        v = make_double(l[0], h[0]) + make_double(l[1], h[1]);
+    }
+    v += make_double(lane_xor<8>(__double2loint(v)), lane_xor<8>(__double2hiint(v)));
+    v += make_double(lane_xor<4>(__double2loint(v)), lane_xor<4>(__double2hiint(v)));
+    v += make_double(lane_xor<2>(__double2loint(v)), lane_xor<2>(__double2hiint(v)));
+    v += make_double(lane_xor<1>(__double2loint(v)), lane_xor<1>(__double2hiint(v)));
+    return v;
+}
+
+// Deterministic block sum (wave_sum, then the waves in order); the
 // result is valid in thread 0.  Every thread of the block must call it; it
 // may be called repeatedly in a loop.
 template <int NT = BLOCK>
 __device__ __forceinline__ double block_sum(double v) {
     __shared__ double ws[NT / 64];
     __syncthreads();
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    v = wave_sum(v);
     if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = v;
     __syncthreads();
     double s = 0.0;
@@ -484,12 +524,12 @@ constexpr int64_t RED_SEG = 8192;  // partials per first-stage segment
 constexpr int RED_MAX_SEGS = 2048;  // so at most 16M partials
 
 // Thread-strided sum of p[lo, hi) then block_sum; valid in thread 0.  Each
-// thread adds its elements in index order; eight loads are in flight at a
-// time, so a long sum costs a few memory latencies rather than one per
-// element.
+// thread adds its elements in index order; all 32 loads of a segment of
+// RED_SEG are in flight at once (the partials come from other XCDs' caches, one
+// memory latency each time a thread waits).
 __device__ __forceinline__ double strided_sum(const double* __restrict__ p, int64_t lo,
                                               int64_t hi) {
-    constexpr int U = 8;
+    constexpr int U = (int)(RED_SEG / BLOCK);
     double s = 0.0;
     int64_t i = lo + threadIdx.x;
     for (; i + (int64_t)(U - 1) * BLOCK < hi; i += (int64_t)U * BLOCK) {
@@ -499,7 +539,17 @@ __device__ __forceinline__ double strided_sum(const double* __restrict__ p, int6
 #pragma unroll
         for (int u = 0; u < U; ++u) s += v[u];
     }
-    for (; i < hi; i += BLOCK) s += p[i];
+    // the rest, eight at a time (beyond the end: element lo, adding zero)
+    for (; i < hi; i += (int64_t)8 * BLOCK) {
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int64_t q = i + (int64_t)u * BLOCK;
+            v[u] = p[q < hi ? q : lo];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += i + (int64_t)u * BLOCK < hi ? v[u] : 0.0;
+    }
     return block_sum(s);
 }
 

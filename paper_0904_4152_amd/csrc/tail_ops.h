@@ -41,46 +41,6 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_wave_barrier();
 }
 
-// v + (v of lane ^ o), as __shfl_xor gives it, without LDS-crossbar latency:
-// row swaps for o = 32 and 16, DPP below.
-template <int CTRL, int BANKS = 0xf>
-__device__ __forceinline__ int dpp_mov(int old, int v) {
-    return __builtin_amdgcn_update_dpp(old, v, CTRL, 0xf, BANKS, false);
-}
-template <int O>
-__device__ __forceinline__ int lane_xor(int v) {
-    if (O == 1) return dpp_mov<0xB1>(v, v);   // quad_perm [1,0,3,2]
-    if (O == 2) return dpp_mov<0x4E>(v, v);   // quad_perm [2,3,0,1]
-    if (O == 8) return dpp_mov<0x128>(v, v);  // row_ror:8
-    // 4: lanes 0-3 and 8-11 of a row read lane + 4, the others lane - 4
-    const int up = dpp_mov<0x104, 0x5>(v, v);
-    return dpp_mov<0x114, 0xa>(up, v);
-}
-__device__ __forceinline__ double make_double(unsigned lo, unsigned hi) {
-    return __hiloint2double((int)hi, (int)lo);
-}
-__device__ __forceinline__ double wave_sum(double v) {
-    {
-        const auto l = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v),
-                                                        false, false);
-        const auto h = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v),
-                                                        false, false);
-        v = make_double(l[0], h[0]) + make_double(l[1], h[1]);
-    }
-    {
-        const auto l = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v),
-                                                        false, false);
-        const auto h = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v),
-                                                        false, false);
-        v = make_double(l[0], h[0]) + make_double(l[1], h[1]);
-    }
-    v += make_double(lane_xor<8>(__double2loint(v)), lane_xor<8>(__double2hiint(v)));
-    v += make_double(lane_xor<4>(__double2loint(v)), lane_xor<4>(__double2hiint(v)));
-    v += make_double(lane_xor<2>(__double2loint(v)), lane_xor<2>(__double2hiint(v)));
-    v += make_double(lane_xor<1>(__double2loint(v)), lane_xor<1>(__double2hiint(v)));
-    return v;
-}
-
 // ---------------------------------------------------------------- coarsest
 // LDS of a coarse solve: the matrix (CG: nine bands, Cholesky: the factor's
 // band up to level 3; at level 4 the factor's 44 KB stay in global memory),
