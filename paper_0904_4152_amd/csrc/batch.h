@@ -142,7 +142,8 @@ private:
     int device_ = 0, cap_ = 0, Lmax_ = 0, Lc_ = 1, nu_pre_ = 2, nu_post_ = 2;
     hipStream_t st_ = nullptr;
     BProb* d_probs_ = nullptr;
-    BState* d_state_ = nullptr;
+    BState* d_state_ = nullptr;       // [-1]: the union of the live problems' flags
+    BState* d_state_alloc_ = nullptr;
     BState* h_state_ = nullptr;  // pinned
     int* d_wl_ = nullptr;
     int* d_iter_ = nullptr;   // iterations run (device counter)

@@ -16,6 +16,7 @@
 #include <algorithm>
 #include <array>
 #include <atomic>
+#include <climits>
 #include <cmath>
 #include <cstring>
 #include <map>
@@ -51,36 +52,71 @@ enum { K_NORM = 0, K_S32 = 1, K_S64 = 2 };
 enum { F_BN = 0, F_S = 1, F_R32 = 3 };
 enum { PH_INIT = 0, PH_OUTER = 2, PH_INNER = 4 };
 
-// Work list: wl[0] = count, wl[1] = cap, prob[cap] at wl+2, tile prefix
-// start[cap+1] at wl+2+cap.  Item t belongs to the last k with start[k] <= t.
-__device__ __forceinline__ int wl_total(const int* wl) { return wl[2 + wl[1] + wl[0]]; }
+// A work list: {count, total tiles, step, 0}, then 64 samples and the entries,
+// both pairs {first tile, problem}.  Item t belongs to the last entry whose
+// first tile is <= t.  Sample i is entry i * step (step = count / 64 rounded
+// up), so the header and the samples, loaded together, find the item of a
+// list of up to 64 problems and one more load that of up to 4096: a tile's
+// chain of dependent loads before its own data is two or three long (header,
+// entries, the problem's descriptor).  Pads hold INT_MAX.
+constexpr int WL_SAMPLES = 4;
+constexpr int WL_ENTRIES = WL_SAMPLES + 2 * 64;
+inline int wl_entry_cap(int cap) { return (cap + 63) / 64 * 64; }
+inline int wl_stride(int cap) { return WL_ENTRIES + 2 * wl_entry_cap(cap); }
 
-//
-// Found by a 64-way search: each round the wavefront's lanes test 64 evenly
-// spaced entries of the range at once and keep the segment after the last
-// one that is <= t (the entries are non-decreasing and start[0] = 0), so a
-// list of up to 4096 problems takes two rounds of loads, not twelve
-// dependent ones.  Every lane of the wavefront must call it with the same t.
+struct WlHead {
+    int count, total, step;
+    int2 sample;  // this lane's
+};
+
+__device__ __forceinline__ const int2* wl_entries(const int* wl) {
+    return reinterpret_cast<const int2*>(wl + WL_ENTRIES);
+}
+
+__device__ __forceinline__ WlHead wl_open(const int* wl) {
+    const int4 h = *reinterpret_cast<const int4*>(wl);
+    const int2 s = reinterpret_cast<const int2*>(wl + WL_SAMPLES)[threadIdx.x & 63];
+    return {h.x, h.y, h.z, s};
+}
+
+// Lane of the last entry <= t among the wavefront's (non-decreasing, lane 0
+// always holds).
+__device__ __forceinline__ int last_le(int v, int t) { return __popcll(__ballot(v <= t)) - 1; }
+
+// Problem and tile of item t (the same t on every lane of the wavefront).
+__device__ __forceinline__ void wl_item(const int* wl, const WlHead& h, int t, int* p, int* tile) {
+    const int lane = (int)(threadIdx.x & 63);
+    int k = last_le(h.sample.x, t);
+    int2 v = h.sample;
+    if (h.step > 1) {
+        const int2* e = wl_entries(wl) + k * h.step;
+        int len = min(h.step, h.count - k * h.step);
+        while (len > 64) {
+            const int step = (len + 63) >> 6, off = lane * step;
+            k = last_le(off < len ? e[off].x : INT_MAX, t);
+            e += k * step;
+            len = min(step, len - k * step);
+        }
+        v = lane < len ? e[lane] : int2{INT_MAX, 0};
+        k = last_le(v.x, t);
+    }
+    *p = __builtin_amdgcn_readlane(v.y, k);
+    *tile = t - __builtin_amdgcn_readlane(v.x, k);
+}
+
+// Last index of a[0, count) (non-decreasing, a[0] <= t) with a[k] <= t, by
+// 64-way search; every lane of the wavefront calls it with the same t.
 __device__ __forceinline__ int find_last_le(const int* a, int count, int t) {
     const int lane = (int)(threadIdx.x & 63);
     int lo = 0, len = count;
     while (len > 1) {
         const int step = (len + 63) >> 6;
         const int off = lane * step;
-        const bool ok = off < len && a[lo + off] <= t;
-        const int last = 63 - __clzll(__ballot(ok));  // lane 0 always holds
+        const int last = last_le(off < len ? a[lo + off] : INT_MAX, t);
         lo += last * step;
         len = min(step, len - last * step);
     }
     return lo;
-}
-
-__device__ __forceinline__ void wl_item(const int* wl, int t, int* p, int* tile) {
-    const int cap = wl[1];
-    const int* start = wl + 2 + cap;
-    const int k = find_last_le(start, wl[0], t);
-    *p = wl[2 + k];
-    *tile = t - start[k];
 }
 
 // Compacted items: the items of the listed problems whose flags meet mask,
@@ -91,17 +127,20 @@ __device__ __forceinline__ void wl_item(const int* wl, int t, int* p, int* tile)
 // Lists of up to ACTIVE_MAX problems; every thread of the workgroup calls it.
 constexpr int ACTIVE_MAX = 4096;
 
-__device__ int active_prefix(const int* wl, const BState* __restrict__ state, int mask,
-                             int* cum) {
+__device__ int active_prefix(const int* wl, const WlHead& h, const BState* __restrict__ state,
+                             int mask, int* cum) {
     __shared__ int wsum[BLOCK / 64];
-    const int count = wl[0], cap = wl[1];
-    const int* prob = wl + 2;
-    const int* start = wl + 2 + cap;
+    const int count = h.count;
+    const int2* e = wl_entries(wl);
+    auto items = [&](int k) {
+        const int n = (k + 1 < count ? e[k + 1].x : h.total) - e[k].x;
+        return (state[e[k].y].flags & mask) ? n : 0;
+    };
     const int per = (count + BLOCK - 1) / BLOCK;
     const int k0 = min((int)threadIdx.x * per, count), k1 = min(k0 + per, count);
     int mine = 0;
     for (int k = k0; k < k1; ++k)
-        mine += (state[prob[k]].flags & mask) ? start[k + 1] - start[k] : 0;
+        mine += items(k);
     // exclusive scan of the threads' sums: within each wavefront, then
     // across the wavefronts
     const int lane = (int)(threadIdx.x & 63), w = (int)(threadIdx.x >> 6);
@@ -122,7 +161,7 @@ __device__ int active_prefix(const int* wl, const BState* __restrict__ state, in
     int run = base + inc - mine;
     for (int k = k0; k < k1; ++k) {
         cum[k] = run;
-        run += (state[prob[k]].flags & mask) ? start[k + 1] - start[k] : 0;
+        run += items(k);
     }
     __syncthreads();
     return total;
@@ -132,35 +171,36 @@ __device__ __forceinline__ float* role32(const BLevel& lv, int r) { return r ? l
 
 // Work items of list wl for the problems whose flags meet `mask`.  The
 // whole launch returns at once when no problem has any of those flags:
-// state[cap] holds the union of every live problem's flags, written by the
+// state[-1] holds the union of every live problem's flags, written by the
 // control kernel after each phase (and set to all bits when new problems
 // are uploaded).
 #define FOR_ITEMS(wl)                                              \
-    if (!(state[wl[1]].flags & mask)) return;                      \
-    const int total_ = wl_total(wl);                               \
-    for (int t_ = blockIdx.x; t_ < total_; t_ += gridDim.x) {      \
+    const WlHead head_ = wl_open(wl);                              \
+    if (!(state[-1].flags & mask)) return;                         \
+    for (int t_ = blockIdx.x; t_ < head_.total; t_ += gridDim.x) { \
         int p, tile;                                               \
-        wl_item(wl, t_, &p, &tile);                                \
+        wl_item(wl, head_, t_, &p, &tile);                         \
         const BProb& P = probs[p];                                 \
         const int flags = state[p].flags;
 
 // The same for the listed problems whose flags meet `mask` only: the items
 // of the others are never visited (see active_prefix).
-#define FOR_ACTIVE_ITEMS(wl)                                                           \
-    if (!(state[wl[1]].flags & mask)) return;                                          \
-    __shared__ int cum_[ACTIVE_MAX];                                                   \
-    const bool compact_ = wl[0] <= ACTIVE_MAX;                                         \
-    const int total_ = compact_ ? active_prefix(wl, state, mask, cum_) : wl_total(wl); \
-    for (int t_ = blockIdx.x; t_ < total_; t_ += gridDim.x) {                          \
-        int p, tile;                                                                   \
-        if (compact_) {                                                                \
-            const int k_ = find_last_le(cum_, wl[0], t_);                              \
-            p = wl[2 + k_];                                                            \
-            tile = t_ - cum_[k_];                                                      \
-        } else {                                                                       \
-            wl_item(wl, t_, &p, &tile);                                                \
-        }                                                                              \
-        const BProb& P = probs[p];                                                     \
+#define FOR_ACTIVE_ITEMS(wl)                                                            \
+    const WlHead head_ = wl_open(wl);                                                   \
+    if (!(state[-1].flags & mask)) return;                                              \
+    __shared__ int cum_[ACTIVE_MAX];                                                    \
+    const bool compact_ = head_.count <= ACTIVE_MAX;                                    \
+    const int total_ = compact_ ? active_prefix(wl, head_, state, mask, cum_) : head_.total; \
+    for (int t_ = blockIdx.x; t_ < total_; t_ += gridDim.x) {                           \
+        int p, tile;                                                                    \
+        if (compact_) {                                                                 \
+            const int k_ = find_last_le(cum_, head_.count, t_);                         \
+            p = wl_entries(wl)[k_].y;                                                   \
+            tile = t_ - cum_[k_];                                                       \
+        } else {                                                                        \
+            wl_item(wl, head_, t_, &p, &tile);                                          \
+        }                                                                               \
+        const BProb& P = probs[p];                                                      \
         const int flags = state[p].flags;
 
 #define END_ITEMS }
@@ -294,12 +334,12 @@ __global__ __launch_bounds__(dev::TAIL_THREADS) void kb_tail(const BProb* __rest
     FOR_ITEMS(wl)
     if (!(flags & mask) || P.L <= Lc) continue;
     __syncthreads();  // the previous item's cycle has read tl and its LDS
-    if (threadIdx.x == 0) {
-        const int top = min(P.L - 1, dev::TAIL_MAX);
-        for (int l = Lc; l <= top; ++l) {
-            const BLevel& v = P.lv[l];
-            tl.lv[l] = dev::TailLevel<float>{v.bands32, v.x32, v.b32, v.bs};
-        }
+    // one thread per level, so that their loads go out together
+    const int top = min(P.L - 1, dev::TAIL_MAX), l = (int)threadIdx.x;
+    if (l >= Lc && l <= top) {
+        const BLevel& v = P.lv[l];
+        tl.lv[l] = dev::TailLevel<float>{v.bands32, v.x32, v.b32, v.bs};
+    } else if (l == dev::TAIL_MAX + 1) {
         tl.cs = P.cs;
         tl.top = top;
         tl.Lc = Lc;
@@ -323,6 +363,39 @@ __global__ __launch_bounds__(BLOCK) void kb_coarse(const BProb* __restrict__ pro
     END_ITEMS
 }
 
+// What a fused pass reads of its problem's descriptor, loaded at once (a test
+// of the problem's flags between the loads would make two memory latencies of
+// them).
+struct FusedLevel {
+    const float* bands32;
+    float *x32, *b32, *t32, *bc, *xc;
+    double* partials;
+    int64_t bs;
+    int N, rh, cw, nstrips, L, dmask;
+    float omega;
+    __device__ __forceinline__ FusedLevel(const BProb& P, int l) {
+        const BLevel &v = P.lv[l], &c = P.lv[l - 1];
+        bands32 = v.bands32;
+        x32 = v.x32;
+        b32 = v.b32;
+        t32 = v.t32;
+        bc = c.b32;
+        xc = c.x32;
+        partials = P.partials;
+        bs = v.bs;
+        N = v.N;
+        rh = v.rh;
+        cw = v.cw;
+        nstrips = v.nstrips;
+        L = P.L;
+        dmask = P.dmask;
+        omega = (float)P.omega;
+        asm volatile("" ::"s"(bands32), "s"(x32), "s"(b32), "s"(t32), "s"(bc), "s"(xc),
+                     "s"(partials), "s"(bs), "s"(N), "s"(rh), "s"(cw), "s"(nstrips), "s"(L),
+                     "s"(dmask));
+    }
+};
+
 // Fused pre-smoothing pass at level l (two sweeps, defect, restriction) for
 // the problems in their inner loop; iterate x -> t, coarse rhs at l-1.
 template <int BT>
@@ -330,16 +403,16 @@ __global__ __launch_bounds__(BT) void kb_fpre(const BProb* __restrict__ probs,
                                               const BState* __restrict__ state,
                                               const int* __restrict__ wl, int l, int mask) {
     FOR_ITEMS(wl)
+    const FusedLevel lv(P, l);
     if (!(flags & mask)) continue;
-    const BLevel& lv = P.lv[l];
     const int strip = tile % lv.nstrips, chunk = tile / lv.nstrips;
-    const float om = (float)P.omega;
-    if (l < P.L || state[p].first)
+    const float om = lv.omega;
+    if (l < lv.L || state[p].first)
         dev::pre_tile<float, true, BT, false>(lv.bands32, lv.bs, lv.N, lv.x32, lv.b32, om, lv.t32,
-                                       P.lv[l - 1].b32, P.dmask, strip, chunk, lv.rh, lv.cw);
+                                       lv.bc, lv.dmask, strip, chunk, lv.rh, lv.cw);
     else
         dev::pre_tile<float, false, BT, false>(lv.bands32, lv.bs, lv.N, lv.x32, lv.b32, om, lv.t32,
-                                        P.lv[l - 1].b32, P.dmask, strip, chunk, lv.rh, lv.cw);
+                                        lv.bc, lv.dmask, strip, chunk, lv.rh, lv.cw);
     END_ITEMS
 }
 
@@ -350,15 +423,15 @@ __global__ __launch_bounds__(BT) void kb_fpost(const BProb* __restrict__ probs,
                                                const BState* __restrict__ state,
                                                const int* __restrict__ wl, int l, int mask) {
     FOR_ITEMS(wl)
+    const FusedLevel lv(P, l);
     if (!(flags & mask)) continue;
-    const BLevel& lv = P.lv[l];
     const int strip = tile % lv.nstrips, chunk = tile / lv.nstrips;
-    const float om = (float)P.omega;
-    if (l == P.L)
-        dev::post_tile<float, true, BT, false>(lv.bands32, lv.bs, lv.N, lv.t32, P.lv[l - 1].x32, lv.b32,
-                                        om, lv.x32, P.partials, strip, chunk, lv.rh, lv.cw);
+    const float om = lv.omega;
+    if (l == lv.L)
+        dev::post_tile<float, true, BT, false>(lv.bands32, lv.bs, lv.N, lv.t32, lv.xc, lv.b32,
+                                        om, lv.x32, lv.partials, strip, chunk, lv.rh, lv.cw);
     else
-        dev::post_tile<float, false, BT, false>(lv.bands32, lv.bs, lv.N, lv.t32, P.lv[l - 1].x32,
+        dev::post_tile<float, false, BT, false>(lv.bands32, lv.bs, lv.N, lv.t32, lv.xc,
                                          lv.b32, om, lv.x32, nullptr, strip, chunk, lv.rh, lv.cw);
     END_ITEMS
 }
@@ -371,17 +444,17 @@ __global__ __launch_bounds__(64 * W) void kb_fpre_blk(const BProb* __restrict__ 
                                                      int mask) {
     __shared__ dev::BlockLds<float, W> s;
     FOR_ITEMS(wl)
+    const FusedLevel lv(P, l);
     if (!(flags & mask)) continue;
     __syncthreads();  // the previous tile is done with LDS
-    const BLevel& lv = P.lv[l];
     const int strip = tile % lv.nstrips, chunk = tile / lv.nstrips;
-    const float om = (float)P.omega;
-    if (l < P.L || state[p].first)
+    const float om = lv.omega;
+    if (l < lv.L || state[p].first)
         dev::pre_block<float, true, W, 2>(s, lv.bands32, lv.bs, lv.N, lv.x32, lv.b32, om, lv.t32,
-                                          P.lv[l - 1].b32, P.dmask, strip, chunk);
+                                          lv.bc, lv.dmask, strip, chunk);
     else
         dev::pre_block<float, false, W, 2>(s, lv.bands32, lv.bs, lv.N, lv.x32, lv.b32, om, lv.t32,
-                                           P.lv[l - 1].b32, P.dmask, strip, chunk);
+                                           lv.bc, lv.dmask, strip, chunk);
     END_ITEMS
 }
 
@@ -392,16 +465,16 @@ __global__ __launch_bounds__(64 * W) void kb_fpost_blk(const BProb* __restrict__
                                                       int mask) {
     __shared__ dev::BlockLds<float, W> s;
     FOR_ITEMS(wl)
+    const FusedLevel lv(P, l);
     if (!(flags & mask)) continue;
     __syncthreads();  // the previous tile is done with LDS
-    const BLevel& lv = P.lv[l];
     const int strip = tile % lv.nstrips, chunk = tile / lv.nstrips;
-    const float om = (float)P.omega;
-    if (l == P.L)
-        dev::post_block<float, true, W, 2>(s, lv.bands32, lv.bs, lv.N, lv.t32, P.lv[l - 1].x32,
-                                           lv.b32, om, lv.x32, P.partials, strip, chunk);
+    const float om = lv.omega;
+    if (l == lv.L)
+        dev::post_block<float, true, W, 2>(s, lv.bands32, lv.bs, lv.N, lv.t32, lv.xc,
+                                           lv.b32, om, lv.x32, lv.partials, strip, chunk);
     else
-        dev::post_block<float, false, W, 2>(s, lv.bands32, lv.bs, lv.N, lv.t32, P.lv[l - 1].x32,
+        dev::post_block<float, false, W, 2>(s, lv.bands32, lv.bs, lv.N, lv.t32, lv.xc,
                                             lv.b32, om, lv.x32, nullptr, strip, chunk);
     END_ITEMS
 }
@@ -513,10 +586,10 @@ __global__ __launch_bounds__(BLOCK) void kb_update(const BProb* __restrict__ pro
 __global__ __launch_bounds__(BLOCK) void kb_zero_unwritten(const BProb* __restrict__ probs,
                                                            const BState* __restrict__ state,
                                                            const int* __restrict__ wl) {
-    const int total = wl_total(wl);
-    for (int t = blockIdx.x; t < total; t += gridDim.x) {
+    const WlHead head = wl_open(wl);
+    for (int t = blockIdx.x; t < head.total; t += gridDim.x) {
         int p, tile;
-        wl_item(wl, t, &p, &tile);
+        wl_item(wl, head, t, &p, &tile);
         const BProb& P = probs[p];
         const BState& S = state[p];
         const bool zero = (S.bn == 0.0 && S.status == MG_OK) || (P.zero_guess && S.outer == 0);
@@ -615,10 +688,10 @@ __device__ void transition(const BProb& P, BState& S, int phase) {
 __device__ void finalize_items(const BProb* __restrict__ probs, BState* __restrict__ state,
                                const int* __restrict__ wl, int kind, int field, int mask,
                                int fused_above, int phase) {
-    const int total = wl_total(wl);
-    for (int t = blockIdx.x; t < total; t += gridDim.x) {
+    const WlHead head = wl_open(wl);
+    for (int t = blockIdx.x; t < head.total; t += gridDim.x) {
         int p, tile;
-        wl_item(wl, t, &p, &tile);
+        wl_item(wl, head, t, &p, &tile);
         const BProb& P = probs[p];
         if (!(state[p].flags & mask)) continue;
         const BLevel& F = P.lv[P.L];
@@ -647,7 +720,7 @@ __device__ void finalize_items(const BProb* __restrict__ probs, BState* __restri
 }
 
 // After a phase's transitions (one block; thread per slot): the union of
-// every live problem's flags into state[cap] (the early exit of the stage
+// every live problem's flags into state[-1] (the early exit of the stage
 // kernels), and at the end of an iteration (PH_INNER) the report to the
 // host, in entry k mod ITER_RING of the pinned ring (k = iterations so far;
 // entries of 2 + cap ints): the problems not done, those still in their
@@ -659,11 +732,11 @@ __device__ void report_all(const BProb* __restrict__ probs, BState* __restrict__
     int* entry = nullptr;
     if (phase == PH_INNER) entry = ring + (int64_t)(*iter % ITER_RING) * (2 + cap);
     for (int p = threadIdx.x; p < cap; p += BLOCK) {
-        if (probs[p].L == 0) {
+        const int L = probs[p].L, f = state[p].flags;  // both loads at once
+        if (L == 0) {
             if (entry) entry[2 + p] = 0;
             continue;
         }
-        const int f = state[p].flags;
         if (!(f & BF_DONE)) ++live;
         if (f == BF_INNER) ++sure;
         present |= f;
@@ -679,7 +752,7 @@ __device__ void report_all(const BProb* __restrict__ probs, BState* __restrict__
             int v = 0;
 #pragma unroll
             for (int w = 0; w < BLOCK / 64; ++w) v |= wor[w];
-            state[cap].flags = v;
+            state[-1].flags = v;
         }
     }
     if (phase == PH_INNER) {
@@ -702,12 +775,12 @@ __device__ void report_all(const BProb* __restrict__ probs, BState* __restrict__
 // (report_all).  The ticket is back to zero after.
 __global__ __launch_bounds__(BLOCK) void kb_finctl(const BProb* __restrict__ probs,
                                                    BState* __restrict__ state,
-                                                   const int* __restrict__ wl, int kind,
+                                                   const int* __restrict__ wl, int cap, int kind,
                                                    int field, int mask, int fused_above,
                                                    int phase, int* __restrict__ iter,
                                                    int* __restrict__ ring,
                                                    unsigned* __restrict__ ticket) {
-    if (state[wl[1]].flags & mask)
+    if (state[-1].flags & mask)
         finalize_items(probs, state, wl, kind, field, mask, fused_above, phase);
     __shared__ unsigned last;
     __syncthreads();
@@ -718,7 +791,7 @@ __global__ __launch_bounds__(BLOCK) void kb_finctl(const BProb* __restrict__ pro
     __syncthreads();
     if (!last) return;
     __threadfence();
-    report_all(probs, state, wl[1], phase, iter, ring);
+    report_all(probs, state, cap, phase, iter, ring);
     if (threadIdx.x == 0) *ticket = 0u;
 }
 
@@ -730,7 +803,7 @@ BatchEngine::~BatchEngine() {
             if (g) (void)hipGraphExecDestroy(g);
     if (st_) (void)hipStreamDestroy(st_);
     if (d_probs_) (void)hipFree(d_probs_);
-    if (d_state_) (void)hipFree(d_state_);
+    if (d_state_alloc_) (void)hipFree(d_state_alloc_);
     if (d_wl_) (void)hipFree(d_wl_);
     if (setup_st_) (void)hipStreamDestroy(setup_st_);
     if (read_st_) (void)hipStreamDestroy(read_st_);
@@ -765,7 +838,7 @@ mg_status BatchEngine::init(int device, int capacity, int Lmax, int Lc, int nu_p
     MG_HIP(hipStreamCreateWithFlags(&read_st_, hipStreamNonBlocking));
     MG_HIP(hipEventCreateWithFlags(&ev_setup_, hipEventDisableTiming));
     for (hipEvent_t& e : ev_upload_) MG_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-    const size_t wl_ints = (size_t)NLISTS * (3 + 2 * cap_);
+    const size_t wl_ints = (size_t)NLISTS * wl_stride(cap_);
     for (int b = 0; b < 2; ++b) {
         MG_HIP(hipHostMalloc((void**)&h_probs_stage_[b], sizeof(BProb) * cap_,
                              hipHostMallocDefault));
@@ -775,8 +848,9 @@ mg_status BatchEngine::init(int device, int capacity, int Lmax, int Lc, int nu_p
     }
     MG_HIP(hipHostMalloc((void**)&h_fetch_, sizeof(BState), hipHostMallocDefault));
     MG_HIP(hipMalloc(&d_probs_, sizeof(BProb) * cap_));
-    MG_HIP(hipMalloc(&d_state_, sizeof(BState) * (cap_ + 1)));  // + flags union
-    MG_HIP(hipMalloc(&d_wl_, sizeof(int) * NLISTS * (3 + 2 * cap_)));
+    MG_HIP(hipMalloc(&d_state_alloc_, sizeof(BState) * (cap_ + 1)));
+    d_state_ = d_state_alloc_ + 1;  // d_state_[-1]: the union of the flags
+    MG_HIP(hipMalloc(&d_wl_, sizeof(int) * wl_ints));
     MG_HIP(hipMalloc(&d_iter_, 64));
     MG_HIP(hipMemset(d_iter_, 0, 64));
     launched_ = 0;
@@ -794,7 +868,7 @@ mg_status BatchEngine::init(int device, int capacity, int Lmax, int Lc, int nu_p
     {
         BState all{};
         all.flags = -1;
-        MG_HIP(hipMemcpy(d_state_ + cap_, &all, sizeof(BState), hipMemcpyHostToDevice));
+        MG_HIP(hipMemcpy(d_state_ - 1, &all, sizeof(BState), hipMemcpyHostToDevice));
     }
     probs_dirty_ = true;
     return MG_OK;
@@ -911,23 +985,28 @@ int BatchEngine::problems_at(int l) const {
 
 // Work lists of the current composition.
 void BatchEngine::build_lists() {
-    const int stride = 3 + 2 * cap_;
+    const int stride = wl_stride(cap_);
     h_wl_.assign((size_t)NLISTS * stride, 0);
     auto fill = [&](int id, auto eligible, auto tiles) {
         int* w = h_wl_.data() + (size_t)id * stride;
+        int* e = w + WL_ENTRIES;
         int count = 0, acc = 0;
-        int* prob = w + 2;
-        int* start = w + 2 + cap_;
         for (int s = 0; s < cap_; ++s) {
             if (hp_[s].L == 0 || !eligible(hp_[s])) continue;
-            prob[count] = s;
-            start[count] = acc;
+            e[2 * count] = acc;
+            e[2 * count + 1] = s;
             acc += tiles(hp_[s]);
             ++count;
         }
-        start[count] = acc;
+        const int step = std::max(1, (count + 63) / 64);
         w[0] = count;
-        w[1] = cap_;
+        w[1] = acc;
+        w[2] = step;
+        for (int i = 0; i < 64; ++i) {
+            const bool in = i * step < count;
+            w[WL_SAMPLES + 2 * i] = in ? e[2 * i * step] : INT_MAX;
+            w[WL_SAMPLES + 2 * i + 1] = in ? e[2 * i * step + 1] : 0;
+        }
     };
     auto ntiles = [](int64_t n) { return (int)((n + TILE - 1) / TILE); };
     auto fused_here = [](const BProb& P, int l) {
@@ -1075,7 +1154,7 @@ mg_status BatchEngine::upload_async() {
         BState& A = h_start_stage_[b][cap_];
         std::memset(&A, 0, sizeof(BState));
         A.flags = -1;
-        MG_HIP(hipMemcpyAsync(d_state_ + cap_, &A, sizeof(BState), hipMemcpyHostToDevice, st_));
+        MG_HIP(hipMemcpyAsync(d_state_ - 1, &A, sizeof(BState), hipMemcpyHostToDevice, st_));
         init_pending_ = true;
     }
     MG_HIP(hipEventRecord(ev_upload_[b], st_));
@@ -1118,7 +1197,7 @@ mg_status BatchEngine::fetch_state(int s, BState* out) {
 // One fused pass (pre or post) at level l over the problems whose flags meet
 // mask, as in an iteration.
 hipError_t BatchEngine::launch_fused(int l, bool pre, int mask) {
-    const int stride = 3 + 2 * cap_;
+    const int stride = wl_stride(cap_);
     const int* wl = d_wl_ + (size_t)wl_fused(l) * stride;
     const int bt = bt_[l];
     if (blk_[l]) {
@@ -1224,7 +1303,7 @@ mg_status BatchEngine::tune(int reps, std::vector<mg_tile_choice>* out) {
 }
 
 hipError_t BatchEngine::enqueue_iteration(bool with_init) {
-    const int stride = 3 + 2 * cap_;
+    const int stride = wl_stride(cap_);
     auto W = [&](int id) { return (const int*)(d_wl_ + (size_t)id * stride); };
     const dim3 G(STAGE_GRID), B(BLOCK);
     const dim3 GA(std::min(cap_, 1024));
@@ -1241,7 +1320,7 @@ hipError_t BatchEngine::enqueue_iteration(bool with_init) {
     // new problems: ||b||
     if (with_init) {
         LAUNCH(kb_sumsq, G, B, 0, st_, P, S, W(WL_FINEST), 0, (int)BF_INIT);
-        LAUNCH(kb_finctl, GA, B, 0, st_, P, S, W(WL_ALL), (int)K_NORM, (int)F_BN, (int)BF_INIT,
+        LAUNCH(kb_finctl, GA, B, 0, st_, P, S, W(WL_ALL), cap_, (int)K_NORM, (int)F_BN, (int)BF_INIT,
                -1, (int)PH_INIT, d_iter_, h_ring_, ticket);
     }
     // finished inner loops: x += s c; then, for them and the new problems,
@@ -1249,7 +1328,7 @@ hipError_t BatchEngine::enqueue_iteration(bool with_init) {
     const int om = BF_OUTER | BF_UPDATE;
     LAUNCH(kb_update, G, B, 0, st_, P, S, W(WL_FINEST), (int)BF_UPDATE);
     LAUNCH(kb_outer_defect, G, B, 0, st_, P, S, W(WL_FINEST), om);
-    LAUNCH(kb_finctl, GA, B, 0, st_, P, S, W(WL_ALL), (int)K_S64, (int)F_S, om, -1,
+    LAUNCH(kb_finctl, GA, B, 0, st_, P, S, W(WL_ALL), cap_, (int)K_S64, (int)F_S, om, -1,
            (int)PH_OUTER, d_iter_, h_ring_, ticket);
     // one FP32 V-cycle for every problem in its inner loop
     const int m = BF_INNER;
@@ -1263,16 +1342,17 @@ hipError_t BatchEngine::enqueue_iteration(bool with_init) {
         for (int l = Lmax_; l > Lc_; --l)
             if (launch_mask_ & (1u << l)) FUSED(true, l)
         LAUNCH(kb_tail, GA, dim3(dev::TAIL_THREADS), 0, st_, P, S, W(WL_ALL), Lc_, m);
-        LAUNCH(kb_coarse, GA, B, 0, st_, P, S, W(WL_ALL), Lc_, m, Lc_);
+        if (launch_mask_ & 1u)  // problems without a level above the coarse one
+            LAUNCH(kb_coarse, GA, B, 0, st_, P, S, W(WL_ALL), Lc_, m, Lc_);
         for (int l = Lc_ + 1; l <= Lmax_; ++l)
             if (launch_mask_ & (1u << l)) FUSED(false, l)
 #undef FUSED
-        // problems without a level above the coarse one: residual from a defect pass
+        // their residual from a defect pass
         if (launch_mask_ & 1u)
             LAUNCH(kb_inner_norm, G, B, 0, st_, P, S, W(WL_FINEST_COARSE), m, Lc_);
         if (launch_mask_ & (1u << 31))
             LAUNCH(kb_segsum, G, B, 0, st_, P, S, W(WL_SEGS32), m, Lc_);
-        LAUNCH(kb_finctl, GA, B, 0, st_, P, S, W(WL_ALL), (int)K_S32, (int)F_R32, m, Lc_,
+        LAUNCH(kb_finctl, GA, B, 0, st_, P, S, W(WL_ALL), cap_, (int)K_S32, (int)F_R32, m, Lc_,
                (int)PH_INNER, d_iter_, h_ring_, ticket);
         return hipSuccess;
     }
@@ -1308,7 +1388,7 @@ hipError_t BatchEngine::enqueue_iteration(bool with_init) {
     LAUNCH(kb_inner_norm, G, B, 0, st_, P, S, W(WL_FINEST), m, -1);
     if (launch_mask_ & (1u << 31))
         LAUNCH(kb_segsum, G, B, 0, st_, P, S, W(WL_SEGS32), m, -1);
-    LAUNCH(kb_finctl, GA, B, 0, st_, P, S, W(WL_ALL), (int)K_S32, (int)F_R32, m, -1,
+    LAUNCH(kb_finctl, GA, B, 0, st_, P, S, W(WL_ALL), cap_, (int)K_S32, (int)F_R32, m, -1,
            (int)PH_INNER, d_iter_, h_ring_, ticket);
 #undef LAUNCH
     return hipSuccess;
@@ -1394,7 +1474,7 @@ mg_status BatchEngine::run(int64_t iter_cap, int64_t* iterations) {
 
 mg_status BatchEngine::zero_unwritten() {
     MG_HIP(hipSetDevice(device_));
-    const int stride = 3 + 2 * cap_;
+    const int stride = wl_stride(cap_);
     hipLaunchKernelGGL(kb_zero_unwritten, dim3(STAGE_GRID), dim3(BLOCK), 0, st_, d_probs_,
                        d_state_, (const int*)(d_wl_ + (size_t)WL_FINEST * stride));
     MG_HIP(hipGetLastError());
