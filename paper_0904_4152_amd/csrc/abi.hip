@@ -236,25 +236,29 @@ mg_status mg_hierarchy_create_bc(mg_context* ctx, int L, int Lc, double jitter, 
     h->Lc = Lc;
     h->dmask = dirichlet_sides;
     h->charged = total;
-    std::vector<void*> ptrs;
-    for (size_t s : sizes) {
-        void* p = nullptr;
-        if (hipMalloc(&p, round_alloc(s)) != hipSuccess) {
-            (void)hipGetLastError();
-            for (void* q : ptrs) (void)hipFree(q);
-            ctx->release(total);
-            delete h;
-            return fail(MG_ERR_NOMEM, "hipMalloc failed for hierarchy L=" + std::to_string(L));
-        }
-        ptrs.push_back(p);
+    // one allocation for all arrays (each on a 4 KB boundary): a hierarchy has
+    // seven a level, and the runtime's calls were most of the time it took to
+    // make a small one
+    void* base = nullptr;
+    if (hipMalloc(&base, total) != hipSuccess) {
+        (void)hipGetLastError();
+        ctx->release(total);
+        delete h;
+        return fail(MG_ERR_NOMEM, "hipMalloc failed for hierarchy L=" + std::to_string(L));
     }
-    h->allocs = ptrs;
-    for (size_t a = 0; a < ptrs.size(); ++a) {
-        if (hipMemset(ptrs[a], 0, round_alloc(sizes[a])) != hipSuccess) {
-            free_arrays(h);
-            ctx->release(total);
-            delete h;
-            return fail(MG_ERR_DEVICE, "hipMemset failed");
+    h->allocs.push_back(base);
+    if (hipMemset(base, 0, total) != hipSuccess) {
+        free_arrays(h);
+        ctx->release(total);
+        delete h;
+        return fail(MG_ERR_DEVICE, "hipMemset failed");
+    }
+    std::vector<void*> ptrs;
+    {
+        char* p = (char*)base;
+        for (size_t s : sizes) {
+            ptrs.push_back(p);
+            p += round_alloc(s);
         }
     }
     size_t a = 0;

@@ -99,7 +99,9 @@ public:
     // Device-to-host copies unordered with the iterations, for data of
     // finished problems only.
     mg_status fetch(const void* dev, void* host, size_t bytes);
-    mg_status fetch_state(int s, BState* out);
+    mg_status fetch_async(const void* dev, void* pinned, size_t bytes);
+    mg_status fetch_state_async(int s, BState* pinned);
+    mg_status fetch_wait();
     // Stream for building new problems (assembly); upload_async orders the
     // iterations after it.
     hipStream_t setup_stream() const { return setup_st_; }
@@ -157,7 +159,6 @@ private:
     BProb* h_probs_stage_[2] = {};   // pinned staging of descriptors,
     int* h_wl_stage_[2] = {};        // work lists
     BState* h_start_stage_[2] = {};  // and started states
-    BState* h_fetch_ = nullptr;      // pinned, one state
     std::vector<BProb> hp_;
     std::vector<int> h_wl_;
     std::vector<char> started_;

@@ -820,7 +820,6 @@ BatchEngine::~BatchEngine() {
         if (h_wl_stage_[b]) (void)hipHostFree(h_wl_stage_[b]);
         if (h_start_stage_[b]) (void)hipHostFree(h_start_stage_[b]);
     }
-    if (h_fetch_) (void)hipHostFree(h_fetch_);
 }
 
 mg_status BatchEngine::init(int device, int capacity, int Lmax, int Lc, int nu_pre,
@@ -846,7 +845,6 @@ mg_status BatchEngine::init(int device, int capacity, int Lmax, int Lc, int nu_p
         MG_HIP(hipHostMalloc((void**)&h_start_stage_[b], sizeof(BState) * (cap_ + 1),
                              hipHostMallocDefault));
     }
-    MG_HIP(hipHostMalloc((void**)&h_fetch_, sizeof(BState), hipHostMallocDefault));
     MG_HIP(hipMalloc(&d_probs_, sizeof(BProb) * cap_));
     MG_HIP(hipMalloc(&d_state_alloc_, sizeof(BState) * (cap_ + 1)));
     d_state_ = d_state_alloc_ + 1;  // d_state_[-1]: the union of the flags
@@ -1188,9 +1186,18 @@ mg_status BatchEngine::fetch(const void* dev, void* host, size_t bytes) {
     return MG_OK;
 }
 
-mg_status BatchEngine::fetch_state(int s, BState* out) {
-    if (mg_status e = fetch(d_state_ + s, h_fetch_, sizeof(BState))) return e;
-    *out = *h_fetch_;
+// The same without the wait, into pinned memory; fetch_wait waits for all.
+mg_status BatchEngine::fetch_async(const void* dev, void* host, size_t bytes) {
+    MG_HIP(hipMemcpyAsync(host, dev, bytes, hipMemcpyDeviceToHost, read_st_));
+    return MG_OK;
+}
+
+mg_status BatchEngine::fetch_state_async(int s, BState* pinned) {
+    return fetch_async(d_state_ + s, pinned, sizeof(BState));
+}
+
+mg_status BatchEngine::fetch_wait() {
+    MG_HIP(hipStreamSynchronize(read_st_));
     return MG_OK;
 }
 

@@ -10,6 +10,8 @@
 #pragma once
 
 #include <algorithm>
+#include <initializer_list>
+#include <utility>
 #include <atomic>
 #include <chrono>
 #include <condition_variable>
@@ -18,6 +20,7 @@
 #include <deque>
 #include <list>
 #include <mutex>
+#include <new>
 #include <string>
 #include <thread>
 #include <unordered_map>
@@ -37,9 +40,56 @@ struct SchedRequest {
     double t_submit = 0.0, t_admit = 0.0;  // executor clock, seconds
 };
 
+// A solution on the host, in memory of the executor's (pinned, given back
+// when the result is collected) or of its own.
+class SolutionBuffer {
+public:
+    using Release = void (*)(void* owner, double* p, size_t n);
+    SolutionBuffer() = default;
+    SolutionBuffer(double* p, size_t n, Release release, void* owner)
+        : p_(p), n_(n), release_(release), owner_(owner) {}
+    SolutionBuffer(SolutionBuffer&& o) noexcept { swap(o); }
+    SolutionBuffer& operator=(SolutionBuffer&& o) noexcept {
+        SolutionBuffer t(std::move(o));
+        swap(t);
+        return *this;
+    }
+    SolutionBuffer& operator=(std::initializer_list<double> v) {
+        SolutionBuffer t = plain(v.size());
+        if (!t.empty()) std::copy(v.begin(), v.end(), t.p_);
+        swap(t);
+        return *this;
+    }
+    ~SolutionBuffer() {
+        if (p_) release_(owner_, p_, n_);
+    }
+    // n values of its own, not initialised (empty when there is no memory)
+    static SolutionBuffer plain(size_t n) {
+        double* p = new (std::nothrow) double[n];
+        if (!p) return {};
+        return {p, n, [](void*, double* q, size_t) { delete[] q; }, nullptr};
+    }
+    double* data() { return p_; }
+    const double* data() const { return p_; }
+    size_t size() const { return n_; }
+    bool empty() const { return n_ == 0; }
+
+private:
+    void swap(SolutionBuffer& o) noexcept {
+        std::swap(p_, o.p_);
+        std::swap(n_, o.n_);
+        std::swap(release_, o.release_);
+        std::swap(owner_, o.owner_);
+    }
+    double* p_ = nullptr;
+    size_t n_ = 0;
+    Release release_ = nullptr;
+    void* owner_ = nullptr;
+};
+
 struct SchedResult {
     mg_stats stats{};
-    std::vector<double> x;
+    SolutionBuffer x;
 };
 
 // What the scheduler needs from the device side.  Every call except now()
@@ -64,6 +114,12 @@ public:
     // Wait for iteration k (k < launched()); done[s] != 0 for every slot
     // whose problem had finished by its end (valid until the next call).
     virtual mg_status wait_iteration(int64_t k, const int** done) = 0;
+    // The finished problems of n slots are about to be collected: start
+    // every copy and wait for all of them once.
+    virtual mg_status begin_finish(const int* slots, void* const* hs, const int* keep_x, int n) {
+        (void)slots, (void)hs, (void)keep_x, (void)n;
+        return MG_OK;
+    }
     // Collect the finished problem of slot s (stats and, with keep_x, the
     // solution) and free the slot.
     virtual mg_status finish(int slot, void* h, int keep_x, SchedResult* out) = 0;
@@ -122,8 +178,8 @@ public:
 
     // MG_ERR_BUSY while pending; else the request's status and results.
     mg_status poll(uint64_t ticket, double* host_x, mg_stats* st, std::string* err) {
-        std::lock_guard<std::mutex> g(mu_);
-        if (done_.count(ticket)) return collect(ticket, host_x, st);
+        std::unique_lock<std::mutex> g(mu_);
+        if (done_.count(ticket)) return collect(g, ticket, host_x, st);
         if (pending_.count(ticket)) {
             if (fatal_ != MG_OK) {
                 if (err) *err = fatal_msg_;
@@ -152,7 +208,7 @@ public:
         }
         const uint64_t t = done_order_.front();
         *ticket = t;
-        return collect(t, host_x, st);
+        return collect(g, t, host_x, st);
     }
 
     void info(mg_server_info_t* info) {
@@ -269,20 +325,21 @@ private:
         return true;
     }
 
-    // Caller holds mu_.
-    mg_status collect(uint64_t t, double* host_x, mg_stats* st) {
+    // Caller holds mu_ through g; released for the copy of the solution (the
+    // worker goes on meanwhile).
+    mg_status collect(std::unique_lock<std::mutex>& g, uint64_t t, double* host_x, mg_stats* st) {
         auto it = done_.find(t);
-        SchedResult& r = it->second;
-        if (host_x && !r.x.empty()) std::memcpy(host_x, r.x.data(), r.x.size() * sizeof(double));
-        if (st) *st = r.stats;
-        const mg_status status = r.stats.status;
+        SchedResult r = std::move(it->second);
         done_.erase(it);
         for (auto q = done_order_.begin(); q != done_order_.end(); ++q)
             if (*q == t) {
                 done_order_.erase(q);
                 break;
             }
-        return status;
+        g.unlock();
+        if (host_x && !r.x.empty()) std::memcpy(host_x, r.x.data(), r.x.size() * sizeof(double));
+        if (st) *st = r.stats;
+        return r.stats.status;
     }
 
     void run() {
@@ -353,8 +410,22 @@ private:
             }
             const int64_t k = next++;
             if (next == ex_->launched()) busy_seconds_.store(busy_seconds_.load() + ex_->now() - t_busy);
+            fin_.clear();
+            fin_h_.clear();
+            fin_keep_.clear();
             for (int s = 0; s < (int)slot_h_.size(); ++s) {
                 if (!slot_h_[s] || slot_first_[s] > k || !done[s]) continue;
+                fin_.push_back(s);
+                fin_h_.push_back(slot_h_[s]);
+                fin_keep_.push_back(slot_req_[s].keep_x);
+            }
+            if (fin_.empty()) continue;
+            if (ex_->begin_finish(fin_.data(), fin_h_.data(), fin_keep_.data(),
+                                  (int)fin_.size()) != MG_OK) {
+                set_fatal(MG_ERR_DEVICE, "result copy failed: " + ex_->error_message());
+                return;
+            }
+            for (int s : fin_) {
                 if (!complete(s)) {
                     set_fatal(MG_ERR_DEVICE, "result copy failed: " + ex_->error_message());
                     return;
@@ -390,6 +461,8 @@ private:
     std::vector<int64_t> slot_first_;  // first iteration that sees the slot's problem
     std::list<PoolEntry> pool_;        // idle hierarchies, least recently used first
     bool dirty_ = false;               // slots changed since the last upload
+    std::vector<int> fin_, fin_keep_;  // slots finished in the iteration just reported
+    std::vector<void*> fin_h_;
 };
 
 }  // namespace mg
