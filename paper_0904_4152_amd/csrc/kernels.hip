@@ -18,6 +18,7 @@
 #include "device_ops.h"
 #include "fused_ops.h"
 #include "mg_internal.h"
+#include "mid_ops.h"
 #include "tail_ops.h"
 
 namespace mg {
@@ -262,6 +263,26 @@ __global__ __launch_bounds__(BT) void k_post(const T* __restrict__ bands, int64_
     if (lb < 0 || skipped(guard)) return;
     dev::post_tile<T, NORM, BT, STREAM>(bands, bs, N, x, xc, b, omega, xout, partials,
                                 (int)(lb % g.nstrips), (int)(lb / g.nstrips), g.rh, g.cw);
+}
+
+// A cycle's post pass and the next one's pre pass in one march
+// (dev::mid_tile): two workgroups (FP64) or three (FP32) of mid_threads lanes
+// a compute unit.
+template <typename T>
+constexpr int mid_threads() {
+    return sizeof(T) == 8 ? 192 : 256;
+}
+template <typename T>
+__global__ __launch_bounds__(mid_threads<T>(), sizeof(T) == 8 ? 2 : 3) void k_mid(
+    const T* __restrict__ bands, int64_t bs, int N, const T* __restrict__ x,
+    const T* __restrict__ xc, const T* __restrict__ b, T omega, T* __restrict__ xpost,
+    T* __restrict__ x2, T* __restrict__ bc, int dmask, double* __restrict__ partials,
+    dev::FusedGeom g, const double* __restrict__ guard) {
+    const int64_t lb = xcd_block((int64_t)g.nstrips * g.nchunks);
+    if (lb < 0 || skipped(guard)) return;
+    dev::mid_tile<T, mid_threads<T>()>(bands, bs, N, x, xc, b, omega, xpost, x2, bc, dmask,
+                                       partials, (int)(lb % g.nstrips), (int)(lb / g.nstrips),
+                                       g.rh, g.cw);
 }
 
 // The same passes in block tiles of W wavefronts, with NU sweeps.
@@ -1256,6 +1277,25 @@ hipError_t launch_post(const Level& lv, const T* bands, const T* x, const T* xc,
     return launch_reduce(partials, dev::fused_norm_parts(lv.N), scal, slot, host, st, guard, ctl);
 }
 
+// Where block tiles serve the separate passes they beat the merged march, whose
+// chain of row steps is as long as theirs is short (FP64 solve, L = 10: 0.91 ms
+// apart, 1.12 merged; L = 11, marching: 2.16 apart, 1.94 merged).
+bool use_mid(int N, int elem_bytes) { return !single_rule(N, elem_bytes).blk; }
+
+template <typename T>
+hipError_t launch_mid(const Level& lv, const T* bands, const T* x, const T* xc, const T* b, T omega,
+                      T* xpost, T* x2, T* bc, int dmask, double* partials, double* scal, int slot,
+                      double* host, hipStream_t st, const double* guard, RedCtl ctl) {
+    const int resident = 256 * (sizeof(T) == 8 ? 2 : 3);  // workgroups the chip holds
+    const dev::FusedGeom g = dev::mid_geom(lv.N, mid_threads<T>(), resident);
+    hipLaunchKernelGGL((k_mid<T>), dim3(grid8((int64_t)g.nstrips * g.nchunks)), dim3(g.bt), 0, st,
+                       bands, lv.bs, lv.N, x, xc, b, omega, xpost, x2, bc, dmask, partials, g,
+                       guard);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    return launch_reduce(partials, dev::fused_norm_parts(lv.N), scal, slot, host, st, guard, ctl);
+}
+
 // One sweep instead of two (V(1,1) and the like): block tiles of 8 rows, on
 // levels where the rule takes block tiles.
 bool one_sweep_blocks(int N, int elem_bytes) { return single_rule(N, elem_bytes).blk != 0; }
@@ -1492,6 +1532,9 @@ hipError_t launch_scalar_copy(double* scal, int from, int to, hipStream_t st) {
     template hipError_t launch_post<T>(const Level&, const T*, const T*, const T*, const T*, T, \
                                        T*, double*, double*, int, double*, hipStream_t,       \
                                        const double*, RedCtl);                                \
+    template hipError_t launch_mid<T>(const Level&, const T*, const T*, const T*, const T*, T, \
+                                      T*, T*, T*, int, double*, double*, int, double*,        \
+                                      hipStream_t, const double*, RedCtl);                    \
     template hipError_t launch_pre1<T>(const Level&, const T*, const T*, bool, const T*, T, T*, \
                                        T*, int, hipStream_t);                                 \
     template hipError_t launch_post1<T>(const Level&, const T*, const T*, const T*, const T*, \

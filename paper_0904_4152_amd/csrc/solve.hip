@@ -18,7 +18,8 @@
 struct GraphEntry {
     int kind;  // 0: FP64 cycle + residual norm; 1: FP32 inner cycle + residual norm;
                // 2, 3: preconditioned CG step with an FP64 / FP32 cycle;
-               // 4: `reps` guarded FP32 inner cycles, each with its norm and control
+               // 4: `reps` guarded FP32 inner cycles, each with its norm and control;
+               // 5: one FP64 cycle + residual norm of a chain, `reps` its CHAIN_ flags
     int reps;
     int nu_pre, nu_post;
     double omega;
@@ -27,6 +28,10 @@ struct GraphEntry {
     double bytes;
     uint64_t epoch;  // tile table epoch the fused passes were captured with
 };
+
+// One cycle of a chain (enqueue_chain): starts with its own pre pass, ends with
+// a post pass, finds the pre-smoothed iterate in the second buffer.
+constexpr int CHAIN_ENTER = 1, CHAIN_LEAVE = 2, CHAIN_ODD = 4;
 
 struct GraphCache {
     hipStream_t st = nullptr;  // internal non-blocking stream (capture needs one)
@@ -149,6 +154,38 @@ template hipError_t enqueue_vcycle<double>(mg_hierarchy*, int, double*, const do
 template hipError_t enqueue_vcycle<float>(mg_hierarchy*, int, float*, const float*, bool, int,
                                           int, double, Enq&);
 
+template <typename T>
+static hipError_t enqueue_pre(mg_hierarchy* h, int l, const T* x, const T* b, bool x_zero, T om,
+                              T* t, Enq& q) {
+    Level &lv = h->lv[l], &lc = h->lv[l - 1];
+    const double s = sizeof(T);
+    q.bytes += (x_zero ? 11 : 12) * s * (double)lv.n + s * (double)lc.n;
+    return launch_pre<T>(lv, LV<T>::bands(lv), x, x_zero, b, om, t, LV<T>::b(lc), h->dmask, q.st,
+                         q.guard);
+}
+
+// The levels below l of a fused cycle, from b_c to x_c.
+template <typename T>
+static hipError_t enqueue_coarse_cycle(mg_hierarchy* h, int l, double omega, Enq& q) {
+    Level& lc = h->lv[l - 1];
+    if (l - 1 > tail_max_level())
+        return enqueue_vcycle_fused<T>(h, l - 1, LV<T>::x(lc), LV<T>::b(lc), true, omega, q,
+                                       nullptr, nullptr, 0, nullptr);
+    // every coarser level in one workgroup; same bytes as the unfused cycle there
+    for (int k = h->Lc + 1; k < l; ++k) q.bytes += 84.0 * sizeof(T) * (double)h->lv[k].n;
+    return launch_tail<T>(h->lv, l - 1, h->Lc, coarse_solver(h), 2, 2, (T)omega, q.st, q.guard);
+}
+
+template <typename T>
+static hipError_t enqueue_post(mg_hierarchy* h, int l, const T* t, const T* b, T om, T* x, Enq& q,
+                               double* partials, double* scal, int slot, double* host) {
+    Level &lv = h->lv[l], &lc = h->lv[l - 1];
+    const double s = sizeof(T);
+    q.bytes += 12 * s * (double)lv.n + s * (double)lc.n;
+    return launch_post<T>(lv, LV<T>::bands(lv), t, LV<T>::x(lc), b, om, x, partials, scal, slot,
+                          host, q.st, q.guard, partials ? q.ctl : RedCtl{});
+}
+
 // V(2,2) cycle from the fused passes: per level one pre pass (two sweeps,
 // defect, restriction: x -> t, b_c) and one post pass (prolongation, two
 // sweeps: t + P x_c -> x).  With partials the top-level post pass also
@@ -173,29 +210,50 @@ hipError_t enqueue_vcycle_fused(mg_hierarchy* h, int l, T* x, const T* b, bool x
         }
         return hipSuccess;
     }
-    Level& lc = h->lv[l - 1];
     T* t = LV<T>::t(lv);
-    MG_TRY(launch_pre<T>(lv, bands, x, x_zero, b, om, t, LV<T>::b(lc), h->dmask, q.st, q.guard));
-    q.bytes += (x_zero ? 11 : 12) * s * n + s * (double)lc.n;
-    if (l - 1 <= tail_max_level()) {
-        // every coarser level in one workgroup; same bytes as the unfused cycle there
-        MG_TRY(launch_tail<T>(h->lv, l - 1, h->Lc, coarse_solver(h), 2, 2, om, q.st,
-                              q.guard));
-        for (int k = h->Lc + 1; k < l; ++k) q.bytes += 84.0 * s * (double)h->lv[k].n;
-    } else {
-        MG_TRY(enqueue_vcycle_fused<T>(h, l - 1, LV<T>::x(lc), LV<T>::b(lc), true, omega, q,
-                                       nullptr, nullptr, 0, nullptr));
-    }
-    MG_TRY(launch_post<T>(lv, bands, t, LV<T>::x(lc), b, om, x, partials, scal, slot, host,
-                          q.st, q.guard, partials ? q.ctl : RedCtl{}));
-    q.bytes += 12 * s * n + s * (double)lc.n;
-    return hipSuccess;
+    MG_TRY(enqueue_pre<T>(h, l, x, b, x_zero, om, t, q));
+    MG_TRY(enqueue_coarse_cycle<T>(h, l, omega, q));
+    return enqueue_post<T>(h, l, t, b, om, x, q, partials, scal, slot, host);
 }
 
 template hipError_t enqueue_vcycle_fused<double>(mg_hierarchy*, int, double*, const double*, bool,
                                                  double, Enq&, double*, double*, int, double*);
 template hipError_t enqueue_vcycle_fused<float>(mg_hierarchy*, int, float*, const float*, bool,
                                                 double, Enq&, double*, double*, int, double*);
+
+// V(2,2) cycles in a row on the finest level, each with its residual norm, a
+// cycle's post pass merged with the next one's pre pass (launch_mid): x gets
+// every cycle's result, the smoothed iterate the next cycle starts from
+// alternates between t and alt.  ENTER: the first cycle starts from x;
+// otherwise from the pre-smoothed iterate in t that a chain without LEAVE
+// left (after an even number of cycles; in alt after an odd one).
+template <typename T>
+static hipError_t enqueue_chain(mg_hierarchy* h, T* x, const T* b, T* t, T* alt, int cycles,
+                                bool x_zero, bool enter, bool leave, double omega, Enq& q,
+                                int slot) {
+    const int L = h->L;
+    Level &lv = h->lv[L], &lc = h->lv[L - 1];
+    const T om = (T)omega;
+    const double s = sizeof(T);
+    if (enter) MG_TRY(enqueue_pre<T>(h, L, x, b, x_zero, om, t, q));
+    for (int i = 0; i < cycles; ++i) {
+        MG_TRY(enqueue_coarse_cycle<T>(h, L, omega, q));
+        if (leave && i == cycles - 1)
+            return enqueue_post<T>(h, L, t, b, om, x, q, h->partials, h->scal, slot, h->host_scal);
+        MG_TRY(launch_mid<T>(lv, LV<T>::bands(lv), t, LV<T>::x(lc), b, om, x, alt, LV<T>::b(lc),
+                             h->dmask, h->partials, h->scal, slot, h->host_scal, q.st, q.guard,
+                             q.ctl));
+        q.bytes += 13 * s * (double)lv.n + 2 * s * (double)lc.n;
+        std::swap(t, alt);
+    }
+    return hipSuccess;
+}
+
+// The second buffer of the pre-smoothed iterate is a finest-level FP64 vector
+// the solver has no use for: d64 in the FP64 solve, t64 in the mixed one.
+static bool chained(const mg_hierarchy* h, int elem_bytes) {
+    return h->L > h->Lc && use_mid(h->lv[h->L].N, elem_bytes);
+}
 
 // One step of CG preconditioned by one V-cycle from zero (Sec. 4.1: a
 // solver as another's preconditioner; the cycle of Sec. 6.2), on the finest
@@ -257,11 +315,24 @@ static hipError_t enqueue_unit(mg_hierarchy* h, int kind, int reps, int nu_pre, 
     if (kind == 4) {
         Enq g{q.st, 0.0, h->scal + SC_STOP};
         g.ctl.mode = RED_STEP;
+        if (chained(h, 4)) {
+            MG_TRY(enqueue_chain<float>(h, F.x32, F.b32, F.t32, (float*)F.t64, reps, x_zero, true,
+                                        true, omega, g, SC_R32));
+            q.bytes += g.bytes;
+            return hipSuccess;
+        }
         for (int i = 0; i < reps; ++i)
             MG_TRY(enqueue_vcycle_fused<float>(h, h->L, F.x32, F.b32, x_zero && i == 0, omega, g,
                                                h->partials, h->scal, SC_R32, h->host_scal));
         q.bytes += g.bytes;
         return hipSuccess;
+    }
+    if (kind == 5) {
+        // one FP64 cycle of a chain
+        double* t = reps & CHAIN_ODD ? h->d64 : F.t64;
+        double* alt = reps & CHAIN_ODD ? F.t64 : h->d64;
+        return enqueue_chain<double>(h, F.x64, F.b64, t, alt, 1, false, reps & CHAIN_ENTER,
+                                     reps & CHAIN_LEAVE, omega, q, SC_R64);
     }
     if (kind >= 2) return enqueue_pcg_step(h, kind == 3, nu_pre, nu_post, omega, q);
     if (nu_pre == 2 && nu_post == 2) {
@@ -650,6 +721,7 @@ extern "C" mg_status mg_solve(mg_hierarchy* h, const double* dev_b, double* dev_
         }
         MG_HIPS(read_scalar(h, SC_R64, q.st, &r));
         st.rel_res = r / bn;
+        const bool chain = o.nu_pre == 2 && o.nu_post == 2 && chained(h, 8);
         for (int k = 1;; ++k) {
             if (o.fixed_cycles > 0) {
                 if (k > o.fixed_cycles) break;
@@ -661,7 +733,16 @@ extern "C" mg_status mg_solve(mg_hierarchy* h, const double* dev_b, double* dev_
                 }
             }
             arm_scalar(h, SC_R64);
-            MG_HIPS(run_unit(h, 0, o, false, graphs, q));
+            if (chain) {
+                // a cycle that may be followed by another also pre-smooths
+                // for it (a seventh more than a post pass alone)
+                const bool lastk = k == (o.fixed_cycles > 0 ? o.fixed_cycles : o.max_cycles);
+                const int part = (k == 1 ? CHAIN_ENTER : 0) | (lastk ? CHAIN_LEAVE : 0) |
+                                 (k % 2 == 0 ? CHAIN_ODD : 0);
+                MG_HIPS(run_unit(h, 5, o, false, graphs, q, part));
+            } else {
+                MG_HIPS(run_unit(h, 0, o, false, graphs, q));
+            }
             MG_HIPS(read_scalar(h, SC_R64, q.st, &r));
             st.cycles = k;
             st.rel_res = r / bn;
