@@ -42,12 +42,12 @@ __device__ __forceinline__ int64_t xcd_block(int64_t nblk) {
 
 inline unsigned grid8(int64_t nblk) { return (unsigned)((nblk + 7) / 8 * 8); }
 
-// Kernels of a guarded sequence (the mixed solve under device control, see
+// Kernels of a guarded sequence (a solve under device control, see
 // red_control) take a guard pointer: a nonzero *guard makes the whole
 // launch return at once.  Null: no guard.
 __device__ __forceinline__ bool skipped(const double* guard) { return guard && *guard != 0.0; }
 
-// Device control of the mixed solve (Sec. 6.2.2), taken by the thread that
+// Device control of a solve (Sec. 6.2.2), taken by the thread that
 // has just written a norm r = scal[slot + 1] (see RedCtl):
 //   RED_OUTER (the FP64 defect of an outer step): the solve is over when r
 //     is not finite, above c.div ||b|| (diverged), at most c.thr ||b||,
@@ -60,6 +60,12 @@ __device__ __forceinline__ bool skipped(const double* guard) { return guard && *
 //     (pow2_scale(||b||) r), into scal[SC_D32 + 1].
 //   RED_ZFLAG (the count of nonzero initial iterate elements):
 //     scal[SC_XZ] = 1 if the iterate is zero, else 0.
+//   RED_START (the FP64 solve's first residual): no cycle run yet; the loop is
+//     over when r is at most c.thr ||b||.  c.thr and the cap c.icap stay for
+//     its cycles.
+//   RED_CYCLE (an FP64 cycle's residual): count the cycle; the loop is over
+//     when r is not finite, above 1e3 ||b||, at most the kept threshold, or
+//     the cap is reached -- the host's tests.  The host mirror's ring gets r.
 //   RED_STEP (an inner cycle's FP32 residual): count the cycle; the loop is
 //     over when the residual is not finite, at most c.thr (= scal[SC_RED])
 //     times the scaled defect's norm (scal[SC_D32 + 1]), or the cap is
@@ -85,6 +91,18 @@ __device__ void red_control(const RedCtl& c, double* __restrict__ scal, double* 
         }
     } else if (c.mode == RED_ZFLAG) {
         scal[SC_XZ] = r == 0.0 ? 1.0 : 0.0;
+    } else if (c.mode == RED_START) {
+        scal[SC_ITER] = 0.0;
+        scal[SC_RED] = c.thr;
+        scal[SC_CAP] = (double)c.icap;
+        scal[SC_STOP] = r <= c.thr * scal[SC_B + 1] ? 1.0 : 0.0;
+    } else if (c.mode == RED_CYCLE) {
+        const double it = scal[SC_ITER] + 1.0, bn = scal[SC_B + 1];
+        const bool done =
+            !isfinite(r) || r > 1e3 * bn || r <= scal[SC_RED] * bn || it >= scal[SC_CAP];
+        scal[SC_ITER] = it;
+        scal[SC_STOP] = done ? 1.0 : 0.0;
+        if (host) host[SC_HIST + (int)it % HIST_RING] = r;
     } else if (c.mode == RED_STEP) {
         const double it = scal[SC_ITER] + 1.0;
         const bool done = !isfinite(r) || r <= scal[SC_RED] * scal[SC_D32 + 1] || it >= scal[SC_CAP];

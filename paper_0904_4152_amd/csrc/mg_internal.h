@@ -108,6 +108,8 @@ struct mg_hierarchy {
     // outer steps of the previous such solve (0: none yet): later steps are
     // not queued ahead of their defect's norm
     int outer_prev = 0;
+    // cycles of the last two FP64 V(2,2) solves (0: none yet)
+    int cycles_prev[2] = {0, 0};
 };
 
 namespace mg {
@@ -133,21 +135,30 @@ enum : int {
     SC_CAP = 24,   // cycle cap of the loop
     SC_CONV = 25,  // nonzero: the outer loop is over (the work queued after returns)
     SC_R64B = 26,  // FP64 outer defect norm of even outer steps (odd ones: SC_R64)
-    SC_XZ = 28     // 1 if the initial iterate is zero (RED_ZFLAG), else 0
+    SC_XZ = 28,    // 1 if the initial iterate is zero (RED_ZFLAG), else 0
+    SC_HIST = 32   // host mirror: the FP64 solve's norm after cycle k at SC_HIST + k % HIST_RING
 };
 constexpr double ITER_DONE = 1000.0;
+constexpr int HIST_RING = 32;
 
 // What the final kernel of a reduction does besides writing the norm: the
-// mixed solve's decisions on the device (see red_control in kernels.hip).
-enum : int { RED_NONE = 0, RED_OUTER = 1, RED_STEP = 3, RED_ZFLAG = 4 };
+// solves' decisions on the device (see red_control in kernels.hip).
+enum : int {
+    RED_NONE = 0,
+    RED_OUTER = 1,
+    RED_STEP = 3,
+    RED_ZFLAG = 4,
+    RED_START = 5,
+    RED_CYCLE = 6
+};
 struct RedCtl {
     int mode = RED_NONE;
-    double thr = 0.0;  // OUTER: stop at norm <= thr ||b||
+    double thr = 0.0;  // OUTER, START: stop at norm <= thr ||b||
     double div = 0.0;  // OUTER: diverged above div ||b||
     int cap = 0;       // OUTER: nonzero stops (step count used up)
     int reset = 0;     // OUTER: a step that goes on also starts its inner loop
     double ithr = 0.0; // OUTER with reset: the inner reduction factor
-    int icap = 0;      // OUTER with reset: the inner cycle cap
+    int icap = 0;      // OUTER with reset, START: the cycle cap
 };
 
 // How the hierarchy's coarsest level is solved.

@@ -19,7 +19,7 @@ struct GraphEntry {
     int kind;  // 0: FP64 cycle + residual norm; 1: FP32 inner cycle + residual norm;
                // 2, 3: preconditioned CG step with an FP64 / FP32 cycle;
                // 4: `reps` guarded FP32 inner cycles, each with its norm and control;
-               // 5: one FP64 cycle + residual norm of a chain, `reps` its CHAIN_ flags
+               // 5: a guarded FP64 cycle with its norm and control, `reps` its CHAIN_ flags
     int reps;
     int nu_pre, nu_post;
     double omega;
@@ -31,7 +31,7 @@ struct GraphEntry {
 
 // One cycle of a chain (enqueue_chain): starts with its own pre pass, ends with
 // a post pass, finds the pre-smoothed iterate in the second buffer.
-constexpr int CHAIN_ENTER = 1, CHAIN_LEAVE = 2, CHAIN_ODD = 4;
+constexpr int CHAIN_ENTER = 1, CHAIN_LEAVE = 2, CHAIN_ODD = 4, CHAIN_CYCLE = 8;
 
 struct GraphCache {
     hipStream_t st = nullptr;  // internal non-blocking stream (capture needs one)
@@ -221,25 +221,29 @@ template hipError_t enqueue_vcycle_fused<double>(mg_hierarchy*, int, double*, co
 template hipError_t enqueue_vcycle_fused<float>(mg_hierarchy*, int, float*, const float*, bool,
                                                 double, Enq&, double*, double*, int, double*);
 
-// V(2,2) cycles in a row on the finest level, each with its residual norm, a
-// cycle's post pass merged with the next one's pre pass (launch_mid): x gets
-// every cycle's result, the smoothed iterate the next cycle starts from
-// alternates between t and alt.  ENTER: the first cycle starts from x;
-// otherwise from the pre-smoothed iterate in t that a chain without LEAVE
-// left (after an even number of cycles; in alt after an odd one).
+// V(2,2) cycles in a row on the finest level, each with its residual norm.
+// MERGED: a cycle's post pass and the next one's pre pass in one (launch_mid):
+// x gets every cycle's result, the smoothed iterate the next cycle starts from
+// alternates between t and alt.  CHAIN_ENTER: the first cycle starts from x;
+// otherwise from the pre-smoothed iterate that a merged chain without
+// CHAIN_LEAVE left in t (in alt after an odd number of cycles).
 template <typename T>
 static hipError_t enqueue_chain(mg_hierarchy* h, T* x, const T* b, T* t, T* alt, int cycles,
-                                bool x_zero, bool enter, bool leave, double omega, Enq& q,
+                                bool merged, bool x_zero, int part, double omega, Enq& q,
                                 int slot) {
     const int L = h->L;
     Level &lv = h->lv[L], &lc = h->lv[L - 1];
     const T om = (T)omega;
     const double s = sizeof(T);
-    if (enter) MG_TRY(enqueue_pre<T>(h, L, x, b, x_zero, om, t, q));
     for (int i = 0; i < cycles; ++i) {
+        if (i == 0 ? (part & CHAIN_ENTER) != 0 : !merged)
+            MG_TRY(enqueue_pre<T>(h, L, x, b, x_zero && i == 0, om, t, q));
         MG_TRY(enqueue_coarse_cycle<T>(h, L, omega, q));
-        if (leave && i == cycles - 1)
-            return enqueue_post<T>(h, L, t, b, om, x, q, h->partials, h->scal, slot, h->host_scal);
+        if (!merged || ((part & CHAIN_LEAVE) && i == cycles - 1)) {
+            MG_TRY(enqueue_post<T>(h, L, t, b, om, x, q, h->partials, h->scal, slot,
+                                   h->host_scal));
+            continue;
+        }
         MG_TRY(launch_mid<T>(lv, LV<T>::bands(lv), t, LV<T>::x(lc), b, om, x, alt, LV<T>::b(lc),
                              h->dmask, h->partials, h->scal, slot, h->host_scal, q.st, q.guard,
                              q.ctl));
@@ -316,8 +320,8 @@ static hipError_t enqueue_unit(mg_hierarchy* h, int kind, int reps, int nu_pre, 
         Enq g{q.st, 0.0, h->scal + SC_STOP};
         g.ctl.mode = RED_STEP;
         if (chained(h, 4)) {
-            MG_TRY(enqueue_chain<float>(h, F.x32, F.b32, F.t32, (float*)F.t64, reps, x_zero, true,
-                                        true, omega, g, SC_R32));
+            MG_TRY(enqueue_chain<float>(h, F.x32, F.b32, F.t32, (float*)F.t64, reps, true, x_zero,
+                                        CHAIN_ENTER | CHAIN_LEAVE, omega, g, SC_R32));
             q.bytes += g.bytes;
             return hipSuccess;
         }
@@ -328,11 +332,14 @@ static hipError_t enqueue_unit(mg_hierarchy* h, int kind, int reps, int nu_pre, 
         return hipSuccess;
     }
     if (kind == 5) {
-        // one FP64 cycle of a chain
+        Enq g{q.st, 0.0, h->scal + SC_STOP};
+        g.ctl.mode = RED_CYCLE;
         double* t = reps & CHAIN_ODD ? h->d64 : F.t64;
         double* alt = reps & CHAIN_ODD ? F.t64 : h->d64;
-        return enqueue_chain<double>(h, F.x64, F.b64, t, alt, 1, false, reps & CHAIN_ENTER,
-                                     reps & CHAIN_LEAVE, omega, q, SC_R64);
+        MG_TRY(enqueue_chain<double>(h, F.x64, F.b64, t, alt, reps / CHAIN_CYCLE, chained(h, 8),
+                                     false, reps % CHAIN_CYCLE, omega, g, SC_R64));
+        q.bytes += g.bytes;
+        return hipSuccess;
     }
     if (kind >= 2) return enqueue_pcg_step(h, kind == 3, nu_pre, nu_post, omega, q);
     if (nu_pre == 2 && nu_post == 2) {
@@ -708,20 +715,68 @@ extern "C" mg_status mg_solve(mg_hierarchy* h, const double* dev_b, double* dev_
         MG_HIPS(read_scalar(h, SC_R64, q.st, &rt));
         st.rel_res = rt / bn;
     } else if (o.precision == MG_PREC_FP64) {
-        double r = 0.0;
-        arm_scalar(h, SC_R64);
+        // V(2,2) cycles run under device control: the reduction that yields a
+        // cycle's norm takes the tests below (RED_CYCLE), and cycles queued
+        // behind the last one return at once.  So several cycles go out in one
+        // graph before the host has read a norm: as many as the shorter of the
+        // last two solves took (or fixed_cycles), in powers of two up to 8, so
+        // that few graphs are captured.  A graph per cycle leaves some 4 us
+        // between cycles, whether or not the host waits for the norm between
+        // them (solves of 9 cycles: L = 6 331 -> 303 us, L = 8 475 -> 435, L = 10
+        // 918 -> 885).  The first solve of a hierarchy, and cycles past the
+        // prediction, go out one by one.
+        const bool guarded = o.nu_pre == 2 && o.nu_post == 2 && h->L > h->Lc;
+        const bool chain = guarded && chained(h, 8);
+        const int cap = o.fixed_cycles > 0 ? o.fixed_cycles : o.max_cycles;
+        double r = 0.0, cycle_cost = 0.0;
+        RedCtl first;
+        if (guarded) {
+            first.mode = RED_START;
+            first.thr = o.fixed_cycles > 0 ? -1.0 : o.rel_tol;
+            first.icap = cap;
+        }
+        // its own slot: a queued cycle's norm must not overtake it
+        arm_scalar(h, SC_R64B);
         if (x_zero) {
-            MG_HIPS(launch_defect_zero_x(F, F.b64, nullptr, h->partials, h->scal, SC_R64,
-                                         h->host_scal, q.st));
+            MG_HIPS(launch_defect_zero_x(F, F.b64, nullptr, h->partials, h->scal, SC_R64B,
+                                         h->host_scal, q.st, nullptr, first));
             q.bytes += 8.0 * n;
         } else {
             MG_HIPS(launch_defect<double>(F, F.bands64, F.b64, F.x64, nullptr, h->partials,
-                                          h->scal, SC_R64, h->host_scal, q.st));
+                                          h->scal, SC_R64B, h->host_scal, q.st, nullptr, first));
             q.bytes += 11.0 * 8 * n;
         }
-        MG_HIPS(read_scalar(h, SC_R64, q.st, &r));
+        auto ring = [](int k) { return SC_HIST + k % HIST_RING - 1; };
+        const int* prev = h->cycles_prev;
+        const int ahead = prev[0] == 0         ? 0
+                          : o.fixed_cycles > 0 ? cap
+                                               : std::min({cap, prev[0], prev[1] ? prev[1] : cap});
+        int sent = 0;  // cycles queued
+        auto queue_to = [&](int k) -> hipError_t {
+            while (sent < k) {
+                int m = 8;
+                while (m > k - sent) m /= 2;
+                const int c = sent + 1;
+                int part = CHAIN_ENTER | CHAIN_LEAVE;
+                if (chain)
+                    part = (c == 1 ? CHAIN_ENTER : 0) | (sent + m == cap ? CHAIN_LEAVE : 0) |
+                           (c % 2 == 0 ? CHAIN_ODD : 0);
+                for (int i = 0; i < m; ++i) arm_scalar(h, ring(c + i));
+                Enq cq{q.st, 0.0};
+                MG_TRY(run_unit(h, 5, o, false, graphs, cq, part + m * CHAIN_CYCLE));
+                cycle_cost = cq.bytes / m;
+                sent += m;
+            }
+            return hipSuccess;
+        };
+        // the cycles to have been queued before the norm of cycle k is read: the
+        // norms in flight stay within half the mirror's ring
+        auto horizon = [&](int k) {
+            return sent >= k ? sent : std::max(k, std::min(ahead, k + HIST_RING / 2 - 1));
+        };
+        if (guarded && ahead > 0) MG_HIPS(queue_to(horizon(1)));
+        MG_HIPS(read_scalar(h, SC_R64B, q.st, &r));
         st.rel_res = r / bn;
-        const bool chain = o.nu_pre == 2 && o.nu_post == 2 && chained(h, 8);
         for (int k = 1;; ++k) {
             if (o.fixed_cycles > 0) {
                 if (k > o.fixed_cycles) break;
@@ -732,18 +787,15 @@ extern "C" mg_status mg_solve(mg_hierarchy* h, const double* dev_b, double* dev_
                     break;
                 }
             }
-            arm_scalar(h, SC_R64);
-            if (chain) {
-                // a cycle that may be followed by another also pre-smooths
-                // for it (a seventh more than a post pass alone)
-                const bool lastk = k == (o.fixed_cycles > 0 ? o.fixed_cycles : o.max_cycles);
-                const int part = (k == 1 ? CHAIN_ENTER : 0) | (lastk ? CHAIN_LEAVE : 0) |
-                                 (k % 2 == 0 ? CHAIN_ODD : 0);
-                MG_HIPS(run_unit(h, 5, o, false, graphs, q, part));
+            if (guarded) {
+                MG_HIPS(queue_to(horizon(k)));
+                MG_HIPS(read_scalar(h, ring(k), q.st, &r));
+                q.bytes += cycle_cost;
             } else {
+                arm_scalar(h, SC_R64);
                 MG_HIPS(run_unit(h, 0, o, false, graphs, q));
+                MG_HIPS(read_scalar(h, SC_R64, q.st, &r));
             }
-            MG_HIPS(read_scalar(h, SC_R64, q.st, &r));
             st.cycles = k;
             st.rel_res = r / bn;
             if (st.n_hist < MG_HIST) st.res_hist[st.n_hist++] = r / bn;
@@ -751,6 +803,10 @@ extern "C" mg_status mg_solve(mg_hierarchy* h, const double* dev_b, double* dev_
                 result = fail(MG_ERR_NUMERIC, "residual diverged or became NaN");
                 break;
             }
+        }
+        if (guarded && result == MG_OK) {
+            h->cycles_prev[1] = h->cycles_prev[0];
+            h->cycles_prev[0] = std::max(st.cycles, 1);
         }
     } else if (!devctl) {
         // host-driven loop: one host read per FP64 defect and per FP32 cycle
