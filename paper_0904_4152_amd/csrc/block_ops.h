@@ -56,8 +56,12 @@ struct BlockLds {
     double ns[W][64];
 };
 
-template <typename T, int W>
+// H: halo rows and columns on every side, a multiple of four (whole wavefronts).
+template <typename T, int W, int H = F_HALO>
 struct BlockTile {
+    static constexpr int OWN = 64 - 2 * H;          // owned columns
+    static constexpr int ROWS = 4 * W - 2 * H;      // owned rows
+    static constexpr int W0 = H / 4, W1 = W - W0;   // wavefronts of owned rows
     BlockLds<T, W>& s;
     const int N, lane, w;
     int col, row0;      // this thread's column and first row
@@ -69,13 +73,12 @@ struct BlockTile {
     __device__ BlockTile(BlockLds<T, W>& s_, int N_, int strip, int chunk)
         : s(s_), N(N_), lane((int)threadIdx.x & 63),
           w(__builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6)) {
-        constexpr int BR = 4 * (W - 2);
-        c0 = strip * BLK_OWN;
-        c1 = min(c0 + BLK_OWN, N);
-        r0 = chunk * BR;
-        r1 = min(r0 + BR, N);
-        col = c0 - F_HALO + lane;
-        row0 = r0 - F_HALO + 4 * w;
+        c0 = strip * OWN;
+        c1 = min(c0 + OWN, N);
+        r0 = chunk * ROWS;
+        r1 = min(r0 + ROWS, N);
+        col = c0 - H + lane;
+        row0 = r0 - H + 4 * w;
 #pragma unroll
         for (int r = 0; r < 4; ++r)
             in[r] = in_range(col, 0, N) && in_range(row0 + r, 0, N);
@@ -149,10 +152,93 @@ struct BlockTile {
         }
     }
     __device__ __forceinline__ void store(T* out, const T (&v)[4]) const {
-        if (!in_range(col, c0, c1) || w == 0 || w == W - 1) return;
+        if (!in_range(col, c0, c1) || w < W0 || w >= W1) return;
 #pragma unroll
         for (int r = 0; r < 4; ++r)
             if (in[r]) out[(int64_t)(row0 + r) * N + col] = v[r];
+    }
+    // v = x + P x_c (the arithmetic of prolong_elem), with every load of the tile.
+    __device__ __forceinline__ void start(const T* bands, int64_t bs, const T* x, const T* xc,
+                                          const T* bb, T (&v)[4]) {
+        const int Nc = (N >> 1) + 1;
+        T k0[3], k1[3];
+        const rsrc_t Rx = make_rsrc(x, (int64_t)N * N * (int64_t)sizeof(T));
+        const rsrc_t Rc = make_rsrc(xc, (int64_t)Nc * Nc * (int64_t)sizeof(T));
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = bload<T>(Rx, off(r));
+        // the coarse values around rows row0 .. row0 + 3 (row0 is even)
+        const int I = col >> 1, J = row0 >> 1;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            const bool ok = in_range(J + q, 0, Nc);
+            const uint32_t o = (uint32_t)((J + q) * Nc + I) * (uint32_t)sizeof(T);
+            k0[q] = bload<T>(Rc, ok && in_range(I, 0, Nc) ? o : OFF_NONE);
+            k1[q] = bload<T>(Rc, ok && in_range(I + 1, 0, Nc) ? o + (uint32_t)sizeof(T) : OFF_NONE);
+        }
+        load(bands, bs, bb);
+        const bool c_even = !(col & 1);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int q = r >> 1;
+            T p;
+            if (r & 1)
+                p = c_even ? T(0.5) * (k0[q] + k0[q + 1])
+                           : T(0.25) * ((k0[q] + k1[q]) + (k0[q + 1] + k1[q + 1]));
+            else
+                p = c_even ? k0[q] : T(0.5) * (k0[q] + k1[q]);
+            v[r] = in[r] ? v[r] + p : T(0);
+        }
+    }
+    // The defect of v, restricted to the owned coarse nodes (row0 and c0 are
+    // even, as every node there).
+    __device__ __forceinline__ void restrict_defect(const T (&v)[4], T* bc, int dmask) {
+        T d[4], up, dn;
+        product(v, d);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) d[r] = in[r] ? b[r] - d[r] : T(0);
+        exchange(d, up, dn);
+        const int Nc = (N >> 1) + 1;
+        const T row[5] = {up, d[0], d[1], d[2], d[3]};
+        T l[5], r[5];
+#pragma unroll
+        for (int i = 0; i < 5; ++i) {
+            l[i] = from_left(row[i]);
+            r[i] = from_right(row[i]);
+        }
+        if ((lane & 1) || !in_range(col, c0, c1) || w < W0 || w >= W1) return;
+#pragma unroll
+        for (int i = 1; i < 5; i += 2) {
+            const int j = row0 + i - 1;
+            if (j < r1) {
+                const T corner = (l[i - 1] + r[i - 1]) + (l[i + 1] + r[i + 1]);
+                const T edge = (row[i - 1] + row[i + 1]) + (l[i] + r[i]);
+                const T res = row[i] + T(0.5) * edge + T(0.25) * corner;
+                const int I = col >> 1, J = j >> 1;
+                bc[(int64_t)J * Nc + I] = is_dirichlet(Nc, I, J, dmask) ? T(0) : res;
+            }
+        }
+    }
+    // The norm partials of the residual e on owned nodes: each column's sum
+    // over the wavefront's rows (one group of F_NORM_ROWS), rows in increasing
+    // order, then the segments' eight column sums.
+    __device__ __forceinline__ void norm_partials(const T (&e)[4], double* rowpart) {
+        static_assert(F_NORM_ROWS == 4 && OWN % F_NORM_COLS == 0 && ROWS % F_NORM_ROWS == 0,
+                      "a wavefront's rows are one group");
+        if (w < W0 || w >= W1) return;
+        const bool own = in_range(col, c0, c1);
+        double acc2 = 0.0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (row0 + r < r1) acc2 += own ? (double)e[r] * (double)e[r] : 0.0;
+        s.ns[w][lane] = acc2;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const int nseg = (N + F_NORM_COLS - 1) / F_NORM_COLS, m = lane;
+        if (m < OWN / F_NORM_COLS && c0 + m * F_NORM_COLS < c1 && row0 < r1) {
+            const double* n = s.ns[w] + H + m * F_NORM_COLS;
+            const double s8 = ((n[0] + n[1]) + (n[2] + n[3])) + ((n[4] + n[5]) + (n[6] + n[7]));
+            rowpart[(int64_t)(row0 / F_NORM_ROWS) * nseg + c0 / F_NORM_COLS + m] = s8;
+        }
     }
 };
 
@@ -182,33 +268,7 @@ __device__ __forceinline__ void pre_block(BlockLds<T, W>& s, const T* __restrict
 #pragma unroll
     for (int k = XZERO ? 1 : 0; k < NU; ++k) t.sweep(v, omega);
     t.store(x2out, v);
-    T d[4];
-    t.product(v, d);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) d[r] = t.in[r] ? t.b[r] - d[r] : T(0);
-    // restriction at the even rows and columns (row0 and c0 are even)
-    T up, dn;
-    t.exchange(d, up, dn);
-    const int Nc = (N >> 1) + 1;
-    const T row[5] = {up, d[0], d[1], d[2], d[3]};
-    T l[5], r[5];
-#pragma unroll
-    for (int i = 0; i < 5; ++i) {
-        l[i] = from_left(row[i]);
-        r[i] = from_right(row[i]);
-    }
-    if ((t.lane & 1) || !in_range(t.col, t.c0, t.c1) || t.w == 0 || t.w == W - 1) return;
-#pragma unroll
-    for (int i = 1; i < 5; i += 2) {
-        const int j = t.row0 + i - 1;
-        if (j < t.r1) {
-            const T corner = (l[i - 1] + r[i - 1]) + (l[i + 1] + r[i + 1]);
-            const T edge = (row[i - 1] + row[i + 1]) + (l[i] + r[i]);
-            const T res = row[i] + T(0.5) * edge + T(0.25) * corner;
-            const int I = t.col >> 1, J = j >> 1;
-            bc[(int64_t)J * Nc + I] = is_dirichlet(Nc, I, J, dmask) ? T(0) : res;
-        }
-    }
+    t.restrict_defect(v, bc, dmask);
 }
 
 // Post-smoothing block: x + P x_c, NU sweeps and with NORM the sums of squares
@@ -219,64 +279,52 @@ __device__ __forceinline__ void post_block(BlockLds<T, W>& s, const T* __restric
                                            const T* __restrict__ xc, const T* __restrict__ b,
                                            T omega, T* __restrict__ xout,
                                            double* __restrict__ rowpart, int strip, int chunk) {
-    static_assert(NU + 1 <= F_HALO && F_NORM_ROWS == 4 && BLK_OWN % F_NORM_COLS == 0,
-                  "halo of the sweeps and the norm; a wavefront's rows are one group");
+    static_assert(NU + 1 <= F_HALO, "halo of the sweeps and the norm");
     BlockTile<T, W> t(s, N, strip, chunk);
-    const int Nc = (N >> 1) + 1;
-    T v[4], k0[3], k1[3];
-    {
-        const rsrc_t Rx = make_rsrc(x, (int64_t)N * N * (int64_t)sizeof(T));
-        const rsrc_t Rc = make_rsrc(xc, (int64_t)Nc * Nc * (int64_t)sizeof(T));
-#pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] = bload<T>(Rx, t.off(r));
-        // the coarse values around rows row0 .. row0 + 3 (row0 is even)
-        const int I = t.col >> 1, J = t.row0 >> 1;
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            const bool ok = in_range(J + q, 0, Nc);
-            const uint32_t o = (uint32_t)((J + q) * Nc + I) * (uint32_t)sizeof(T);
-            k0[q] = bload<T>(Rc, ok && in_range(I, 0, Nc) ? o : OFF_NONE);
-            k1[q] = bload<T>(Rc, ok && in_range(I + 1, 0, Nc) ? o + (uint32_t)sizeof(T) : OFF_NONE);
-        }
-    }
-    t.load(bands, bs, b);
-    const bool c_even = !(t.col & 1);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int q = r >> 1;
-        T p;
-        if (r & 1)
-            p = c_even ? T(0.5) * (k0[q] + k0[q + 1])
-                       : T(0.25) * ((k0[q] + k1[q]) + (k0[q + 1] + k1[q + 1]));
-        else
-            p = c_even ? k0[q] : T(0.5) * (k0[q] + k1[q]);
-        v[r] = t.in[r] ? v[r] + p : T(0);
-    }
+    T v[4];
+    t.start(bands, bs, x, xc, b, v);
 #pragma unroll
     for (int k = 0; k < NU; ++k) t.sweep(v, omega);
     t.store(xout, v);
     if (!NORM) return;
     T d[4];
     t.product(v, d);
-    if (t.w == 0 || t.w == W - 1) return;
-    // the column's sum over the wavefront's rows (one group of F_NORM_ROWS),
-    // rows in increasing order, then the segments' eight column sums
-    const bool own = in_range(t.col, t.c0, t.c1);
-    double acc2 = 0.0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) d[r] = t.b[r] - d[r];
+    t.norm_partials(d, rowpart);
+}
+
+// Halo of a merged block pass: six steps, in whole wavefronts of rows, and in
+// columns as many (whole norm segments owned).
+constexpr int BLK_MID_HALO = 8;
+static_assert((64 - 2 * BLK_MID_HALO) % F_NORM_COLS == 0, "");
+
+// Merged pass (see mid_ops.h) in a block tile: post_block with the norm and
+// pre_block of the next cycle, the third sweep from the product of the norm.
+template <typename T, int W>
+__device__ __forceinline__ void mid_block(BlockLds<T, W>& s, const T* __restrict__ bands,
+                                          int64_t bs, int N, const T* __restrict__ x,
+                                          const T* __restrict__ xc, const T* __restrict__ b,
+                                          T omega, T* __restrict__ xpost, T* __restrict__ x2,
+                                          T* __restrict__ bc, int dmask,
+                                          double* __restrict__ rowpart, int strip, int chunk) {
+    BlockTile<T, W, BLK_MID_HALO> t(s, N, strip, chunk);
+    T v[4], e[4];
+    t.start(bands, bs, x, xc, b, v);
+    t.sweep(v, omega);
+    t.sweep(v, omega);
+    t.store(xpost, v);
+    t.product(v, e);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const T e = t.b[r] - d[r];
-        if (t.row0 + r < t.r1) acc2 += own ? (double)e * (double)e : 0.0;
+        e[r] = t.b[r] - e[r];
+        const T x3 = v[r] + jacobi_div(omega * e[r], t.bk[r][4]);
+        v[r] = t.in[r] ? x3 : T(0);
     }
-    s.ns[t.w][t.lane] = acc2;
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    const int nseg = (N + F_NORM_COLS - 1) / F_NORM_COLS, m = t.lane;
-    if (m < BLK_OWN / F_NORM_COLS && t.c0 + m * F_NORM_COLS < t.c1 && t.row0 < t.r1) {
-        const double* n = s.ns[t.w] + F_HALO + m * F_NORM_COLS;
-        const double s8 = ((n[0] + n[1]) + (n[2] + n[3])) + ((n[4] + n[5]) + (n[6] + n[7]));
-        rowpart[(int64_t)(t.row0 / F_NORM_ROWS) * nseg + t.c0 / F_NORM_COLS + m] = s8;
-    }
+    t.norm_partials(e, rowpart);
+    t.sweep(v, omega);
+    t.store(x2, v);
+    t.restrict_defect(v, bc, dmask);
 }
 
 }  // namespace dev

@@ -328,6 +328,20 @@ __global__ __launch_bounds__(64 * W) void k_post_blk(
                                     (int)(lb % g.nstrips), (int)(lb / g.nstrips));
 }
 
+// The merged pass in block tiles of W wavefronts.
+template <typename T, int W>
+__global__ __launch_bounds__(64 * W) void k_mid_blk(
+    const T* __restrict__ bands, int64_t bs, int N, const T* __restrict__ x,
+    const T* __restrict__ xc, const T* __restrict__ b, T omega, T* __restrict__ xpost,
+    T* __restrict__ x2, T* __restrict__ bc, int dmask, double* __restrict__ partials, int nstrips,
+    int nchunks, const double* __restrict__ guard) {
+    const int64_t lb = xcd_block((int64_t)nstrips * nchunks);
+    if (lb < 0 || skipped(guard)) return;
+    __shared__ dev::BlockLds<T, W> s;
+    dev::mid_block<T, W>(s, bands, bs, N, x, xc, b, omega, xpost, x2, bc, dmask, partials,
+                         (int)(lb % nstrips), (int)(lb / nstrips));
+}
+
 // Coarse tail: the V(nu_pre, nu_post) sub-cycle over levels top..Lc in one
 // workgroup (see tail_ops.h).
 template <typename T, int NU>
@@ -1295,20 +1309,50 @@ hipError_t launch_post(const Level& lv, const T* bands, const T* x, const T* xc,
     return launch_reduce(partials, dev::fused_norm_parts(lv.N), scal, slot, host, st, guard, ctl);
 }
 
-// Where block tiles serve the separate passes they beat the merged march, whose
-// chain of row steps is as long as theirs is short (FP64 solve, L = 10: 0.91 ms
-// apart, 1.12 merged; L = 11, marching: 2.16 apart, 1.94 merged).
-bool use_mid(int N, int elem_bytes) { return !single_rule(N, elem_bytes).blk; }
+// Wavefronts of a merged block tile (0: no block tile).  A merged pass saves a
+// launch and a load of the bands and pays with its halo of 8 (owned 48 of 64
+// columns and 4 W - 16 of 4 W rows): short tiles where the level does not fill
+// the chip, tall ones beyond.  Solves apart -> merged, in us: FP64 L = 6 294 ->
+// 281, L = 8 446 -> 432 with W = 6 (444 with 8); L = 9 597 -> 586 with 12; L = 10 886 ->
+// 895 with 12 (972 with 8), so not there.  Mixed L = 6 328 -> 319, L = 8 481 -> 463
+// with W = 8 (472 with 6); L = 10 847 -> 829, L = 11 1651 -> 1610 with 12.
+static int mid_waves(int N, int elem_bytes) {
+    if (!single_rule(N, elem_bytes).blk) return 0;
+    if (elem_bytes == 8) return N <= 257 ? 6 : N <= 513 ? 12 : 0;
+    return N <= 513 ? 8 : 12;
+}
+
+// Every level but those whose block tiles are better apart: the merged march
+// is for the levels on which the separate passes march (FP64 solve, L = 11:
+// 2.16 ms apart, 1.94 merged; L = 10, block tiles: 0.91 apart, 1.12 with a
+// merged march).
+bool use_mid(int N, int elem_bytes) {
+    return mid_waves(N, elem_bytes) || !single_rule(N, elem_bytes).blk;
+}
 
 template <typename T>
 hipError_t launch_mid(const Level& lv, const T* bands, const T* x, const T* xc, const T* b, T omega,
                       T* xpost, T* x2, T* bc, int dmask, double* partials, double* scal, int slot,
                       double* host, hipStream_t st, const double* guard, RedCtl ctl) {
-    const int resident = 256 * (sizeof(T) == 8 ? 2 : 3);  // workgroups the chip holds
-    const dev::FusedGeom g = dev::mid_geom(lv.N, mid_threads<T>(), resident);
-    hipLaunchKernelGGL((k_mid<T>), dim3(grid8((int64_t)g.nstrips * g.nchunks)), dim3(g.bt), 0, st,
-                       bands, lv.bs, lv.N, x, xc, b, omega, xpost, x2, bc, dmask, partials, g,
-                       guard);
+    if (const int W = mid_waves(lv.N, sizeof(T))) {
+        const int own = 64 - 2 * dev::BLK_MID_HALO, rows = 4 * W - 2 * dev::BLK_MID_HALO;
+        const int ns = (lv.N + own - 1) / own, nc = (lv.N + rows - 1) / rows;
+#define MID_BLK(W)                                                                             \
+    hipLaunchKernelGGL((k_mid_blk<T, W>), dim3(grid8((int64_t)ns * nc)), dim3(64 * W), 0, st,  \
+                       bands, lv.bs, lv.N, x, xc, b, omega, xpost, x2, bc, dmask, partials,    \
+                       ns, nc, guard)
+        if (W == 12)
+            MID_BLK(12);
+        else
+            MID_BLK((sizeof(T) == 8 ? 6 : 8));
+#undef MID_BLK
+    } else {
+        const int resident = 256 * (sizeof(T) == 8 ? 2 : 3);  // workgroups the chip holds
+        const dev::FusedGeom g = dev::mid_geom(lv.N, mid_threads<T>(), resident);
+        hipLaunchKernelGGL((k_mid<T>), dim3(grid8((int64_t)g.nstrips * g.nchunks)), dim3(g.bt), 0,
+                           st, bands, lv.bs, lv.N, x, xc, b, omega, xpost, x2, bc, dmask,
+                           partials, g, guard);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_reduce(partials, dev::fused_norm_parts(lv.N), scal, slot, host, st, guard, ctl);

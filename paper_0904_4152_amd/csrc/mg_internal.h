@@ -291,7 +291,7 @@ hipError_t launch_post(const Level& lv, const T* bands, const T* x, const T* xc,
                        T omega, T* xout, double* partials, double* scal, int slot, double* host,
                        hipStream_t st, const double* guard = nullptr, RedCtl ctl = {});
 // On finest levels where use_mid holds, the post pass of a V(2,2) cycle and
-// the pre pass of the next in one (dev::mid_tile): x_post with its residual
+// the pre pass of the next in one (dev::mid_tile, dev::mid_block): x_post with its residual
 // norm as launch_post's, x2 and bc as launch_pre's from x_post.  x2 must not
 // alias x.
 bool use_mid(int N, int elem_bytes);

@@ -1,4 +1,4 @@
-// Merged pass on the finest level between two V(2,2) cycles: the post pass of
+// Merged pass (marching tiles) on the finest level between two V(2,2) cycles: the post pass of
 // one (prolongation, two sweeps, residual norm) and the pre pass of the next
 // (two sweeps, defect, restriction) in one march.
 //

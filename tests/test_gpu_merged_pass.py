@@ -17,7 +17,8 @@ def problem(level, sides, coarse=1):
     return ctx, h, b
 
 
-@pytest.mark.parametrize("level,sides,coarse", [(11, 15, 1), (11, 5, 2), (12, 14, 2)])
+@pytest.mark.parametrize("level,sides,coarse", [(3, 15, 2), (6, 5, 1), (8, 15, 2), (9, 14, 1), (10, 15, 1),
+                                                (11, 15, 1), (11, 5, 2), (12, 14, 2)])
 @pytest.mark.parametrize("cycles", [1, 2, 5])
 def test_fp64_chain_is_its_cycles(level, sides, coarse, cycles):
     ctx, h, b = problem(level, sides, coarse)
@@ -31,19 +32,22 @@ def test_fp64_chain_is_its_cycles(level, sides, coarse, cycles):
         h.solve(b, got, mg.default_opts(precision=0, fixed_cycles=cycles, use_graph=graph))
         torch.cuda.synchronize()
         assert torch.equal(got, want)
-        # stopped by the tolerance: the chain ends with a merged pass
+        # stopped by the tolerance (a hair above the last residual: r <= (r / |b|) |b|
+        # may fail by rounding): the chain ends with a merged pass
         again = start.clone()
         st = h.solve(b, again, mg.default_opts(precision=0, max_cycles=cycles, rel_tol=0.0,
                                                use_graph=graph), raise_on_error=False)
         assert st.cycles == cycles and torch.equal(again, want)
         loose = start.clone()
-        st = h.solve(b, loose, mg.default_opts(precision=0, rel_tol=st.rel_res, use_graph=graph))
+        st = h.solve(b, loose, mg.default_opts(precision=0, rel_tol=st.rel_res * (1 + 1e-9),
+                                               use_graph=graph))
         assert st.cycles == cycles and torch.equal(loose, want)
     h.close()
     ctx.close()
 
 
-@pytest.mark.parametrize("level,sides,coarse", [(12, 15, 1), (12, 5, 2)])
+@pytest.mark.parametrize("level,sides,coarse", [(6, 15, 1), (8, 5, 2), (9, 15, 1), (10, 14, 2),
+                                                (11, 15, 1), (12, 15, 1), (12, 5, 2)])
 def test_mixed_chain_is_its_cycles(level, sides, coarse):
     # a first solve queues two inner cycles and then single ones, a second the
     # number the first one took, as one chain
