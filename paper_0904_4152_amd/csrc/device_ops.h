@@ -243,7 +243,9 @@ __device__ __forceinline__ double stencil_tile(const T* __restrict__ bands, int6
     if (NORM) {
 #pragma unroll
         for (int v = 0; v < W; ++v)
-            if (p0 + v < n) sq = add_sq(sq, (double)res[v]);
+            if (p0 + v < n)
+                sq = OP == OP_SPMV ? fma((double)xv[1][v + 1], (double)res[v], sq)
+                                   : add_sq(sq, (double)res[v]);
     }
     if (STORE && CAST) {
         float f[W];
@@ -384,7 +386,9 @@ __device__ __forceinline__ double stencil_tile_staged(const T* __restrict__ band
     }
     if (NORM) {
 #pragma unroll
-        for (int v = 0; v < W; ++v) sq = add_sq(sq, (double)res[v]);
+        for (int v = 0; v < W; ++v)
+            sq = OP == OP_SPMV ? fma((double)xv[1][v + 1], (double)res[v], sq)
+                               : add_sq(sq, (double)res[v]);
     }
     if (STORE && CAST) {
         float f[W];
@@ -394,7 +398,10 @@ __device__ __forceinline__ double stencil_tile_staged(const T* __restrict__ band
     } else if (STORE) {
         VT v;
         __builtin_memcpy(&v, res, sizeof(VT));
-        __builtin_nontemporal_store(v, reinterpret_cast<VT*>(out + p0));
+        if (OP == OP_SPMV && NORM)  // read again at once by the step that asked for x.y
+            *reinterpret_cast<VT*>(out + p0) = v;
+        else
+            __builtin_nontemporal_store(v, reinterpret_cast<VT*>(out + p0));
     }
     return sq;
 }

@@ -66,6 +66,8 @@ __device__ __forceinline__ bool skipped(const double* guard) { return guard && *
 //   RED_CYCLE (an FP64 cycle's residual): count the cycle; the loop is over
 //     when r is not finite, above 1e3 ||b||, at most the kept threshold, or
 //     the cap is reached -- the host's tests.  The host mirror's ring gets r.
+//   RED_SHIFT (r.z of a preconditioned CG step): the previous value moves to
+//     scal[SC_RZ_OLD] first.
 //   RED_STEP (an inner cycle's FP32 residual): count the cycle; the loop is
 //     over when the residual is not finite, at most c.thr (= scal[SC_RED])
 //     times the scaled defect's norm (scal[SC_D32 + 1]), or the cap is
@@ -173,6 +175,7 @@ __global__ __launch_bounds__(BLOCK) void k_reduce_final(const double* __restrict
     if (skipped(guard)) return;
     const double s = dev::reduce_partials(partials, np);
     if (threadIdx.x == 0) {
+        if (ctl.mode == RED_SHIFT) scal[SC_RZ_OLD] = scal[slot];
         scal[slot] = s;
         scal[slot + 1] = sqrt(s);
         red_control(ctl, scal, host, sqrt(s));
@@ -235,6 +238,7 @@ __global__ __launch_bounds__(BLOCK) void k_reduce_segs(const double* __restrict_
     __threadfence();
     const double s = dev::strided_sum(segs, 0, gridDim.x);
     if (threadIdx.x == 0) {
+        if (ctl.mode == RED_SHIFT) scal[SC_RZ_OLD] = scal[slot];
         scal[slot] = s;
         scal[slot + 1] = sqrt(s);
         red_control(ctl, scal, host, sqrt(s));
@@ -843,7 +847,7 @@ __global__ __launch_bounds__(BLOCK) void k_dot(const double* __restrict__ u,
 }
 
 // p = z + beta p, beta = scal[s_new] / scal[s_old] (0 for the first
-// direction, where scal[s_old] is +inf).
+// direction, where scal[s_old] is +inf: whatever p holds is not used).
 template <typename TZ>
 __global__ __launch_bounds__(BLOCK) void k_pcg_dir(double* __restrict__ pv,
                                                    const TZ* __restrict__ z, int64_t n,
@@ -853,7 +857,8 @@ __global__ __launch_bounds__(BLOCK) void k_pcg_dir(double* __restrict__ pv,
     if (p >= n) return;
     const double s = zslot >= 0 ? scal[zslot + 1] : 1.0;
     const double beta = scal[s_new] / scal[s_old];
-    pv[p] = z_value(z, p, s) + beta * pv[p];
+    const double zv = z_value(z, p, s);
+    pv[p] = beta == 0.0 ? zv : zv + beta * pv[p];
 }
 
 // alpha = scal[s_num] / scal[s_den]; x += alpha p; r -= alpha q; partial
@@ -880,14 +885,6 @@ __global__ __launch_bounds__(BLOCK) void k_pcg_step(double* __restrict__ x, doub
     }
     const double t = dev::block_sum(acc);
     if (threadIdx.x == 0) partials[lb] = t;
-}
-
-// scal[to], scal[to + 1] = scal[from], scal[from + 1] (one thread).
-__global__ void k_scalar_copy(double* __restrict__ scal, int from, int to) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        scal[to] = scal[from];
-        scal[to + 1] = scal[from + 1];
-    }
 }
 
 inline unsigned blocks1d(int64_t n) { return (unsigned)((n + BLOCK - 1) / BLOCK); }
@@ -1000,6 +997,16 @@ hipError_t launch_spmv(const Level& lv, const T* bands, const T* x, T* y, hipStr
     MG_STENCIL(T, OP_SPMV, false, true, bands, lv.bs, lv.N, lv.n, x, (const T*)nullptr, y, T(0),
                (double*)nullptr, nb, (const double*)nullptr);
     return hipGetLastError();
+}
+
+hipError_t launch_spmv_dot(const Level& lv, const double* bands, const double* x, double* y,
+                           double* partials, double* scal, int slot, hipStream_t st) {
+    const int64_t nb = stencil_blocks(lv.n, sizeof(double));
+    MG_STENCIL(double, OP_SPMV, true, true, bands, lv.bs, lv.N, lv.n, x, (const double*)nullptr, y,
+               0.0, partials, nb, (const double*)nullptr);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    return launch_reduce(partials, nb, scal, slot, nullptr, st);
 }
 
 template <typename T>
@@ -1531,18 +1538,18 @@ hipError_t launch_defect_zero_x_cast(const Level& lv, const double* b, float* d3
 
 template <typename TZ>
 hipError_t launch_dot(const double* u, const TZ* z, int64_t n, const double* zscal, int zslot,
-                      double* partials, double* scal, int slot, hipStream_t st) {
+                      double* partials, double* scal, int slot, hipStream_t st, RedCtl ctl) {
     const int64_t nb = norm_blocks(n);
     hipLaunchKernelGGL(k_dot<TZ>, dim3(grid8(nb)), dim3(BLOCK), 0, st, u, z, n, zscal, zslot,
                        partials, nb);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_reduce(partials, nb, scal, slot, nullptr, st);
+    return launch_reduce(partials, nb, scal, slot, nullptr, st, nullptr, ctl);
 }
 template hipError_t launch_dot<double>(const double*, const double*, int64_t, const double*, int,
-                                       double*, double*, int, hipStream_t);
+                                       double*, double*, int, hipStream_t, RedCtl);
 template hipError_t launch_dot<float>(const double*, const float*, int64_t, const double*, int,
-                                      double*, double*, int, hipStream_t);
+                                      double*, double*, int, hipStream_t, RedCtl);
 
 template <typename TZ>
 hipError_t launch_pcg_dir(double* p, const TZ* z, int64_t n, const double* scal, int zslot,
@@ -1565,11 +1572,6 @@ hipError_t launch_pcg_step(double* x, double* r, const double* p, const double* 
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_reduce(partials, nb, scal, slot, host, st);
-}
-
-hipError_t launch_scalar_copy(double* scal, int from, int to, hipStream_t st) {
-    hipLaunchKernelGGL(k_scalar_copy, dim3(1), dim3(64), 0, st, scal, from, to);
-    return hipGetLastError();
 }
 
 #define MG_INSTANTIATE(T)                                                                     \

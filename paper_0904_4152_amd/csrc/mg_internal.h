@@ -149,7 +149,8 @@ enum : int {
     RED_STEP = 3,
     RED_ZFLAG = 4,
     RED_START = 5,
-    RED_CYCLE = 6
+    RED_CYCLE = 6,
+    RED_SHIFT = 7
 };
 struct RedCtl {
     int mode = RED_NONE;
@@ -188,6 +189,9 @@ hipError_t launch_rhs_uniform(int N, uint64_t seed, int dmask, double* b, double
 // from HBM instead of nine).
 template <typename T>
 hipError_t launch_spmv(const Level& lv, const T* bands, const T* x, T* y, hipStream_t st);
+// y = A x and scal[slot] = x.y in the same pass.
+hipError_t launch_spmv_dot(const Level& lv, const double* bands, const double* x, double* y,
+                           double* partials, double* scal, int slot, hipStream_t st);
 // Reductions land in scal[slot] (sum of squares) and scal[slot+1] (norm) in
 // device memory and, when host is not null, also in host[slot], host[slot+1]
 // (pinned memory, for the host to read once the stream has synchronized).
@@ -266,17 +270,17 @@ hipError_t launch_reduce(double* partials, int64_t np, double* scal, int slot, d
 // zscal[zslot + 1] (zslot >= 0).  u . z into scal[slot]; p = z + beta p with
 // beta = scal[s_new] / scal[s_old]; alpha = scal[s_num] / scal[s_den],
 // x += alpha p, r -= alpha q and ||r||^2 into scal[slot] (norm at slot + 1,
-// mirrored to host when not null); scal[to..to+1] = scal[from..from+1].
+// mirrored to host when not null).
 template <typename TZ>
 hipError_t launch_dot(const double* u, const TZ* z, int64_t n, const double* zscal, int zslot,
-                      double* partials, double* scal, int slot, hipStream_t st);
+                      double* partials, double* scal, int slot, hipStream_t st,
+                      RedCtl ctl = {});
 template <typename TZ>
 hipError_t launch_pcg_dir(double* p, const TZ* z, int64_t n, const double* scal, int zslot,
                           int s_new, int s_old, hipStream_t st);
 hipError_t launch_pcg_step(double* x, double* r, const double* p, const double* q, int64_t n,
                            double* scal, int s_num, int s_den, double* partials, int slot,
                            double* host, hipStream_t st);
-hipError_t launch_scalar_copy(double* scal, int from, int to, hipStream_t st);
 
 // Fused smoothing passes of a V(2,2) level (see fused_ops.h): pre = two
 // sweeps (x_zero: the first from a zero iterate) + defect + restriction into

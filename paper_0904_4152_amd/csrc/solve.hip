@@ -267,7 +267,10 @@ static bool chained(const mg_hierarchy* h, int elem_bytes) {
 //   z = M r (kind 2: FP64 cycle; kind 3: FP32 cycle on r / ||r||, z =
 //   ||r|| c32); rz = r.z; p = z + (rz / rz_old) p; rz_old = rz; q = A p;
 //   alpha = rz / p.q; x += alpha p; r -= alpha q; ||r|| to the host mirror.
-// Before the first step scal[SC_RZ_OLD] is +inf, so the first p is z.
+// Before the first step scal[SC_RZ] is +inf; the reduction of r.z moves it to
+// scal[SC_RZ_OLD] before it writes its own, so the first p is z.  p.q comes out
+// of the product's own pass (a pass over two vectors and two launches a step
+// less: L = 11 with FP32 cycles, a solve of 6 steps 1.83 -> 1.74 ms).
 static hipError_t enqueue_pcg_step(mg_hierarchy* h, bool mixed, int nu_pre, int nu_post,
                                    double omega, Enq& q) {
     Level& F = h->lv[h->L];
@@ -277,13 +280,16 @@ static hipError_t enqueue_pcg_step(mg_hierarchy* h, bool mixed, int nu_pre, int 
     double* p = F.b64;
     double* zq = reinterpret_cast<double*>(F.x32);
     const bool fused = nu_pre == 2 && nu_post == 2;
+    RedCtl shift;
+    shift.mode = RED_SHIFT;
     if (!mixed) {
         if (fused)
             MG_TRY(enqueue_vcycle_fused<double>(h, h->L, zq, r, true, omega, q, nullptr, nullptr,
                                                 0, nullptr));
         else
             MG_TRY(enqueue_vcycle<double>(h, h->L, zq, r, true, nu_pre, nu_post, omega, q));
-        MG_TRY(launch_dot<double>(r, zq, n, h->scal, -1, h->partials, h->scal, SC_RZ, q.st));
+        MG_TRY(launch_dot<double>(r, zq, n, h->scal, -1, h->partials, h->scal, SC_RZ, q.st,
+                                  shift));
         MG_TRY(launch_pcg_dir<double>(p, zq, n, h->scal, -1, SC_RZ, SC_RZ_OLD, q.st));
         q.bytes += (16.0 + 24.0) * dn;
     } else {
@@ -293,16 +299,15 @@ static hipError_t enqueue_pcg_step(mg_hierarchy* h, bool mixed, int nu_pre, int 
                                                nullptr, 0, nullptr));
         else
             MG_TRY(enqueue_vcycle<float>(h, h->L, F.x32, F.b32, true, nu_pre, nu_post, omega, q));
-        MG_TRY(launch_dot<float>(r, F.x32, n, h->scal, SC_RR, h->partials, h->scal, SC_RZ, q.st));
+        MG_TRY(launch_dot<float>(r, F.x32, n, h->scal, SC_RR, h->partials, h->scal, SC_RZ, q.st,
+                                 shift));
         MG_TRY(launch_pcg_dir<float>(p, F.x32, n, h->scal, SC_RR, SC_RZ, SC_RZ_OLD, q.st));
         q.bytes += (12.0 + 12.0 + 20.0) * dn;
     }
-    MG_TRY(launch_scalar_copy(h->scal, SC_RZ, SC_RZ_OLD, q.st));
-    MG_TRY(launch_spmv<double>(F, F.bands64, p, zq, q.st));
-    MG_TRY(launch_dot<double>(p, zq, n, h->scal, -1, h->partials, h->scal, SC_PQ, q.st));
+    MG_TRY(launch_spmv_dot(F, F.bands64, p, zq, h->partials, h->scal, SC_PQ, q.st));
     MG_TRY(launch_pcg_step(F.x64, r, p, zq, n, h->scal, SC_RZ, SC_PQ, h->partials, SC_RR,
                            h->host_scal, q.st));
-    q.bytes += (88.0 + 16.0 + 48.0) * dn;
+    q.bytes += (88.0 + 48.0) * dn;
     return hipSuccess;
 }
 
@@ -575,18 +580,19 @@ extern "C" mg_status mg_solve(mg_hierarchy* h, const double* dev_b, double* dev_
     // updates the caller's x in place; the other solvers' captured graphs
     // work on the hierarchy's own copies.
     const bool direct = !o.krylov && o.precision == MG_PREC_MIXED;
-    const double* B64 = direct ? dev_b : F.b64;
+    // (The preconditioned CG reads b only there too: its own b64 holds p.)
+    const double* B64 = direct || o.krylov ? dev_b : F.b64;
     double* X64 = direct ? dev_x : F.x64;
     // zero_guess: x0 = 0 whatever dev_x holds (not read; the mixed solve's
     // first update writes x without reading it)
     const bool zg = o.zero_guess != 0;
     if (!direct) {
-        MG_HIPS(launch_copy<double>(dev_b, F.b64, n, q.st));
+        if (!o.krylov) MG_HIPS(launch_copy<double>(dev_b, F.b64, n, q.st));
         if (zg)
             MG_HIPS(launch_fill<double>(F.x64, n, 0.0, q.st));
         else
             MG_HIPS(launch_copy<double>(dev_x, F.x64, n, q.st));
-        q.bytes += zg ? 8.0 * 3 * n : 8.0 * 4 * n;
+        q.bytes += ((zg ? 8.0 : 16.0) + (o.krylov ? 0.0 : 16.0)) * n;
     }
     // the mixed solve under device control (see the last branch below)
     const bool devctl = !o.krylov && o.precision == MG_PREC_MIXED && o.nu_pre == 2 &&
@@ -674,15 +680,15 @@ extern "C" mg_status mg_solve(mg_hierarchy* h, const double* dev_b, double* dev_
         double r = 0.0;
         arm_scalar(h, SC_RR);
         if (x_zero) {
-            MG_HIPS(launch_defect_zero_x(F, F.b64, h->d64, h->partials, h->scal, SC_RR,
+            MG_HIPS(launch_defect_zero_x(F, B64, h->d64, h->partials, h->scal, SC_RR,
                                          h->host_scal, q.st));
             q.bytes += 16.0 * n;
         } else {
-            MG_HIPS(launch_defect<double>(F, F.bands64, F.b64, F.x64, h->d64, h->partials,
+            MG_HIPS(launch_defect<double>(F, F.bands64, B64, F.x64, h->d64, h->partials,
                                           h->scal, SC_RR, h->host_scal, q.st));
             q.bytes += 12.0 * 8 * n;
         }
-        MG_HIPS(launch_fill<double>(h->scal + SC_RZ_OLD, 1, INFINITY, q.st));
+        MG_HIPS(launch_fill<double>(h->scal + SC_RZ, 1, INFINITY, q.st));
         MG_HIPS(read_scalar(h, SC_RR, q.st, &r));
         st.rel_res = r / bn;
         const int kind = o.precision == MG_PREC_FP64 ? 2 : 3;
