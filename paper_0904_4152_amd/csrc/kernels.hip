@@ -167,24 +167,47 @@ __global__ __launch_bounds__(BLOCK) void k_defect_cast(const double* __restrict_
     if (threadIdx.x == 0) partials[lb] = s;
 }
 
-__global__ __launch_bounds__(BLOCK) void k_reduce_final(const double* __restrict__ partials,
-                                                        int64_t np, double* __restrict__ scal,
-                                                        int slot, double* __restrict__ host,
-                                                        const double* __restrict__ guard,
-                                                        RedCtl ctl) {
-    if (skipped(guard)) return;
-    const double s = dev::reduce_partials(partials, np);
-    if (threadIdx.x == 0) {
-        if (ctl.mode == RED_SHIFT) scal[SC_RZ_OLD] = scal[slot];
-        scal[slot] = s;
-        scal[slot + 1] = sqrt(s);
-        red_control(ctl, scal, host, sqrt(s));
-        if (host) {
-            host[slot] = s;
-            host[slot + 1] = sqrt(s);
-            __threadfence_system();
+// One workgroup's share of a reduction, threads 0 .. BLOCK - 1 (whole wavefronts
+// beyond them return).  Up to RED_SEG partials one workgroup sums them all.
+// More: one per RED_SEG partials writes its segment's sum, and the one that
+// finishes last (an integer ticket counts them) sums the segment sums in the
+// same way and resets the ticket for the next reduction.  The fences order
+// each segment sum before its ticket and the last workgroup's reads after it,
+// across the XCDs' caches.
+__device__ void reduce_block(const RedJob& j, int blk) {
+    if (threadIdx.x >= BLOCK) return;
+    double s;
+    if (j.blocks == 1) {
+        s = dev::strided_sum(j.partials, 0, j.np);
+    } else {
+        const double v = dev::strided_sum(j.partials, blk * dev::RED_SEG,
+                                          std::min<int64_t>(j.np, (blk + 1) * dev::RED_SEG));
+        __shared__ unsigned last;
+        if (threadIdx.x == 0) {
+            j.segs[blk] = v;
+            __threadfence();
+            last = atomicAdd(j.ticket, 1u) == (unsigned)j.blocks - 1;
         }
+        __syncthreads();
+        if (!last) return;
+        __threadfence();
+        s = dev::strided_sum(j.segs, 0, j.blocks);
     }
+    if (threadIdx.x != 0) return;
+    if (j.ctl.mode == RED_SHIFT) j.scal[SC_RZ_OLD] = j.scal[j.slot];
+    j.scal[j.slot] = s;
+    j.scal[j.slot + 1] = sqrt(s);
+    red_control(j.ctl, j.scal, j.host, sqrt(s));
+    if (j.blocks > 1) *j.ticket = 0u;
+    if (j.host) {
+        j.host[j.slot] = s;
+        j.host[j.slot + 1] = sqrt(s);
+        __threadfence_system();
+    }
+}
+
+__global__ __launch_bounds__(BLOCK) void k_reduce(RedJob job, const double* __restrict__ guard) {
+    if (!skipped(guard)) reduce_block(job, (int)blockIdx.x);
 }
 
 template <typename T>
@@ -209,48 +232,6 @@ __global__ __launch_bounds__(BLOCK) void k_prolong(int Nf, const T* __restrict__
     const int i = blockIdx.x * BLOCK + threadIdx.x;
     if (i < Nf) dev::prolong_elem(Nf, xc, xf, i, (int)blockIdx.y);
 }
-
-// Segmented reduction in one launch: one block per RED_SEG partials writes
-// its segment's sum; the block that finishes last (an integer ticket counts
-// the finished blocks) sums the segment sums as k_reduce_final would, and
-// resets the ticket for the next reduction.  The fences order each block's
-// segment sum before its ticket and the last block's reads after it, across
-// the XCDs' caches.
-__global__ __launch_bounds__(BLOCK) void k_reduce_segs(const double* __restrict__ partials,
-                                                       int64_t np, double* __restrict__ segs,
-                                                       unsigned* __restrict__ ticket,
-                                                       double* __restrict__ scal, int slot,
-                                                       double* __restrict__ host,
-                                                       const double* __restrict__ guard,
-                                                       RedCtl ctl) {
-    if (skipped(guard)) return;
-    const int64_t sg = blockIdx.x;
-    const double v = dev::strided_sum(partials, sg * dev::RED_SEG,
-                                      std::min<int64_t>(np, (sg + 1) * dev::RED_SEG));
-    __shared__ unsigned last;
-    if (threadIdx.x == 0) {
-        segs[sg] = v;
-        __threadfence();
-        last = atomicAdd(ticket, 1u) == gridDim.x - 1;
-    }
-    __syncthreads();
-    if (!last) return;
-    __threadfence();
-    const double s = dev::strided_sum(segs, 0, gridDim.x);
-    if (threadIdx.x == 0) {
-        if (ctl.mode == RED_SHIFT) scal[SC_RZ_OLD] = scal[slot];
-        scal[slot] = s;
-        scal[slot + 1] = sqrt(s);
-        red_control(ctl, scal, host, sqrt(s));
-        *ticket = 0u;
-        if (host) {
-            host[slot] = s;
-            host[slot + 1] = sqrt(s);
-            __threadfence_system();
-        }
-    }
-}
-
 
 template <typename T>
 __global__ __launch_bounds__(64) void k_coarse(dev::CoarseSolver cs, int Nc, const T* __restrict__ b,
@@ -347,10 +328,17 @@ __global__ __launch_bounds__(64 * W) void k_mid_blk(
 }
 
 // Coarse tail: the V(nu_pre, nu_post) sub-cycle over levels top..Lc in one
-// workgroup (see tail_ops.h).
+// workgroup (see tail_ops.h).  Workgroups 1 and up, if any, take a reduction
+// beside it: the norm of the cycle before, whose decision nothing before the
+// tail's end depends on.
 template <typename T, int NU>
 __global__ __launch_bounds__(dev::TAIL_THREADS) void k_tail(dev::TailLevels<T> tl, T omega,
-                                                             const double* __restrict__ guard) {
+                                                             const double* __restrict__ guard,
+                                                             RedJob job) {
+    if (blockIdx.x > 0) {
+        if (!skipped(guard)) reduce_block(job, (int)blockIdx.x - 1);
+        return;
+    }
     // The kernel arguments span several cache lines of host-written memory.
     // Asked for here, all at once, they cost one miss; read where the cycle
     // branches on them they cost one each.
@@ -359,9 +347,8 @@ __global__ __launch_bounds__(dev::TAIL_THREADS) void k_tail(dev::TailLevels<T> t
                  "s"(tl.lv[2].bands), "s"(tl.lv[2].bs), "s"(tl.cs.chol), "s"(tl.cs.m),
                  "s"(tl.cs.dmask), "s"(tl.cs.cg), "s"(tl.top), "s"(tl.Lc), "s"(omega),
                  "s"(guard));
-    if (skipped(guard)) return;
     __shared__ dev::TailLds<T> m;
-    dev::tail_cycle<T, NU>(m, tl, omega);
+    dev::tail_cycle<T, NU>(m, tl, omega, guard);
 }
 
 // Dense Cholesky factor (lower triangle, row-major m x m) of the coarsest
@@ -894,20 +881,26 @@ inline unsigned blocks1d(int64_t n) { return (unsigned)((n + BLOCK - 1) / BLOCK)
 // scal[slot] = sum of the np partials (the order of dev::reduce_partials),
 // scal[slot + 1] = its square root; the same into host[slot..] if not null.
 // Segment sums go right after the partials, which the partials buffer leaves
-// room for; the word before the buffer is the ticket of k_reduce_segs.
+// room for; the word before the buffer is the ticket of reduce_block.
+RedJob reduce_job(double* partials, int64_t np, double* scal, int slot, double* host, RedCtl ctl) {
+    RedJob j;
+    j.partials = partials;
+    j.np = np;
+    j.blocks = (int)std::max<int64_t>(1, (np + dev::RED_SEG - 1) / dev::RED_SEG);
+    j.segs = partials + (np + 63) / 64 * 64;
+    j.ticket = reinterpret_cast<unsigned*>(partials - 1);
+    j.scal = scal;
+    j.slot = slot;
+    j.host = host;
+    j.ctl = ctl;
+    return j;
+}
+
 hipError_t launch_reduce(double* partials, int64_t np, double* scal, int slot, double* host,
                          hipStream_t st, const double* guard, RedCtl ctl) {
-    if (np <= dev::RED_SEG) {
-        hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(BLOCK), 0, st, partials, np, scal, slot,
-                           host, guard, ctl);
-        return hipGetLastError();
-    }
-    const int64_t ns = (np + dev::RED_SEG - 1) / dev::RED_SEG;
-    if (ns > dev::RED_MAX_SEGS) return hipErrorInvalidValue;
-    double* segs = partials + (np + 63) / 64 * 64;
-    unsigned* ticket = reinterpret_cast<unsigned*>(partials - 1);
-    hipLaunchKernelGGL(k_reduce_segs, dim3(ns), dim3(BLOCK), 0, st, partials, np, segs, ticket,
-                       scal, slot, host, guard, ctl);
+    const RedJob j = reduce_job(partials, np, scal, slot, host, ctl);
+    if (j.blocks < 1 || j.blocks > dev::RED_MAX_SEGS) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_reduce, dim3(j.blocks), dim3(BLOCK), 0, st, j, guard);
     return hipGetLastError();
 }
 
@@ -1312,7 +1305,7 @@ hipError_t launch_post(const Level& lv, const T* bands, const T* x, const T* xc,
 #undef POST
 #undef POST_T
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !partials) return e;
+    if (e != hipSuccess || !partials || !scal) return e;
     return launch_reduce(partials, dev::fused_norm_parts(lv.N), scal, slot, host, st, guard, ctl);
 }
 
@@ -1361,7 +1354,7 @@ hipError_t launch_mid(const Level& lv, const T* bands, const T* x, const T* xc, 
                            partials, g, guard);
     }
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess || !scal) return e;
     return launch_reduce(partials, dev::fused_norm_parts(lv.N), scal, slot, host, st, guard, ctl);
 }
 
@@ -1397,7 +1390,9 @@ hipError_t launch_post1(const Level& lv, const T* bands, const T* x, const T* xc
 
 template <typename T>
 hipError_t launch_tail(const Level* lv, int top, int Lc, const dev::CoarseSolver& cs, int nu_pre,
-                       int nu_post, T omega, hipStream_t st, const double* guard) {
+                       int nu_post, T omega, hipStream_t st, const double* guard,
+                       const RedJob& job) {
+    if (job.blocks > dev::RED_MAX_SEGS) return hipErrorInvalidValue;
     dev::TailLevels<T> tl{};
     for (int l = Lc; l <= top; ++l) {
         dev::TailLevel<T>& d = tl.lv[l];
@@ -1413,11 +1408,11 @@ hipError_t launch_tail(const Level* lv, int top, int Lc, const dev::CoarseSolver
     tl.nu_pre = nu_pre;
     tl.nu_post = nu_post;
     if (nu_pre == 2 && nu_post == 2)
-        hipLaunchKernelGGL((k_tail<T, 2>), dim3(1), dim3(dev::TAIL_THREADS), 0, st, tl, omega,
-                           guard);
+        hipLaunchKernelGGL((k_tail<T, 2>), dim3(1 + job.blocks), dim3(dev::TAIL_THREADS), 0, st,
+                           tl, omega, guard, job);
     else
-        hipLaunchKernelGGL((k_tail<T, 0>), dim3(1), dim3(dev::TAIL_THREADS), 0, st, tl, omega,
-                           guard);
+        hipLaunchKernelGGL((k_tail<T, 0>), dim3(1 + job.blocks), dim3(dev::TAIL_THREADS), 0, st,
+                           tl, omega, guard, job);
     return hipGetLastError();
 }
 
@@ -1604,7 +1599,7 @@ hipError_t launch_pcg_step(double* x, double* r, const double* p, const double* 
     template hipError_t launch_post1<T>(const Level&, const T*, const T*, const T*, const T*, \
                                         T, T*, hipStream_t);                                  \
     template hipError_t launch_tail<T>(const Level*, int, int, const dev::CoarseSolver&, int,  \
-                                       int, T, hipStream_t, const double*);
+                                       int, T, hipStream_t, const double*, const RedJob&);
 
 MG_INSTANTIATE(float)
 MG_INSTANTIATE(double)

@@ -162,6 +162,20 @@ struct RedCtl {
     int icap = 0;      // OUTER with reset, START: the cycle cap
 };
 
+// A reduction of np partials by `blocks` workgroups (0: none), see launch_reduce.
+struct RedJob {
+    const double* partials = nullptr;
+    int64_t np = 0;
+    int blocks = 0;
+    double* segs = nullptr;
+    unsigned* ticket = nullptr;
+    double* scal = nullptr;
+    int slot = 0;
+    double* host = nullptr;
+    RedCtl ctl;
+};
+RedJob reduce_job(double* partials, int64_t np, double* scal, int slot, double* host, RedCtl ctl);
+
 // How the hierarchy's coarsest level is solved.
 dev::CoarseSolver coarse_solver(const mg_hierarchy* h);
 
@@ -297,7 +311,8 @@ hipError_t launch_post(const Level& lv, const T* bands, const T* x, const T* xc,
 // On finest levels where use_mid holds, the post pass of a V(2,2) cycle and
 // the pre pass of the next in one (dev::mid_tile, dev::mid_block): x_post with its residual
 // norm as launch_post's, x2 and bc as launch_pre's from x_post.  x2 must not
-// alias x.
+// alias x.  Without scal (launch_post likewise) the partials are left for a
+// later reduce_job.
 bool use_mid(int N, int elem_bytes);
 template <typename T>
 hipError_t launch_mid(const Level& lv, const T* bands, const T* x, const T* xc, const T* b, T omega,
@@ -314,10 +329,11 @@ hipError_t launch_post1(const Level& lv, const T* bands, const T* x, const T* xc
                         T omega, T* xout, hipStream_t st);
 // The V(nu_pre, nu_post) sub-cycle over levels top..Lc (top <=
 // tail_max_level(), entered with a zero iterate on level top) in one
-// workgroup.  lv is indexed by level.
+// workgroup, and the reduction `job` beside it.  lv is indexed by level.
 template <typename T>
 hipError_t launch_tail(const Level* lv, int top, int Lc, const dev::CoarseSolver& cs, int nu_pre,
-                       int nu_post, T omega, hipStream_t st, const double* guard = nullptr);
+                       int nu_post, T omega, hipStream_t st, const double* guard = nullptr,
+                       const RedJob& job = {});
 int tail_max_level();
 // Tiling of the fused passes on a level of N nodes per side: workgroup
 // width and chunk height of a batched pass over `count` problems, geometry of

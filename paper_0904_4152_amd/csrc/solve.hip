@@ -173,7 +173,10 @@ static hipError_t enqueue_coarse_cycle(mg_hierarchy* h, int l, double omega, Enq
                                        nullptr, nullptr, 0, nullptr);
     // every coarser level in one workgroup; same bytes as the unfused cycle there
     for (int k = h->Lc + 1; k < l; ++k) q.bytes += 84.0 * sizeof(T) * (double)h->lv[k].n;
-    return launch_tail<T>(h->lv, l - 1, h->Lc, coarse_solver(h), 2, 2, (T)omega, q.st, q.guard);
+    const RedJob job = q.pending;
+    q.pending = RedJob{};
+    return launch_tail<T>(h->lv, l - 1, h->Lc, coarse_solver(h), 2, 2, (T)omega, q.st, q.guard,
+                          job);
 }
 
 template <typename T>
@@ -227,6 +230,12 @@ template hipError_t enqueue_vcycle_fused<float>(mg_hierarchy*, int, float*, cons
 // alternates between t and alt.  CHAIN_ENTER: the first cycle starts from x;
 // otherwise from the pre-smoothed iterate that a merged chain without
 // CHAIN_LEAVE left in t (in alt after an odd number of cycles).
+//
+// Under a guard, the norm of every cycle but the last is reduced beside the
+// next cycle's coarse tail (on a level with 33 k partials a reduction took 6 us
+// and a launch gap, a twelfth of a cycle).  If it ends the loop, what ran
+// since (the way down to the tail) has written coarse vectors and t only; all
+// that follows is skipped.
 template <typename T>
 static hipError_t enqueue_chain(mg_hierarchy* h, T* x, const T* b, T* t, T* alt, int cycles,
                                 bool merged, bool x_zero, int part, double omega, Enq& q,
@@ -236,19 +245,23 @@ static hipError_t enqueue_chain(mg_hierarchy* h, T* x, const T* b, T* t, T* alt,
     const T om = (T)omega;
     const double s = sizeof(T);
     for (int i = 0; i < cycles; ++i) {
+        const bool last = i == cycles - 1;
         if (i == 0 ? (part & CHAIN_ENTER) != 0 : !merged)
             MG_TRY(enqueue_pre<T>(h, L, x, b, x_zero && i == 0, om, t, q));
         MG_TRY(enqueue_coarse_cycle<T>(h, L, omega, q));
-        if (!merged || ((part & CHAIN_LEAVE) && i == cycles - 1)) {
-            MG_TRY(enqueue_post<T>(h, L, t, b, om, x, q, h->partials, h->scal, slot,
-                                   h->host_scal));
-            continue;
+        double* scal = last ? h->scal : nullptr;
+        if (!merged || ((part & CHAIN_LEAVE) && last)) {
+            MG_TRY(enqueue_post<T>(h, L, t, b, om, x, q, h->partials, scal, slot, h->host_scal));
+        } else {
+            MG_TRY(launch_mid<T>(lv, LV<T>::bands(lv), t, LV<T>::x(lc), b, om, x, alt,
+                                 LV<T>::b(lc), h->dmask, h->partials, scal, slot, h->host_scal,
+                                 q.st, q.guard, q.ctl));
+            q.bytes += 13 * s * (double)lv.n + 2 * s * (double)lc.n;
+            std::swap(t, alt);
         }
-        MG_TRY(launch_mid<T>(lv, LV<T>::bands(lv), t, LV<T>::x(lc), b, om, x, alt, LV<T>::b(lc),
-                             h->dmask, h->partials, h->scal, slot, h->host_scal, q.st, q.guard,
-                             q.ctl));
-        q.bytes += 13 * s * (double)lv.n + 2 * s * (double)lc.n;
-        std::swap(t, alt);
+        if (!last)
+            q.pending = reduce_job(h->partials, dev::fused_norm_parts(lv.N), h->scal, slot,
+                                   h->host_scal, q.ctl);
     }
     return hipSuccess;
 }
@@ -324,15 +337,8 @@ static hipError_t enqueue_unit(mg_hierarchy* h, int kind, int reps, int nu_pre, 
     if (kind == 4) {
         Enq g{q.st, 0.0, h->scal + SC_STOP};
         g.ctl.mode = RED_STEP;
-        if (chained(h, 4)) {
-            MG_TRY(enqueue_chain<float>(h, F.x32, F.b32, F.t32, (float*)F.t64, reps, true, x_zero,
-                                        CHAIN_ENTER | CHAIN_LEAVE, omega, g, SC_R32));
-            q.bytes += g.bytes;
-            return hipSuccess;
-        }
-        for (int i = 0; i < reps; ++i)
-            MG_TRY(enqueue_vcycle_fused<float>(h, h->L, F.x32, F.b32, x_zero && i == 0, omega, g,
-                                               h->partials, h->scal, SC_R32, h->host_scal));
+        MG_TRY(enqueue_chain<float>(h, F.x32, F.b32, F.t32, (float*)F.t64, reps, chained(h, 4),
+                                    x_zero, CHAIN_ENTER | CHAIN_LEAVE, omega, g, SC_R32));
         q.bytes += g.bytes;
         return hipSuccess;
     }

@@ -286,6 +286,7 @@ template <typename T>
 struct TailLds {
     alignas(16) T v[(tail_off(TAIL_MAX + 1) + 3) / 4 * 4];
     CoarseLds cs;
+    int stop;
 };
 
 // The nodes of level l a thread owns, with their bands, right-hand side and
@@ -452,9 +453,14 @@ struct TailNodes {
 
 // The V(nu_pre, nu_post) sub-cycle from a zero iterate over levels top..Lc
 // of one problem, one workgroup of TAIL_THREADS threads: x_top = V(b_top).
-// NU > 0: both smoothing counts are NU (tl's are not read).
+// NU > 0: both smoothing counts are NU (tl's are not read).  A guard that is not
+// null and not zero ends the cycle before it writes: one thread reads it while
+// the loads are out, and every wavefront takes that thread's word (a guard that
+// changes meanwhile must not split the workgroup).
 template <typename T, int NU>
-__device__ void tail_cycle(TailLds<T>& m, const TailLevels<T>& tl, T omega) {
+__device__ void tail_cycle(TailLds<T>& m, const TailLevels<T>& tl, T omega,
+                           const double* __restrict__ guard = nullptr) {
+    if (guard && threadIdx.x == 0) m.stop = *guard != 0.0;
     const int top = tl.top, Lc = tl.Lc, dmask = tl.cs.dmask;
     const int pre = NU > 0 ? NU : tl.nu_pre, post = NU > 0 ? NU : tl.nu_post;
     const bool wave0 = threadIdx.x < 64;
@@ -478,6 +484,7 @@ __device__ void tail_cycle(TailLds<T>& m, const TailLevels<T>& tl, T omega) {
             reinterpret_cast<typename V16<T>::type*>(m.v)[e] = zero;
     }
     __syncthreads();
+    if (guard && m.stop) return;
     T* const lds = m.v;
     int at = 0;  // vector of the level just finished: a defect, or an iterate
     if (top >= 5) at = n5.down(lds, omega, pre);
