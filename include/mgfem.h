@@ -296,7 +296,9 @@ mg_status mg_batch_clear_tiles(void);
  * each block tile, and stores the fastest under problems = 1 (on a level
  * above that where the rule's block tile is faster than every candidate it
  * stores none, and out reports the fastest candidate).  Tiles
- * change no result bit; solves captured before are captured again.
+ * change no result bit; solves captured before are captured again.  (Between two
+ * V(2,2) cycles of one solve the finest level's post and pre passes run as one,
+ * with tiles of its own that the table does not set.)
  * Synchronous; not thread safe per hierarchy. */
 mg_status mg_hierarchy_autotune(mg_hierarchy* h, int reps, mg_tile_choice* out, int out_cap,
                                 int* n_out);

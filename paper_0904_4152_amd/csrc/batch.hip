@@ -614,7 +614,7 @@ __device__ __forceinline__ int64_t s32_parts(const BProb& P, int fused_above) {
 
 // First stage of the inner residual's fixed-order sum for problems with more
 // than dev::RED_SEG partials: one work item per segment of RED_SEG partials,
-// its sum right after the partials (padded to 64), as k_reduce_segs does.
+// its sum right after the partials (padded to 64), as reduce_block does.
 __global__ __launch_bounds__(BLOCK) void kb_segsum(const BProb* __restrict__ probs,
                                                    const BState* __restrict__ state,
                                                    const int* __restrict__ wl, int mask,

@@ -47,6 +47,17 @@ __device__ __forceinline__ T from_right(T v) {
     return lane_shift<0x130>(v);  // wave_shl:1
 }
 
+// Guarded passes (*guard not zero: do nothing).  A test before the loads puts a
+// memory latency of its own in front of theirs, 0.6 to 0.8 us in a pass of 3 to 5
+// us.  So on levels of up to BLK_GUARD_N nodes per side the guard is read among
+// the other loads and withholds the stores (a skipped pass then runs its 4 us);
+// larger levels, whose passes are longer, test first.
+constexpr int BLK_GUARD_N = 513;
+static __device__ double zero_guard;  // stands for no guard (a select, not a branch around the load)
+__device__ __forceinline__ bool pass_over(const double* guard, int N) {
+    return N > BLK_GUARD_N && guard && *(const volatile double*)guard != 0.0;
+}
+
 // LDS of a block pass: the wavefronts' first and last rows, two steps of them
 // in turn (so one barrier per step separates writers and readers), and with
 // the norm each column's sum over a wavefront's four rows.
@@ -69,6 +80,8 @@ struct BlockTile {
     int turn = 0;       // edge buffer of the next exchange
     T bk[4][9], b[4];
     bool in[4];         // node inside the grid
+    bool go = true;     // not a skipped pass
+    bool own;           // this lane's column owned, and not a skipped pass
 
     __device__ BlockTile(BlockLds<T, W>& s_, int N_, int strip, int chunk)
         : s(s_), N(N_), lane((int)threadIdx.x & 63),
@@ -78,10 +91,17 @@ struct BlockTile {
         r0 = chunk * ROWS;
         r1 = min(r0 + ROWS, N);
         col = c0 - H + lane;
+        own = in_range(col, c0, c1);
         row0 = r0 - H + 4 * w;
 #pragma unroll
         for (int r = 0; r < 4; ++r)
             in[r] = in_range(col, 0, N) && in_range(row0 + r, 0, N);
+    }
+    // Store nothing if the pass is to be skipped.
+    __device__ __forceinline__ void heed(const double* guard) {
+        if (__builtin_constant_p(guard) && !guard) return;
+        go = !(*(guard ? guard : &zero_guard) != 0.0);
+        own &= go;
     }
     __device__ __forceinline__ uint32_t off(int r) const {
         return in[r] ? node_off(row0 + r, N, col, sizeof(T)) : OFF_NONE;
@@ -152,12 +172,13 @@ struct BlockTile {
         }
     }
     __device__ __forceinline__ void store(T* out, const T (&v)[4]) const {
-        if (!in_range(col, c0, c1) || w < W0 || w >= W1) return;
+        if (!own || w < W0 || w >= W1) return;
 #pragma unroll
         for (int r = 0; r < 4; ++r)
             if (in[r]) out[(int64_t)(row0 + r) * N + col] = v[r];
     }
-    // v = x + P x_c (the arithmetic of prolong_elem), with every load of the tile.
+    // v = x + P x_c (the arithmetic of prolong_elem), with every load of the
+    // tile.
     __device__ __forceinline__ void start(const T* bands, int64_t bs, const T* x, const T* xc,
                                           const T* bb, T (&v)[4]) {
         const int Nc = (N >> 1) + 1;
@@ -205,7 +226,7 @@ struct BlockTile {
             l[i] = from_left(row[i]);
             r[i] = from_right(row[i]);
         }
-        if ((lane & 1) || !in_range(col, c0, c1) || w < W0 || w >= W1) return;
+        if ((lane & 1) || !own || w < W0 || w >= W1) return;
 #pragma unroll
         for (int i = 1; i < 5; i += 2) {
             const int j = row0 + i - 1;
@@ -225,7 +246,6 @@ struct BlockTile {
         static_assert(F_NORM_ROWS == 4 && OWN % F_NORM_COLS == 0 && ROWS % F_NORM_ROWS == 0,
                       "a wavefront's rows are one group");
         if (w < W0 || w >= W1) return;
-        const bool own = in_range(col, c0, c1);
         double acc2 = 0.0;
 #pragma unroll
         for (int r = 0; r < 4; ++r)
@@ -234,7 +254,7 @@ struct BlockTile {
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
         const int nseg = (N + F_NORM_COLS - 1) / F_NORM_COLS, m = lane;
-        if (m < OWN / F_NORM_COLS && c0 + m * F_NORM_COLS < c1 && row0 < r1) {
+        if (go && m < OWN / F_NORM_COLS && c0 + m * F_NORM_COLS < c1 && row0 < r1) {
             const double* n = s.ns[w] + H + m * F_NORM_COLS;
             const double s8 = ((n[0] + n[1]) + (n[2] + n[3])) + ((n[4] + n[5]) + (n[6] + n[7]));
             rowpart[(int64_t)(row0 / F_NORM_ROWS) * nseg + c0 / F_NORM_COLS + m] = s8;
@@ -248,9 +268,11 @@ template <typename T, bool XZERO, int W, int NU>
 __device__ __forceinline__ void pre_block(BlockLds<T, W>& s, const T* __restrict__ bands,
                                           int64_t bs, int N, const T* __restrict__ x,
                                           const T* __restrict__ b, T omega, T* __restrict__ x2out,
-                                          T* __restrict__ bc, int dmask, int strip, int chunk) {
+                                          T* __restrict__ bc, int dmask, int strip, int chunk,
+                                          const double* __restrict__ guard = nullptr) {
     static_assert(NU + 2 <= F_HALO, "halo of the sweeps, the defect and the restriction");
     BlockTile<T, W> t(s, N, strip, chunk);
+    t.heed(guard);
     T v[4];
     if (!XZERO) {
         const rsrc_t Rx = make_rsrc(x, (int64_t)N * N * (int64_t)sizeof(T));
@@ -278,9 +300,11 @@ __device__ __forceinline__ void post_block(BlockLds<T, W>& s, const T* __restric
                                            int64_t bs, int N, const T* __restrict__ x,
                                            const T* __restrict__ xc, const T* __restrict__ b,
                                            T omega, T* __restrict__ xout,
-                                           double* __restrict__ rowpart, int strip, int chunk) {
+                                           double* __restrict__ rowpart, int strip, int chunk,
+                                           const double* __restrict__ guard = nullptr) {
     static_assert(NU + 1 <= F_HALO, "halo of the sweeps and the norm");
     BlockTile<T, W> t(s, N, strip, chunk);
+    t.heed(guard);
     T v[4];
     t.start(bands, bs, x, xc, b, v);
 #pragma unroll
@@ -307,8 +331,10 @@ __device__ __forceinline__ void mid_block(BlockLds<T, W>& s, const T* __restrict
                                           const T* __restrict__ xc, const T* __restrict__ b,
                                           T omega, T* __restrict__ xpost, T* __restrict__ x2,
                                           T* __restrict__ bc, int dmask,
-                                          double* __restrict__ rowpart, int strip, int chunk) {
+                                          double* __restrict__ rowpart, int strip, int chunk,
+                                          const double* __restrict__ guard) {
     BlockTile<T, W, BLK_MID_HALO> t(s, N, strip, chunk);
+    t.heed(guard);
     T v[4], e[4];
     t.start(bands, bs, x, xc, b, v);
     t.sweep(v, omega);

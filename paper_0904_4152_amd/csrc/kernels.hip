@@ -174,14 +174,20 @@ __global__ __launch_bounds__(BLOCK) void k_defect_cast(const double* __restrict_
 // same way and resets the ticket for the next reduction.  The fences order
 // each segment sum before its ticket and the last workgroup's reads after it,
 // across the XCDs' caches.
-__device__ void reduce_block(const RedJob& j, int blk) {
+//
+// A guard that is not zero ends it before it writes; it is read beside the
+// partials (a test before them would cost a memory latency).
+__device__ void reduce_block(const RedJob& j, int blk, const double* __restrict__ guard) {
     if (threadIdx.x >= BLOCK) return;
+    const double stop = *(guard ? guard : &dev::zero_guard);
     double s;
     if (j.blocks == 1) {
         s = dev::strided_sum(j.partials, 0, j.np);
+        if (stop != 0.0) return;
     } else {
         const double v = dev::strided_sum(j.partials, blk * dev::RED_SEG,
                                           std::min<int64_t>(j.np, (blk + 1) * dev::RED_SEG));
+        if (stop != 0.0) return;
         __shared__ unsigned last;
         if (threadIdx.x == 0) {
             j.segs[blk] = v;
@@ -207,7 +213,7 @@ __device__ void reduce_block(const RedJob& j, int blk) {
 }
 
 __global__ __launch_bounds__(BLOCK) void k_reduce(RedJob job, const double* __restrict__ guard) {
-    if (!skipped(guard)) reduce_block(job, (int)blockIdx.x);
+    reduce_block(job, (int)blockIdx.x, guard);
 }
 
 template <typename T>
@@ -288,17 +294,27 @@ __global__ __launch_bounds__(mid_threads<T>(), sizeof(T) == 8 ? 2 : 3) void k_mi
                                        g.rh, g.cw);
 }
 
+// Kernel arguments lie in host-written memory, a miss for every wait on them.
+// Asked for at the start, all at once, they cost one; the compiler reads them
+// where the code branches on them.  With the guard read among the tile's loads
+// (dev::pass_over): mixed solves L = 8 452 -> 419 us, L = 9 576 -> 537, L = 10 795 ->
+// 754, FP64 L = 10 852 -> 794.
+#define MG_ARGS_AT_ONCE(p0, p1, p2, p3, p4, p5, p6, p7)                                    \
+    asm volatile("" ::"s"(p0), "s"(p1), "s"(p2), "s"(p3), "s"(p4), "s"(p5), "s"(p6), "s"(p7), \
+                 "s"(bands), "s"(bs), "s"(N), "s"(omega))
+
 // The same passes in block tiles of W wavefronts, with NU sweeps.
 template <typename T, bool XZERO, int W, int NU>
 __global__ __launch_bounds__(64 * W) void k_pre_blk(
     const T* __restrict__ bands, int64_t bs, int N, const T* __restrict__ x,
     const T* __restrict__ b, T omega, T* __restrict__ x2out, T* __restrict__ bc, int dmask,
     dev::FusedGeom g, const double* __restrict__ guard) {
+    MG_ARGS_AT_ONCE(x, b, x2out, bc, dmask, g.nstrips, g.nchunks, guard);
     const int64_t lb = xcd_block((int64_t)g.nstrips * g.nchunks);
-    if (lb < 0 || skipped(guard)) return;
+    if (lb < 0 || dev::pass_over(guard, N)) return;
     __shared__ dev::BlockLds<T, W> s;
     dev::pre_block<T, XZERO, W, NU>(s, bands, bs, N, x, b, omega, x2out, bc, dmask,
-                                    (int)(lb % g.nstrips), (int)(lb / g.nstrips));
+                                    (int)(lb % g.nstrips), (int)(lb / g.nstrips), guard);
 }
 
 template <typename T, bool NORM, int W, int NU>
@@ -306,11 +322,12 @@ __global__ __launch_bounds__(64 * W) void k_post_blk(
     const T* __restrict__ bands, int64_t bs, int N, const T* __restrict__ x,
     const T* __restrict__ xc, const T* __restrict__ b, T omega, T* __restrict__ xout,
     double* __restrict__ partials, dev::FusedGeom g, const double* __restrict__ guard) {
+    MG_ARGS_AT_ONCE(x, xc, b, xout, partials, g.nstrips, g.nchunks, guard);
     const int64_t lb = xcd_block((int64_t)g.nstrips * g.nchunks);
-    if (lb < 0 || skipped(guard)) return;
+    if (lb < 0 || dev::pass_over(guard, N)) return;
     __shared__ dev::BlockLds<T, W> s;
     dev::post_block<T, NORM, W, NU>(s, bands, bs, N, x, xc, b, omega, xout, partials,
-                                    (int)(lb % g.nstrips), (int)(lb / g.nstrips));
+                                    (int)(lb % g.nstrips), (int)(lb / g.nstrips), guard);
 }
 
 // The merged pass in block tiles of W wavefronts.
@@ -320,11 +337,12 @@ __global__ __launch_bounds__(64 * W) void k_mid_blk(
     const T* __restrict__ xc, const T* __restrict__ b, T omega, T* __restrict__ xpost,
     T* __restrict__ x2, T* __restrict__ bc, int dmask, double* __restrict__ partials, int nstrips,
     int nchunks, const double* __restrict__ guard) {
+    MG_ARGS_AT_ONCE(x, xc, b, xpost, x2, nstrips, nchunks, guard);
     const int64_t lb = xcd_block((int64_t)nstrips * nchunks);
-    if (lb < 0 || skipped(guard)) return;
+    if (lb < 0 || dev::pass_over(guard, N)) return;
     __shared__ dev::BlockLds<T, W> s;
     dev::mid_block<T, W>(s, bands, bs, N, x, xc, b, omega, xpost, x2, bc, dmask, partials,
-                         (int)(lb % nstrips), (int)(lb / nstrips));
+                         (int)(lb % nstrips), (int)(lb / nstrips), guard);
 }
 
 // Coarse tail: the V(nu_pre, nu_post) sub-cycle over levels top..Lc in one
@@ -336,7 +354,7 @@ __global__ __launch_bounds__(dev::TAIL_THREADS) void k_tail(dev::TailLevels<T> t
                                                              const double* __restrict__ guard,
                                                              RedJob job) {
     if (blockIdx.x > 0) {
-        if (!skipped(guard)) reduce_block(job, (int)blockIdx.x - 1);
+        reduce_block(job, (int)blockIdx.x - 1, guard);
         return;
     }
     // The kernel arguments span several cache lines of host-written memory.
