@@ -127,7 +127,7 @@ enum : int {
     SC_RZ_OLD = 14,
     SC_RR = 16,
     SC_XNZ = 18,  // nonzero elements of the initial iterate
-    // device control of the mixed solve's inner loop (k_inner_ctrl)
+    // device control of a solve's loop (red_control)
     SC_STOP = 20,  // nonzero: the loop is over (its remaining cycles return at once)
     SC_WAIT = 21,  // nonzero: the loop is still running (the update waits)
     SC_ITER = 22,  // cycles run; host mirror: the same, plus ITER_DONE once over

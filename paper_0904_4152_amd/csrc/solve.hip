@@ -466,7 +466,7 @@ static hipError_t read_scalar(mg_hierarchy* h, int slot, hipStream_t st, double*
     return hipSuccess;
 }
 
-// The inner-loop state k_inner_ctrl mirrors (cycles run, plus ITER_DONE once
+// The inner-loop state red_control mirrors (cycles run, plus ITER_DONE once
 // the loop is over): wait until the loop is over or has run `want` cycles.
 static void arm_iter(mg_hierarchy* h) { ((volatile double*)h->host_scal)[SC_ITER] = kArmed; }
 
