@@ -108,8 +108,10 @@ struct mg_hierarchy {
     // outer steps of the previous such solve (0: none yet): later steps are
     // not queued ahead of their defect's norm
     int outer_prev = 0;
-    // cycles of the last two FP64 V(2,2) solves (0: none yet)
-    int cycles_prev[2] = {0, 0};
+    // an FP64 V(2,2) solve has run cycles; log residual reduction a cycle of
+    // the last two that ended at their tolerance (0: none yet)
+    bool fp64_solved = false;
+    double rate_prev[2] = {0.0, 0.0};
 };
 
 namespace mg {

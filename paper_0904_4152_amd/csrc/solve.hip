@@ -730,13 +730,18 @@ extern "C" mg_status mg_solve(mg_hierarchy* h, const double* dev_b, double* dev_
         // V(2,2) cycles run under device control: the reduction that yields a
         // cycle's norm takes the tests below (RED_CYCLE), and cycles queued
         // behind the last one return at once.  So several cycles go out in one
-        // graph before the host has read a norm: as many as the shorter of the
-        // last two solves took (or fixed_cycles), in powers of two up to 8, so
+        // graph before the host has read a norm, in powers of two up to 8, so
         // that few graphs are captured.  A graph per cycle leaves some 4 us
         // between cycles, whether or not the host waits for the norm between
         // them (solves of 9 cycles: L = 6 331 -> 303 us, L = 8 475 -> 435, L = 10
-        // 918 -> 885).  The first solve of a hierarchy, and cycles past the
-        // prediction, go out one by one.
+        // 918 -> 885).  A cycle too many costs more, about eight launches that
+        // do nothing (10 us at L = 6, 40 at L = 9, 60 at L = 12): as many go out
+        // as the first residual needs at the rate of the faster of the last two
+        // solves, rounded up (or fixed_cycles).  From a zero iterate that
+        // residual is b; any other one is read first, as the iterate may be the
+        // solution already (with as many cycles as earlier solves took queued
+        // behind it, such a call took 452 us at L = 9, now 109).  The first solve of
+        // a hierarchy, and cycles past the prediction, go out one by one.
         const bool guarded = o.nu_pre == 2 && o.nu_post == 2 && h->L > h->Lc;
         const bool chain = guarded && chained(h, 8);
         const int cap = o.fixed_cycles > 0 ? o.fixed_cycles : o.max_cycles;
@@ -759,10 +764,13 @@ extern "C" mg_status mg_solve(mg_hierarchy* h, const double* dev_b, double* dev_
             q.bytes += 11.0 * 8 * n;
         }
         auto ring = [](int k) { return SC_HIST + k % HIST_RING - 1; };
-        const int* prev = h->cycles_prev;
-        const int ahead = prev[0] == 0         ? 0
-                          : o.fixed_cycles > 0 ? cap
-                                               : std::min({cap, prev[0], prev[1] ? prev[1] : cap});
+        const double rate = std::max(h->rate_prev[0], h->rate_prev[1]);
+        auto cycles_for = [&](double r0) -> int {
+            if (o.fixed_cycles > 0) return h->fp64_solved ? cap : 0;
+            if (!(rate > 0.0)) return 0;
+            const double need = std::log(r0 / (o.rel_tol * bn)) / rate;
+            return need > 0.0 ? (int)std::min((double)cap, std::ceil(need)) : 0;
+        };
         int sent = 0;  // cycles queued
         auto queue_to = [&](int k) -> hipError_t {
             while (sent < k) {
@@ -783,12 +791,16 @@ extern "C" mg_status mg_solve(mg_hierarchy* h, const double* dev_b, double* dev_
         };
         // the cycles to have been queued before the norm of cycle k is read: the
         // norms in flight stay within half the mirror's ring
+        const bool known = x_zero || o.fixed_cycles > 0;
+        int ahead = guarded && known ? cycles_for(bn) : 0;
         auto horizon = [&](int k) {
             return sent >= k ? sent : std::max(k, std::min(ahead, k + HIST_RING / 2 - 1));
         };
-        if (guarded && ahead > 0) MG_HIPS(queue_to(horizon(1)));
+        if (ahead > 0) MG_HIPS(queue_to(horizon(1)));
         MG_HIPS(read_scalar(h, SC_R64B, q.st, &r));
         st.rel_res = r / bn;
+        const double r0 = r;
+        if (guarded && !known) ahead = cycles_for(r0);
         for (int k = 1;; ++k) {
             if (o.fixed_cycles > 0) {
                 if (k > o.fixed_cycles) break;
@@ -816,9 +828,13 @@ extern "C" mg_status mg_solve(mg_hierarchy* h, const double* dev_b, double* dev_
                 break;
             }
         }
-        if (guarded && result == MG_OK) {
-            h->cycles_prev[1] = h->cycles_prev[0];
-            h->cycles_prev[0] = std::max(st.cycles, 1);
+        if (guarded && result == MG_OK && st.cycles > 0) {
+            h->fp64_solved = true;
+            const double rate_now = std::log(r0 / r) / st.cycles;
+            if (o.fixed_cycles == 0 && std::isfinite(rate_now)) {
+                h->rate_prev[1] = h->rate_prev[0];
+                h->rate_prev[0] = rate_now;
+            }
         }
     } else if (!devctl) {
         // host-driven loop: one host read per FP64 defect and per FP32 cycle
