@@ -11,13 +11,15 @@ pytestmark = pytest.mark.gpu
 
 
 def seconds(h, b, x, opts, before=lambda: None):
-    """Shortest of seven calls that find x solved, after `before` each time."""
+    """Shortest of seven calls that find x solved, to the end of what they queued,
+    after `before` each time."""
     best = 1.0
     for _ in range(7):
         before()
         torch.cuda.synchronize()
         t = time.perf_counter()
         st = h.solve(b, x, opts)
+        torch.cuda.synchronize()
         best = min(best, time.perf_counter() - t)
         assert st.cycles == 0
     return best
