@@ -205,6 +205,25 @@ __device__ __forceinline__ float* role32(const BLevel& lv, int r) { return r ? l
 
 #define END_ITEMS }
 
+// A band product tile of the separate kernels (nine bands).  Bands of a list
+// that together exceed the 256 MB last-level cache are loaded non-temporally,
+// those below stay in it (V(1,1) solves, all cached / all non-temporal: 40
+// problems of L = 8, 95 MB, 4411 / 4481 us; of L = 9, 379 MB, 11280 / 10282; 8 of
+// L = 11, 1.2 GB, 30660 / 29308).
+__device__ __forceinline__ bool streams(const WlHead& h) {
+    return h.total > (256 << 20) / (9 * (int)sizeof(float) * TILE);
+}
+template <int OP>
+__device__ __forceinline__ void band_tile(const BLevel& lv, int src, int dst, float omega,
+                                          int64_t base, bool stream) {
+    if (stream)
+        dev::stencil_tile<float, OP, false, true, false, false, true>(
+            lv.bands32, lv.bs, lv.N, lv.n, role32(lv, src), lv.b32, role32(lv, dst), omega, base);
+    else
+        dev::stencil_tile<float, OP, false, true>(lv.bands32, lv.bs, lv.N, lv.n, role32(lv, src),
+                                                  lv.b32, role32(lv, dst), omega, base);
+}
+
 // First pre-smoothing sweep at level l: from a zero iterate on every level
 // below the problem's finest and on the finest level at the first inner
 // cycle of an outer step; otherwise a full sweep src -> dst.
@@ -226,9 +245,7 @@ __global__ __launch_bounds__(BLOCK) void kb_pre1(const BProb* __restrict__ probs
             if (q < lv.n) dev::jacobi_zero_elem(diag, (const float*)lv.b32, xo, q, om);
         }
     } else {
-        dev::stencil_tile<float, dev::OP_JACOBI, false, true>(lv.bands32, lv.bs, lv.N, lv.n,
-                                                              role32(lv, src), lv.b32,
-                                                              role32(lv, dst), om, base);
+        band_tile<dev::OP_JACOBI>(lv, src, dst, om, base, streams(head_));
     }
     END_ITEMS
 }
@@ -261,9 +278,7 @@ __global__ __launch_bounds__(BLOCK) void kb_band(const BProb* __restrict__ probs
     FOR_ITEMS(wl)
     if (!(flags & mask)) continue;
     const BLevel& lv = P.lv[l];
-    dev::stencil_tile<float, OP, false, true>(lv.bands32, lv.bs, lv.N, lv.n, role32(lv, src),
-                                              lv.b32, role32(lv, dst), (float)P.omega,
-                                              (int64_t)tile * TILE);
+    band_tile<OP>(lv, src, dst, (float)P.omega, (int64_t)tile * TILE, streams(head_));
     END_ITEMS
 }
 

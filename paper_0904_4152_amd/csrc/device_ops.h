@@ -167,7 +167,8 @@ __device__ __forceinline__ void store_floats(float* __restrict__ p, const float*
 // streamed by the tiles just before (same XCD), so the shifted reads are
 // served by the cache and HBM sees 5 band streams instead of 9.  Same
 // values, same results.
-template <typename T, int OP, bool NORM, bool STORE, bool SYM = false, bool CAST = false>
+template <typename T, int OP, bool NORM, bool STORE, bool SYM = false, bool CAST = false,
+          bool STREAM = false>
 __device__ __forceinline__ double stencil_tile(const T* __restrict__ bands, int64_t bs, int N,
                                                int64_t n, const T* __restrict__ x,
                                                const T* __restrict__ b, T* __restrict__ out,
@@ -201,7 +202,8 @@ __device__ __forceinline__ double stencil_tile(const T* __restrict__ bands, int6
 #pragma unroll
     for (int k = SYM ? 4 : 0; k < 9; ++k) {
         // band arrays are padded beyond n, so the vector load stays in bounds
-        const VT v = *reinterpret_cast<const VT*>(bands + k * bs + p0);
+        const VT* src = reinterpret_cast<const VT*>(bands + k * bs + p0);
+        const VT v = STREAM && (!SYM || k == 4) ? __builtin_nontemporal_load(src) : *src;
         __builtin_memcpy(bk[k], &v, sizeof(VT));
     }
     if (SYM) {
