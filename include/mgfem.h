@@ -277,7 +277,8 @@ typedef struct {
     int tile_rows;    /* chosen rows per tile */
     int row_waves;    /* chosen wavefronts per workgroup (across a strip's row when marching) */
     int tile_cols;    /* 0: marching tile; 32: a block tile */
-    double us;        /* one pre + post pass pair with that tile, microseconds */
+    double us;        /* one pre + post pass pair with that tile, microseconds;
+                         mg_hierarchy_autotune: negative if the choice is not stored */
 } mg_tile_choice;
 mg_status mg_batch_autotune(mg_hierarchy* const* hs, int count, const mg_solve_opts* opts,
                             int reps, mg_tile_choice* out, int out_cap, int* n_out);
@@ -290,12 +291,14 @@ mg_status mg_batch_clear_tiles(void);
  * FP64, and above that the marching tile of least modelled cost): for
  * every level on which h's V(2,2) cycle runs fused passes, times the FP32
  * pre- and post-smoothing passes as the mixed solve runs them (reps pairs
- * per candidate, on h's FP32 work vectors) for 4, 8, 12, 16, 24, 32, 40, 48,
+ * per candidate, on h's work vectors) for 4, 8, 12, 16, 24, 32, 40, 48,
  * 64, 80, 96, 128, 160, 192 and 256 rows per tile and 1 .. 4 wavefronts per
  * row, and on levels of at most 1025 nodes per side for
- * each block tile, and stores the fastest under problems = 1 (on a level
- * above that where the rule's block tile is faster than every candidate it
- * stores none, and out reports the fastest candidate).  Tiles
+ * each block tile.  The fastest is timed against the rule, in turn and in both
+ * types (an entry serves FP32 and FP64 passes), and stored under problems = 1 if
+ * it is faster in FP32 and not slower in FP64; else the level keeps the rule
+ * (an entry it had is removed), and out still reports the fastest candidate,
+ * with -us: such a choice is not for mg_batch_set_tile.  Tiles
  * change no result bit; solves captured before are captured again.  (Between two
  * V(2,2) cycles of one solve the finest level's post and pre passes run as one,
  * with tiles of its own that the table does not set.)

@@ -386,7 +386,8 @@ class Hierarchy:
 
     def autotune(self, reps=10):
         """Tune the single-problem fused passes' tiles of this hierarchy's
-        levels (mg_hierarchy_autotune); returns the choices as dicts."""
+        levels (mg_hierarchy_autotune); returns the fastest candidates as dicts,
+        "installed" where they are in force (elsewhere the rule is)."""
         out = (TileChoice * 16)()
         got = _i()
         check(lib().mg_hierarchy_autotune(self._h, reps, out, 16, ctypes.byref(got)))
@@ -401,7 +402,8 @@ class Hierarchy:
 
 def _choice(c):
     return {"level": c.level, "problems": c.problems, "tile_rows": c.tile_rows,
-            "row_waves": c.row_waves, "tile_cols": c.tile_cols, "us": c.us}
+            "row_waves": c.row_waves, "tile_cols": c.tile_cols, "us": abs(c.us),
+            "installed": c.us > 0}
 
 
 def batch_autotune(hierarchies, opts=None, reps=10):
@@ -420,8 +422,10 @@ def batch_autotune(hierarchies, opts=None, reps=10):
 def batch_set_tiles(rows):
     """Install tile choices (the rows batch_autotune returns, e.g. from JSON;
     a missing row_waves keeps the width rule, a missing tile_cols means a
-    marching tile)."""
+    marching tile); rows that say they were not installed are left out."""
     for r in rows:
+        if not r.get("installed", True):
+            continue
         check(lib().mg_batch_set_tile(int(r["level"]), int(r["problems"]), int(r["tile_rows"]),
                                       int(r.get("row_waves", 0)), int(r.get("tile_cols", 0))))
 

@@ -980,13 +980,29 @@ extern "C" mg_status mg_solve(mg_hierarchy* h, const double* dev_b, double* dev_
 }
 
 // ---------------------------------------------------------------- tiles
+namespace mg {
+// The post- and pre-smoothing pass of level l as a solve runs them, on h's own
+// work vectors (which no solve reads before writing).
+template <typename T>
+static hipError_t tile_pair(mg_hierarchy* h, int l, hipStream_t st) {
+    Level &v = h->lv[l], &c = h->lv[l - 1];
+    const bool finest = l == h->L;
+    const T om = T(0.7);
+    MG_TRY(launch_pre<T>(v, LV<T>::bands(v), LV<T>::x(v), !finest, LV<T>::b(v), om, LV<T>::t(v),
+                         LV<T>::b(c), h->dmask, st));
+    return launch_post<T>(v, LV<T>::bands(v), LV<T>::t(v), LV<T>::x(c), LV<T>::b(v), om,
+                          LV<T>::x(v), finest ? h->partials : nullptr, h->scal, SC_USER, nullptr,
+                          st);
+}
+}  // namespace mg
+
 // Sec. 3: the thread-block partition of the GPU kernels is a runtime
 // parameter.  For every level on which the hierarchy's V(2,2) cycle runs
 // fused passes, time the FP32 pre- and post-smoothing passes (as the mixed
 // solve runs them: the finest level's pre pass from a given iterate and its
 // post pass with the residual norm, the others from zero and without) for
 // each candidate tile and keep the fastest in the tile table under one
-// problem.
+// problem where it beats the rule.
 extern "C" mg_status mg_hierarchy_autotune(mg_hierarchy* h, int reps, mg_tile_choice* out,
                                            int out_cap, int* n_out) {
     if (n_out) *n_out = 0;
@@ -1011,69 +1027,69 @@ extern "C" mg_status mg_hierarchy_autotune(mg_hierarchy* h, int reps, mg_tile_ch
     } g;
     MG_HIP(hipEventCreate(&g.a));
     MG_HIP(hipEventCreate(&g.b));
-    const float om = 0.7f;
     std::vector<mg_tile_choice> rows;
     for (int l = h->L; l > h->Lc; --l) {
         if (!(l > tail_max_level() || l == h->L)) continue;
-        Level& v = h->lv[l];
-        Level& c = h->lv[l - 1];
-        const bool finest = l == h->L;
-        auto pair = [&]() -> hipError_t {
-            MG_TRY(launch_pre<float>(v, v.bands32, v.x32, !finest, v.b32, om, v.t32, c.b32,
-                                     h->dmask, st));
-            return launch_post<float>(v, v.bands32, v.t32, c.x32, v.b32, om, v.x32,
-                                      finest ? h->partials : nullptr, h->scal, SC_USER, nullptr,
-                                      st);
+        const int N = h->lv[l].N;
+        // reps pairs of passes with a tile, in ms
+        auto time_pairs = [&](const std::array<int, 3>& c, bool fp64, float* ms) -> hipError_t {
+            auto pair = [&] { return fp64 ? tile_pair<double>(h, l, st) : tile_pair<float>(h, l, st); };
+            set_single_trial(N, c[1], c[0], c[2]);
+            for (int w = 0; w < 2; ++w) MG_TRY(pair());
+            MG_TRY(hipEventRecord(g.a, st));
+            for (int r = 0; r < reps; ++r) MG_TRY(pair());
+            MG_TRY(hipEventRecord(g.b, st));
+            MG_TRY(hipEventSynchronize(g.b));
+            return hipEventElapsedTime(ms, g.a, g.b);
         };
-        int best_rows = 0, best_bt = 0, best_cols = 0;
-        float best_ms = 0.0f;
         // marching tiles (width x rows), then block tiles on small levels
         std::vector<std::array<int, 3>> cand;
         for (int bt : kWidths)
             for (int rh : kRows) cand.push_back({bt, rh, 0});
-        if (v.N <= dev::BLK_MAX_N)
+        if (N <= dev::BLK_MAX_N)
             for (int s = 1; s <= dev::BLK_SHAPES; ++s)
                 cand.push_back({64 * dev::BLK_TAG_WAVES, dev::block_rows(s), dev::BLK_TAG});
+        std::array<int, 3> best{};
+        float best_ms = 0.0f;
         for (const auto& c : cand) {
-            {
-                const int bt = c[0], rh = c[1];
-                set_single_trial(v.N, rh, bt, c[2]);
-                for (int w = 0; w < 2; ++w) MG_HIP(pair());
-                MG_HIP(hipEventRecord(g.a, st));
-                for (int r = 0; r < reps; ++r) MG_HIP(pair());
-                MG_HIP(hipEventRecord(g.b, st));
-                MG_HIP(hipEventSynchronize(g.b));
-                float ms = 0.0f;
-                MG_HIP(hipEventElapsedTime(&ms, g.a, g.b));
-                if (!best_rows || ms < best_ms) {
-                    best_rows = rh;
-                    best_bt = bt;
-                    best_cols = c[2];
-                    best_ms = ms;
-                }
+            float ms = 0.0f;
+            MG_HIP(time_pairs(c, false, &ms));
+            if (best_ms == 0.0f || ms < best_ms) {
+                best = c;
+                best_ms = ms;
             }
         }
-        // where the rule takes block tiles on larger levels than they are
-        // candidates on, it stays in force unless a candidate beat it
-        const dev::FusedGeom rule = single_rule(v.N, sizeof(float));
-        bool keep_rule = false;
-        if (rule.blk && v.N > dev::BLK_MAX_N) {
-            set_single_trial(v.N, rule.rh, 64 * dev::BLK_TAG_WAVES, dev::BLK_TAG);
-            for (int w = 0; w < 2; ++w) MG_HIP(pair());
-            MG_HIP(hipEventRecord(g.a, st));
-            for (int r = 0; r < reps; ++r) MG_HIP(pair());
-            MG_HIP(hipEventRecord(g.b, st));
-            MG_HIP(hipEventSynchronize(g.b));
-            float ms = 0.0f;
-            MG_HIP(hipEventElapsedTime(&ms, g.a, g.b));
-            keep_rule = ms < best_ms;
+        // An entry replaces the rule in both types, and the rule's tiles differ by
+        // type (FP32 L = 10 and 11, L = 12: 16 rows, block tiles, another march).
+        // It is stored only if, timed in turn with the rule, it is faster in FP32
+        // and not slower in FP64: stored regardless, FP64 passes went 30.5 -> 33.5
+        // us at L = 10 and 461 -> 473 at L = 12, the FP64 solve 5281 -> 5383.
+        bool keep = true, same = true;
+        for (const bool fp64 : {false, true}) {
+            const dev::FusedGeom r = single_rule(N, fp64 ? 8 : 4);
+            const std::array<int, 3> rule =
+                r.blk ? std::array<int, 3>{64 * dev::BLK_TAG_WAVES, r.rh, dev::BLK_TAG}
+                      : std::array<int, 3>{r.bt, r.rh, 0};
+            if (rule == best) continue;
+            same = false;
+            float mine = 0.0f, ruled = 0.0f;
+            for (int turn = 0; turn < 3; ++turn) {
+                float a = 0.0f, b = 0.0f;
+                MG_HIP(time_pairs(rule, fp64, &a));
+                MG_HIP(time_pairs(best, fp64, &b));
+                ruled += a;
+                mine += b;
+            }
+            if (mine > ruled) keep = false;
         }
+        keep = keep && !same;
         set_single_trial(0, 0, 0);
-        if (keep_rule)
-            tile_table_erase(l, 1);
+        if (keep)
+            tile_table_set(l, 1, best[1], best[0], best[2]);
         else
-            tile_table_set(l, 1, best_rows, best_bt, best_cols);
-        rows.push_back({l, 1, best_rows, best_bt / 64, best_cols, 1e3 * best_ms / reps});
+            tile_table_erase(l, 1);
+        const double us = 1e3 * best_ms / reps;
+        rows.push_back({l, 1, best[1], best[0] / 64, best[2], keep ? us : -us});
     }
     const int n = std::min<int>(out_cap, (int)rows.size());
     for (int i = 0; i < n; ++i) out[i] = rows[i];
