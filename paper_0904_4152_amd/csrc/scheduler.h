@@ -19,6 +19,7 @@
 #include <cstring>
 #include <deque>
 #include <list>
+#include <map>
 #include <mutex>
 #include <new>
 #include <string>
@@ -85,6 +86,75 @@ private:
     size_t n_ = 0;
     Release release_ = nullptr;
     void* owner_ = nullptr;
+};
+
+// Solution buffers by length from an allocator of the executor's: kept for
+// later results of that length, at most max_bytes in all (in use and idle; idle
+// ones of other lengths make room), freed with the pool, which outlives them.
+// Threads that collect results give buffers back; that allocates nothing and so
+// cannot fail (room for a buffer in its list is made before the buffer).
+class ResultPool {
+public:
+    using Alloc = double* (*)(size_t bytes);  // null: no memory
+    using Free = void (*)(double*);
+    ResultPool(size_t max_bytes, Alloc alloc, Free free)
+        : max_(max_bytes), alloc_(alloc), free_(free) {}
+    ResultPool(const ResultPool&) = delete;
+    ResultPool& operator=(const ResultPool&) = delete;
+    ~ResultPool() {
+        for (auto& c : lists_)
+            for (double* p : c.second.idle) free_(p);
+    }
+    // n values, not initialised (empty when they do not fit)
+    SolutionBuffer take(size_t n) {
+        std::lock_guard<std::mutex> g(mu_);
+        double* p = nullptr;
+        try {
+            p = find(n);
+        } catch (const std::bad_alloc&) {
+        }
+        if (!p) return {};
+        return {p, n, [](void* self, double* q, size_t m) { ((ResultPool*)self)->give(q, m); }, this};
+    }
+
+private:
+    struct List {
+        std::vector<double*> idle;
+        size_t count = 0;  // in use and idle
+    };
+    double* find(size_t n) {
+        List& c = lists_[n];
+        if (!c.idle.empty()) {
+            double* p = c.idle.back();
+            c.idle.pop_back();
+            return p;
+        }
+        const size_t need = n * sizeof(double);
+        for (auto& o : lists_)
+            while (bytes_ + need > max_ && !o.second.idle.empty()) {
+                free_(o.second.idle.back());
+                o.second.idle.pop_back();
+                --o.second.count;
+                bytes_ -= o.first * sizeof(double);
+            }
+        if (bytes_ + need > max_) return nullptr;
+        if (c.idle.capacity() <= c.count) c.idle.reserve(2 * c.count + 1);
+        double* p = alloc_(need);
+        if (!p) return nullptr;
+        ++c.count;
+        bytes_ += need;
+        return p;
+    }
+    void give(double* p, size_t n) noexcept {
+        std::lock_guard<std::mutex> g(mu_);
+        lists_.find(n)->second.idle.push_back(p);
+    }
+    const size_t max_;
+    const Alloc alloc_;
+    const Free free_;
+    std::mutex mu_;
+    std::map<size_t, List> lists_;
+    size_t bytes_ = 0;
 };
 
 struct SchedResult {

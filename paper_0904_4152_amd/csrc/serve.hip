@@ -13,8 +13,6 @@
 
 #include <chrono>
 #include <cstring>
-#include <map>
-#include <mutex>
 #include <vector>
 
 #include "batch.h"
@@ -101,9 +99,10 @@ public:
             if (!keep_x[i]) continue;
             const mg_hierarchy* h = (const mg_hierarchy*)hs[i];
             const Level& F = h->lv[h->L];
-            if (double* p = take_pinned(F.n)) {
-                f.x = SolutionBuffer(p, (size_t)F.n, &HipExecutor::give_pinned, this);
-                if (mg_status s = eng_.fetch_async(F.x64, p, (size_t)F.n * sizeof(double)))
+            f.x = pool_.take((size_t)F.n);
+            if (!f.x.empty()) {
+                if (mg_status s =
+                        eng_.fetch_async(F.x64, f.x.data(), (size_t)F.n * sizeof(double)))
                     return s;
             } else {
                 f.x = SolutionBuffer::plain((size_t)F.n);
@@ -128,9 +127,6 @@ public:
     std::string error_message() override { return mg_last_error(); }
 
     ~HipExecutor() override {
-        fetched_.clear();  // its buffers go back to idle_
-        for (auto& c : idle_)
-            for (double* p : c.second) (void)hipHostFree(p);
         if (states_) (void)hipHostFree(states_);
     }
 
@@ -139,52 +135,26 @@ private:
         bool state = false;
         SolutionBuffer x;
     };
-    // Pinned solution buffers by length: kept for later results of that
-    // length, at most PINNED_MAX bytes in all (in use and idle; idle ones of
-    // other lengths make room), freed with the server.  Without one the copy
-    // goes to pageable memory: the runtime then stages it, and every page of a
-    // fresh vector faults (2 ms of a burst of 32 requests, 23 MB).
+    // Pinned solution buffers.  Without one the copy goes to pageable memory: the
+    // runtime then stages it, and every page of a fresh vector faults (2 ms of a
+    // burst of 32 requests, 23 MB).
     static constexpr size_t PINNED_MAX = (size_t)256 << 20;
-    double* take_pinned(int64_t n) {
-        std::lock_guard<std::mutex> g(pin_mu_);
-        std::vector<double*>& c = idle_[n];
-        if (!c.empty()) {
-            double* p = c.back();
-            c.pop_back();
-            return p;
-        }
-        const size_t need = (size_t)n * sizeof(double);
-        for (auto& o : idle_)
-            while (pinned_ + need > PINNED_MAX && !o.second.empty()) {
-                (void)hipHostFree(o.second.back());
-                o.second.pop_back();
-                pinned_ -= (size_t)o.first * sizeof(double);
-            }
-        if (pinned_ + need > PINNED_MAX) return nullptr;
+    static double* pinned_alloc(size_t bytes) {
         double* p = nullptr;
-        if (hipHostMalloc((void**)&p, need, hipHostMallocDefault) != hipSuccess) {
-            (void)hipGetLastError();
-            return nullptr;
-        }
-        pinned_ += need;
-        return p;
+        if (hipHostMalloc((void**)&p, bytes, hipHostMallocDefault) == hipSuccess) return p;
+        (void)hipGetLastError();
+        return nullptr;
     }
-    static void give_pinned(void* self, double* p, size_t n) {
-        HipExecutor* e = (HipExecutor*)self;
-        std::lock_guard<std::mutex> g(e->pin_mu_);
-        e->idle_[(int64_t)n].push_back(p);
-    }
+    static void pinned_free(double* p) { (void)hipHostFree(p); }
 
     mg_context* ctx_ = nullptr;
     int Lc_ = 1;
     mg_solve_opts opts_{};
     BatchEngine eng_;
     std::vector<int> done_;
+    ResultPool pool_{PINNED_MAX, pinned_alloc, pinned_free};
     std::vector<Fetched> fetched_;   // by slot, between begin_finish and finish
     BState* states_ = nullptr;       // pinned, by slot
-    std::mutex pin_mu_;              // collecting threads give buffers back
-    std::map<int64_t, std::vector<double*>> idle_;
-    size_t pinned_ = 0;
 };
 
 }  // namespace
