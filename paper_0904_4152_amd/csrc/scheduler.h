@@ -292,8 +292,9 @@ public:
         info->busy_seconds = busy_seconds_.load();
     }
 
-    // Finish every queued and running request, stop the worker and destroy
-    // the idle hierarchies.  Idempotent.
+    // Finish every queued and running request, stop the worker, wait for the
+    // threads that are taking a result out and destroy the idle hierarchies.
+    // Idempotent.
     void shutdown() {
         {
             std::lock_guard<std::mutex> g(mu_);
@@ -301,6 +302,10 @@ public:
             cv_work_.notify_all();
         }
         if (worker_.joinable()) worker_.join();
+        {
+            std::unique_lock<std::mutex> g(mu_);
+            cv_collected_.wait(g, [&] { return collecting_ == 0; });
+        }
         for (PoolEntry& e : pool_) ex_->destroy_hierarchy(e.h);
         pool_.clear();
         for (size_t s = 0; s < slot_h_.size(); ++s)
@@ -396,20 +401,29 @@ private:
     }
 
     // Caller holds mu_ through g; released for the copy of the solution (the
-    // worker goes on meanwhile).
+    // worker goes on meanwhile).  The result's buffer is back with the executor
+    // before the collection counts as over.
     mg_status collect(std::unique_lock<std::mutex>& g, uint64_t t, double* host_x, mg_stats* st) {
-        auto it = done_.find(t);
-        SchedResult r = std::move(it->second);
-        done_.erase(it);
-        for (auto q = done_order_.begin(); q != done_order_.end(); ++q)
-            if (*q == t) {
-                done_order_.erase(q);
-                break;
-            }
-        g.unlock();
-        if (host_x && !r.x.empty()) std::memcpy(host_x, r.x.data(), r.x.size() * sizeof(double));
-        if (st) *st = r.stats;
-        return r.stats.status;
+        mg_status status;
+        {
+            auto it = done_.find(t);
+            SchedResult r = std::move(it->second);
+            done_.erase(it);
+            for (auto q = done_order_.begin(); q != done_order_.end(); ++q)
+                if (*q == t) {
+                    done_order_.erase(q);
+                    break;
+                }
+            ++collecting_;
+            g.unlock();
+            if (host_x && !r.x.empty())
+                std::memcpy(host_x, r.x.data(), r.x.size() * sizeof(double));
+            if (st) *st = r.stats;
+            status = r.stats.status;
+        }
+        g.lock();
+        if (--collecting_ == 0) cv_collected_.notify_all();
+        return status;
     }
 
     void run() {
@@ -509,7 +523,8 @@ private:
     std::thread worker_;
     // shared with the submitting and collecting threads (under mu_)
     std::mutex mu_;
-    std::condition_variable cv_work_, cv_done_;
+    std::condition_variable cv_work_, cv_done_, cv_collected_;
+    int collecting_ = 0;  // threads taking a result out
     bool stop_ = false;
     mg_status fatal_ = MG_OK;
     std::string fatal_msg_;

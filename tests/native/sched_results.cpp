@@ -3,6 +3,7 @@
 // of several problems fetched together, and the collecting threads' share.
 // Built and run by tests/test_native_results.py; prints "ALL PASS".
 #include <atomic>
+#include <chrono>
 #include <cstdio>
 #include <cstdlib>
 #include <new>
@@ -76,10 +77,16 @@ static void scenario_pool() {
     std::printf("PASS pool\n");
 }
 
+static std::atomic<bool> executor_alive{false};
+static std::atomic<bool> releasing{false};
+
 // One iteration per problem; results fetched in begin_finish.
 class Exec final : public Executor {
 public:
-    explicit Exec(int slots) : used_(slots, 0), done_(slots, 0), x_(slots) {}
+    explicit Exec(int slots, bool slow) : slow_(slow), used_(slots, 0), done_(slots, 0), x_(slots) {
+        executor_alive = true;
+    }
+    ~Exec() override { executor_alive = false; }
     double now() override { return 0.0; }
     int capacity() const override { return (int)used_.size(); }
     size_t hierarchy_bytes(int) const override { return 1; }
@@ -104,7 +111,7 @@ public:
         for (int i = 0; i < n; ++i) {
             if (!keep_x[i]) continue;
             SolutionBuffer& b = x_[slots[i]];
-            b = pool_.take(2);
+            b = slow_ ? SolutionBuffer(new double[2], 2, &Exec::slow_release, this) : pool_.take(2);
             if (b.empty()) b = SolutionBuffer::plain(2);
             b.data()[0] = (double)used_[slots[i]];
             b.data()[1] = *(int*)hs[i];
@@ -119,17 +126,26 @@ public:
     }
 
 private:
+    static void slow_release(void* self, double* p, size_t) {
+        releasing = true;
+        std::this_thread::sleep_for(std::chrono::milliseconds(200));
+        CHECK(executor_alive);
+        ++((Exec*)self)->released_;
+        delete[] p;
+    }
+    const bool slow_;
     ResultPool pool_{8 * sizeof(double), hold, drop};  // four results
     std::vector<uint64_t> used_;
     std::vector<int> done_;
     std::vector<SolutionBuffer> x_;
     int64_t launched_ = 0;
+    int released_ = 0;
 };
 
 // Three threads collect the results of two submitters, by ticket and in order
 // of completion: each is its ticket's, from the pool or beyond it.
 static void scenario_collectors() {
-    auto* ex = new Exec(8);
+    auto* ex = new Exec(8, false);
     auto* sched = new Scheduler(ex, 1 << 20);
     sched->start();
     const int per = 300;
@@ -164,9 +180,40 @@ static void scenario_collectors() {
     std::printf("PASS collectors\n");
 }
 
+// A server is destroyed while a thread is still taking a result out of it: the
+// executor lives until the result's buffer is back.
+static void scenario_destroyed_while_collecting() {
+    auto* ex = new Exec(1, true);
+    auto* sched = new Scheduler(ex, 1 << 20);
+    sched->start();
+    uint64_t t = 0;
+    std::string err;
+    CHECK(sched->submit(3, 1e-8, 0.0, 1, 1, 1, &t, &err) == MG_OK);
+    mg_server_info_t info{};
+    for (int i = 0; i < 20000 && info.completed == 0; ++i) {
+        std::this_thread::sleep_for(std::chrono::microseconds(100));
+        sched->info(&info);
+    }
+    CHECK(info.completed == 1);
+    std::thread collector([&] {
+        double x[2] = {0, 0};
+        mg_stats st{};
+        std::string e;
+        CHECK(sched->poll(t, x, &st, &e) == MG_OK && x[0] == (double)t);
+    });
+    for (int i = 0; i < 20000 && !releasing; ++i)
+        std::this_thread::sleep_for(std::chrono::microseconds(100));
+    CHECK(releasing);
+    delete sched;
+    delete ex;
+    collector.join();
+    std::printf("PASS destroyed_while_collecting\n");
+}
+
 int main() {
     scenario_pool();
     scenario_collectors();
+    scenario_destroyed_while_collecting();
     std::printf("ALL PASS\n");
     return 0;
 }
