@@ -1061,12 +1061,25 @@ static int env_int(const char* name, int dflt) {
     return e ? atoi(e) : dflt;
 }
 
+// MG_FUSED_BT (64, 128, 192 or 256) forces the width of marching tiles and
+// MG_FUSED_WAVES the wavefronts their heights aim at; with either, passes
+// without a tuned entry are marching tiles on every level (except the merged
+// and the one-sweep passes, which have tiles of their own).  0: not forced.
+static int forced_bt() {
+    static const int bt = env_int("MG_FUSED_BT", 0);
+    return bt == 64 || bt == 128 || bt == 192 || bt == 256 ? bt : 0;
+}
+static int forced_waves() {  // 0: not forced
+    static const int waves =
+        getenv("MG_FUSED_WAVES") ? std::max(1, env_int("MG_FUSED_WAVES", 0)) : 0;
+    return waves;
+}
+static bool forced_march() { return forced_bt() || forced_waves(); }
+
 // Workgroup width of the fused passes on a level with N nodes per side: the
 // width that covers a row with the fewest threads, ties to the wider one.
-// MG_FUSED_BT (64, 128, 192 or 256) forces one width for every level.
 int fused_bt(int N) {
-    static const int forced = env_int("MG_FUSED_BT", 0);
-    if (forced == 64 || forced == 128 || forced == 192 || forced == 256) return forced;
+    if (const int forced = forced_bt()) return forced;
     int best = dev::F_MAX_THREADS;
     int64_t best_threads = INT64_MAX;
     for (int bt = dev::F_MAX_THREADS; bt >= dev::F_MIN_THREADS; bt -= 64) {
@@ -1083,17 +1096,22 @@ int64_t fused_max_norm_parts(int N) { return dev::fused_norm_parts(N); }
 
 // Owned rows per chunk of a fused pass over `count` problems on a level with
 // N nodes per side: the longest chunk (a power of two from 64 down to 4)
-// that still gives at least MG_FUSED_WAVES (default 3500, about 14 per
-// compute unit) wavefronts, so that levels with little work keep the device
+// that still gives at least 3500 wavefronts (about 14 per compute unit; or
+// MG_FUSED_WAVES), so that levels with little work keep the device
 // busy and their marching pipelines short, and levels with much work waste
 // little on the recomputed halo rows.  Chunk heights are multiples of
 // F_NORM_ROWS.
 int fused_rh(int N, int bt, int64_t count) {
-    static const int64_t target = std::max(1, env_int("MG_FUSED_WAVES", 3500));
+    const int64_t target = forced_waves() ? forced_waves() : 3500;
     const int64_t per_chunk = count * dev::fused_geom(N, bt, 4).nstrips * (bt / 64);
     int rh = 64;
     while (rh > 4 && per_chunk * ((N + rh - 1) / rh) < target) rh /= 2;
     return rh;
+}
+
+// Whether single_rule takes block tiles (see there).
+static bool block_level(int N, int elem_bytes) {
+    return (int64_t)N * N * 8 * elem_bytes <= (int64_t)160 << 20;
 }
 
 // Tiles of one problem's fused passes on a level without a tuned entry.
@@ -1123,10 +1141,12 @@ int fused_rh(int N, int bt, int64_t count) {
 // FP32 L = 12 113/121 -> 99/103 us; FP64 L = 11 65/73 -> 56/61, L = 12 237/274 ->
 // 211/252 us.
 dev::FusedGeom single_rule(int N, int elem_bytes) {
-    const int64_t n = (int64_t)N * N;
     const bool fp64 = elem_bytes == 8;
-    if (n * 8 * elem_bytes <= (int64_t)160 << 20)
-        return dev::block_geom(N, !fp64 && N > 513 ? 2 : 1);
+    if (forced_march()) {
+        const int bt = fused_bt(N);
+        return dev::fused_geom(N, bt, fused_rh(N, bt, 1));
+    }
+    if (block_level(N, elem_bytes)) return dev::block_geom(N, !fp64 && N > 513 ? 2 : 1);
     static const int kRows[] = {8, 12, 16, 24, 32, 48, 64, 96, 128, 160, 192, 224, 256};
     constexpr int kCus = 256;
     const double lat = fp64 ? 0.68 : 0.55;
@@ -1161,7 +1181,7 @@ dev::FusedGeom single_rule(int N, int elem_bytes) {
 // change of shape captures its graph again).
 dev::FusedGeom batch_rule(int N, int64_t count, bool fixed) {
     const int64_t total = count * N * N;
-    if (fixed ? N <= 1025 : total <= 4000000) {
+    if (!forced_march() && (fixed ? N <= 1025 : total <= 4000000)) {
         if (!fixed && total <= 300000) return dev::block_geom(N, 1);
         int best = 1;
         int64_t best_waves = 0;
@@ -1335,7 +1355,7 @@ hipError_t launch_post(const Level& lv, const T* bands, const T* x, const T* xc,
 // 895 with 12 (972 with 8), so not there.  Mixed L = 6 328 -> 319, L = 8 481 -> 463
 // with W = 8 (472 with 6); L = 10 847 -> 829, L = 11 1651 -> 1610 with 12.
 static int mid_waves(int N, int elem_bytes) {
-    if (!single_rule(N, elem_bytes).blk) return 0;
+    if (!block_level(N, elem_bytes)) return 0;
     if (elem_bytes == 8) return N <= 257 ? 6 : N <= 513 ? 12 : 0;
     return N <= 513 ? 8 : 12;
 }
@@ -1345,7 +1365,7 @@ static int mid_waves(int N, int elem_bytes) {
 // 2.16 ms apart, 1.94 merged; L = 10, block tiles: 0.91 apart, 1.12 with a
 // merged march).
 bool use_mid(int N, int elem_bytes) {
-    return mid_waves(N, elem_bytes) || !single_rule(N, elem_bytes).blk;
+    return mid_waves(N, elem_bytes) || !block_level(N, elem_bytes);
 }
 
 template <typename T>
@@ -1378,7 +1398,7 @@ hipError_t launch_mid(const Level& lv, const T* bands, const T* x, const T* xc, 
 
 // One sweep instead of two (V(1,1) and the like): block tiles of 8 rows, on
 // levels where the rule takes block tiles.
-bool one_sweep_blocks(int N, int elem_bytes) { return single_rule(N, elem_bytes).blk != 0; }
+bool one_sweep_blocks(int N, int elem_bytes) { return block_level(N, elem_bytes); }
 
 template <typename T>
 hipError_t launch_pre1(const Level& lv, const T* bands, const T* x, bool x_zero, const T* b,
