@@ -39,7 +39,8 @@ FUSED_ALG_B = 12 * 4
 FUSED_MIN_B = 8 * 4
 # Sources the fused passes are built from: a counter record taken on other
 # sources is stale.
-TRAFFIC_SOURCES = ["csrc/kernels.hip", "csrc/fused_ops.h", "csrc/device_ops.h",
+TRAFFIC_SOURCES = ["csrc/kernels.hip", "csrc/blas1.hip", "csrc/band4.hip", "csrc/fused_ops.h",
+                   "csrc/block_ops.h", "csrc/mid_ops.h", "csrc/tail_ops.h", "csrc/device_ops.h",
                    "csrc/mg_internal.h", "build.py"]
 
 
