@@ -159,7 +159,7 @@ mg_status mg_hierarchy_assemble(mg_hierarchy* h, void* stream);
  * coarse solve of the single-precision cycles):
  *   MG_COARSE_CHOLESKY (the default): the Cholesky factor of the block of
  *     the nodes off the Dirichlet sides, made by mg_hierarchy_assemble
- *     (single-threaded substitutions: fast up to coarse level 2 or 3);
+ *     (substitutions by one wavefront: fast up to coarse level 2 or 3);
  *   MG_COARSE_CG: unpreconditioned conjugate gradients from a zero iterate
  *     (Sec. 6.2 uses CG for the coarse grid problems), stopping before a step
  *     once ||r|| <= tol ||b|| (r by the recurrence) or after max_iter steps
@@ -275,7 +275,8 @@ typedef struct {
     int level;
     int problems;     /* problems at this level in the tuned composition */
     int tile_rows;    /* chosen rows per tile */
-    int row_waves;    /* chosen wavefronts per workgroup (across a strip's row when marching) */
+    int row_waves;    /* marching: wavefronts across a strip's row; a block tile: 4, a
+                         mark (its workgroup has 4, 6 or 10 by its rows) */
     int tile_cols;    /* 0: marching tile; 32: a block tile */
     double us;        /* one pre + post pass pair with that tile, microseconds;
                          mg_hierarchy_autotune: negative if the choice is not stored */

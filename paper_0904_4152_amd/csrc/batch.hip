@@ -1772,9 +1772,9 @@ extern "C" mg_status mg_batch_set_tile(int level, int problems, int tile_rows, i
     if (problems < 1) return fail(MG_ERR_INVALID, "problems must be >= 1");
     if (tile_cols) {
         if (!dev::block_shape(tile_rows, tile_cols))
-            return fail(MG_ERR_INVALID, "a block tile is 8, 16 or 32 rows by 32 columns");
+            return fail(MG_ERR_INVALID, "a block tile has 8, 16 or 32 rows and tile_cols 32");
         if (row_waves != 0 && row_waves != dev::BLK_TAG_WAVES)
-            return fail(MG_ERR_INVALID, "a block tile has 4 wavefronts (row_waves 0 or 4)");
+            return fail(MG_ERR_INVALID, "row_waves of a block tile is 0 or 4");
         tile_table_set(level, problems, tile_rows, 64 * dev::BLK_TAG_WAVES, tile_cols);
         return MG_OK;
     }

@@ -6,9 +6,9 @@
 // All band-streaming kernels are HBM-bandwidth bound (about 0.2-0.4 flop per
 // byte), so they use no matrix cores: each thread owns 16 contiguous bytes of
 // every band (4 floats or 2 doubles), the x halo of the three grid rows and
-// the lower bands (shifted upper bands) come through L1/L2, and workgroups
-// are renumbered so that each XCD walks a contiguous part of the grid (its L2
-// then sees the row reuse).
+// the lower bands (shifted upper bands) are staged through LDS, on small levels
+// read through L1/L2, and workgroups are renumbered so that each XCD walks a
+// contiguous part of the grid (its L2 then sees the row reuse).
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
