@@ -539,7 +539,11 @@ def main():
     x_mixed = x.cpu().numpy()
     progress("timed step: %.3f ms per mixed solve" % (t_mixed * 1e3))
 
-    st_f = solve(h, b, x, fp64)  # warm the FP64 graphs
+    # warm the FP64 graphs (a hierarchy's first solve goes cycle by cycle, its
+    # second captures the groups of cycles that later ones replay)
+    for _ in range(2):
+        solve(h, b, x, fp64)
+    torch.cuda.synchronize()
     t0 = time.perf_counter()
     nf = 2
     for _ in range(nf):
