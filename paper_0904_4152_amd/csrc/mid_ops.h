@@ -7,9 +7,10 @@
 // read once (5 bands, b, the iterate; two iterates written: 9 words), and the
 // third sweep shares its band product with the norm.  At L = 12 the pair took
 // 482 us in FP64 and 237 us in FP32, near the rate cold copies reach; merged
-// 320 and 165 us, now closer to the instruction stream of its row step (about
-// 380 instructions a wavefront; LDS busy 42 % of the time) than to memory
-// (270 and 135 us with the halo).
+// 320 and 163 us.  Memory would take 270 and 135 us with the halo; a row step is
+// about 270 (FP64) and 190 (FP32) instructions a wavefront, LDS is busy 43 and
+// 50 % of the time, and two or three wavefronts a SIMD (249 and 149 registers)
+// spend half of theirs waiting.
 #pragma once
 
 #include <utility>
