@@ -11,10 +11,10 @@ pytestmark = pytest.mark.gpu
 
 
 def seconds(h, b, x, opts, before=lambda: None):
-    """Shortest of seven calls that find x solved, to the end of what they queued,
+    """Shortest of fifteen calls that find x solved, to the end of what they queued,
     after `before` each time."""
     best = 1.0
-    for _ in range(7):
+    for _ in range(15):
         before()
         torch.cuda.synchronize()
         t = time.perf_counter()
