@@ -194,11 +194,21 @@ class Context:
         h = _vp()
         check(lib().mg_context_create(device, budget_bytes, ctypes.byref(h)))
         self._h = h
+        self._users = 0  # hierarchies and servers alive: they use the context to their end
+        self._closing = False
         self.device = device
 
     @property
     def handle(self):
         return self._h
+
+    def _hold(self):
+        self._users += 1
+
+    def _drop(self):
+        self._users -= 1
+        if self._closing:
+            self.close()
 
     def memory(self):
         a, b = _sz(), _sz()
@@ -253,7 +263,10 @@ class Context:
         return out.value
 
     def close(self):
-        if self._h:
+        """Destroy the context, with the last hierarchy or server on it (a
+        collector of garbage cycles finalises objects in any order)."""
+        self._closing = True
+        if self._h and not self._users:
             lib().mg_context_destroy(self._h)
             self._h = None
 
@@ -279,6 +292,7 @@ class Hierarchy:
         check(lib().mg_hierarchy_create_bc(ctx.handle, L, coarse_level, jitter, seed, xy_ptr,
                                            dirichlet_sides, ctypes.byref(h)))
         self._h = h
+        ctx._hold()
         self.dirichlet_sides = dirichlet_sides
         self.ctx = ctx
         self.L = L
@@ -306,6 +320,7 @@ class Hierarchy:
         if self._h:
             lib().mg_hierarchy_destroy(self._h)
             self._h = None
+            self.ctx._drop()
 
     def __del__(self):
         try:
@@ -479,6 +494,7 @@ class Server:
                                      ctypes.byref(h)))
         self._h = h
         self.ctx = ctx
+        ctx._hold()
 
     def submit(self, L, rel_tol, jitter, geom_seed, rhs_seed, keep_x=False) -> int:
         t = _u64()
@@ -517,6 +533,7 @@ class Server:
         if self._h:
             check(lib().mg_server_destroy(self._h))
             self._h = None
+            self.ctx._drop()
 
     def __del__(self):
         try:
